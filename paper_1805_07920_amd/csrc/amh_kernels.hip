@@ -242,7 +242,12 @@ struct WinStats {
 // constants (1 / W_r, W_r / W_<=r, W_<r W_r / W_<=r, A_r) with W_r the row's
 // weight sum and A_r its sum of w (a - mean); they let the source moments be
 // formed row by row and merged exactly (see ncc_cost).
-constexpr int kWinStride = 48;  // float2 units: 36 + 6 float4
+// The blocks are 100 dwords apart (4 of them padding): the 7 pixels of a half-pass wave, or the 16 cells of a sweep
+// wave, read the same entry of their blocks in one 16-byte access, and 100 mod 64 = 36 puts 16 consecutive blocks on
+// disjoint groups of 4 of the 64 LDS banks.  At 96 dwords they met on two groups: the sweep spent 98 % of its cycles
+// in LDS, 86 % of them conflicts (1920x1280, 4 sources: 2.95 -> 2.1 ms), the half-pass 65 %, two thirds of them
+// conflicts (1920x1280, 10 sources: 3.95 -> 3.90 ms, the vector ALU and the texture path bind it).
+constexpr int kWinStride = 50;  // float2 units: 36 + 6 float4 + 2 of padding
 
 // Computes a pixel's window block and hands each entry to the sink: sink.sample(s, (w, w (a - mean))) for the
 // 36 samples, sink.row(r, constants) for the 6 rows.
@@ -338,10 +343,14 @@ __device__ __forceinline__ WinStats build_window(const Reader &rd, const MethodD
     return build_window_to(rd, m, sink);
 }
 
-// Reader of a window block in LDS for the source loop.
+// Reader of a window block in LDS for the source loop: two samples per 16-byte read (18 + 6 LDS instructions per
+// evaluation instead of 36 + 6).
 struct LdsWin {
     const float2 *__restrict__ rw;
-    __device__ __forceinline__ float2 sample(int s) const { return rw[s]; }
+    __device__ __forceinline__ float2 sample(int s) const {
+        const gf4 v = reinterpret_cast<const gf4 *>(rw)[s >> 1];
+        return (s & 1) ? make_float2(v.z, v.w) : make_float2(v.x, v.y);
+    }
     __device__ __forceinline__ float4 row(int r) const { return reinterpret_cast<const float4 *>(rw + 36)[r]; }
 };
 
