@@ -34,13 +34,6 @@ METRIC = "hypothesis·view NCC evals/s; sec per depth map at equal accuracy vs p
 # shift-subtract, w*b and 3 moment accumulations (5) = 26; x 36, + ~20 for the epilogue (variances,
 # rsqrt, clamp) + ~15 for the warp from the plane -> ~950.  The roofline fraction is taken on this count.
 OPS_PER_EVAL = 950
-# What this implementation issues per evaluation, counted on its instruction stream in full-rate slots (one
-# wave instruction every 2 clocks per SIMD, the rate of v_add_f32 / v_fma_f32 with vector-register operands;
-# bench.py --calibrate-valu measures each kind): 621 full-rate fp32 instructions, 284 at half rate
-# (conversions, fractions, clamps, integer address arithmetic, fp64 set-up, fp32 instructions reading a
-# scalar register: 2 slots each) and 38 reciprocals at quarter rate (4 slots) -> 1341.  Reported beside the
-# fraction as the issue-slot figure.
-ISSUE_SLOTS_PER_EVAL = 1341
 # MI355X: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz = 78.6 T fp32 lane-operations/s (157.3 TFLOP/s with an FMA
 # counted as two): unpacked v_add_f32 issues at 91 % of it and v_fma_f32 at 72 % (bench.py --calibrate-valu)
 VALU_PEAK_OPS = 256 * 128 * 2.4e9
@@ -793,6 +786,9 @@ def main():
                    "width": W, "height": H, "n_src": n, "iters": cfg["iters"], "refine": cfg["refine"],
                    "seed": args.seed, "parallelism": "single GPU"},
         "sec_per_depth_map": ms_per_step / 1000.0,
+        "value_basis": "the method's evaluations per second: a plane that several regions of a pixel hold counts for "
+                       "each and the pixel's own plane on every view, as the counters do, though equal ones share one "
+                       "computation and costs that nothing reads are not computed; ms_per_step is the wall clock",
         # the same rate over the evaluations that took their 36 samples (those decided by the range and
         # visibility tests alone are counted in value, as the library performs them)
         "sampled_evals_per_s": (ev["evals_total"] - ev["evals_short"] - ev["evals_init_short"]) / (ms_per_step / 1000.0),
@@ -813,11 +809,11 @@ def main():
                                f"(fused checkerboard half-pass, {2 if best_cfg & 4 else 4}-row tiles)",
                      "ops_per_eval": OPS_PER_EVAL, "evals_per_launch": evals_per_pass,
                      "sampled_evals_per_launch": sampled_per_pass,
-                     "achieved_basis": "evaluations that took their 36 samples x ops_per_eval (algorithmic) / "
-                                       "mean launch time",
-                     "issue_slots_per_eval": ISSUE_SLOTS_PER_EVAL,
-                     "issue_slot_frac": sampled_per_pass * ISSUE_SLOTS_PER_EVAL / (avg_pass_ms / 1000.0)
-                                        / VALU_PEAK_OPS},
+                     # what the method asks for, not what the kernel executes: evaluations shared between regions
+                     # that hold the same plane, and the own planes' on views without weight, are counted
+                     "achieved_basis": "the method's evaluations of propagated and own planes (shared or unread ones "
+                                       "included) and the scored refinement evaluations, those decided before any "
+                                       "sample left out, x ops_per_eval (algorithmic) / mean launch time"},
         "speedup_vs_plain": learned["speedup_vs_plain"] if learned else None,
         "equal_accuracy": learned["equal_accuracy"] if learned else None,
         "learned_vs_plain": learned,

@@ -114,8 +114,11 @@ typedef struct {
 typedef struct {
     uint64_t evals_total;       /* hypothesis x view NCC evaluations (36 samples each) */
     uint64_t evals_init;        /* ... in the random initialisation */
-    uint64_t evals_propagation; /* ... of the 8 propagated planes and the pixel's own */
-    uint64_t evals_refine;      /* ... of refinement candidates */
+    uint64_t evals_propagation; /* ... of the 8 propagated planes and the pixel's own, on every view (a plane that
+                                 * several regions hold counts for each, the pixel's own also on views without
+                                 * weight, though such evaluations are shared or left out) */
+    uint64_t evals_refine;      /* ... of refinement candidates, as far as they were scored (a candidate out of the
+                                 * running after its first view is not scored on the others) */
     int n_passes;
     float ms_per_pass[64];      /* device time of each half-pass (timing = 1), else 0 */
     float ms_init;

@@ -219,12 +219,13 @@ PassArgs pass_args(amh_ctx *c, int t, int colour) {
     a.colour = colour;
     const int W = c->refdev.W, H = c->refdev.H;
     const int per_row = (W + 1) / 2;  // same-colour pixels per row (upper bound)
-    a.tiles_x = (per_row + kTilePix - 1) / kTilePix;
-    const int tiles_y = (H + c->cfg_waves - 1) / c->cfg_waves;
-    a.n_tiles = a.tiles_x * tiles_y;
+    const int tile_pix = ablation_build(a.m) ? kTilePix : kPix;
+    a.tiles_x = (per_row + tile_pix - 1) / tile_pix;
+    a.rows = c->cfg_rows;
+    if (!ablation_build(a.m) && a.tiles_x * ((H + 3) / 4) <= kSmallTiles) a.rows = 1;
+    a.n_tiles = a.tiles_x * ((H + a.rows - 1) / a.rows);
     a.counters = c->counters;
     a.order = c->cfg_order;
-    a.waves = c->cfg_waves;
     return a;
 }
 
@@ -293,7 +294,7 @@ constexpr int kTuneConfigs = 16;
 void apply_config(amh_ctx *c, int cfg) {
     c->cfg_order = cfg & 1;
     c->cfg_job_order = (cfg >> 1) & 1;
-    c->cfg_waves = (cfg & 4) ? 2 : kDefaultTileRows;
+    c->cfg_rows = (cfg & 4) ? 2 : kDefaultTileRows;
     c->cfg_persist = (cfg >> 3) & 1;
 }
 
@@ -412,8 +413,8 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
         b.view_off = so;
         b.n_src = jobs[j].n_src;
         b.st = StateDev{c->jobs[j].planes, c->jobs[j].cost, c->jobs[j].S, c->jobs[j].v};
-        b.tiles_x = ((r.W + 1) / 2 + kTilePix - 1) / kTilePix;
-        b.n_tiles = b.tiles_x * ((r.H + c->cfg_waves - 1) / c->cfg_waves);
+        b.tiles_x = ((r.W + 1) / 2 + kPix - 1) / kPix;
+        b.n_tiles = b.tiles_x * ((r.H + c->cfg_rows - 1) / c->cfg_rows);
         b.n_iblocks = (int)init_blocks(r.W, r.H);
         b.prop = proposal ? c->jobs[j].pred : nullptr;
         b.prop_w = proposal ? cell_rows(r.W) : 0;
@@ -433,8 +434,8 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
     // A half-pass is launched once per LDS class: workgroups whose sources need less LDS fit more of them on
     // a CU (160 KB), so the jobs of a phase are grouped by how many workgroups per CU their view count
     // allows (capped at 4 waves per SIMD); one launch per group, largest occupancy first.
-    const int wg_cap = 16 / c->cfg_waves;
-    auto wg_per_cu = [&](int n) { return std::min(wg_cap, (int)((size_t)160 * 1024 / pass_lds_bytes(n, c->cfg_waves))); };
+    const int wg_cap = 16 / tile_waves(c->cfg_rows);
+    auto wg_per_cu = [&](int n) { return std::min(wg_cap, (int)((size_t)160 * 1024 / pass_lds_bytes(n, c->cfg_rows))); };
     auto add_group = [&](int kind, int colour, int t, const std::vector<int> &act) {
         Phase ph{kind, colour, t, 0, 0, (int)tab.size(), 0, 0};
         ph.n_active = (int)act.size();
@@ -529,7 +530,7 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
         int cus = 0, khz = 0;
         HIPCHK(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
         HIPCHK(c, hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device));
-        const int per_cu = persist_blocks_per_cu(c->half, c->cfg_waves, max_src);
+        const int per_cu = persist_blocks_per_cu(c->half, c->cfg_rows, max_src);
         if (per_cu < 1 || cus < 1 || khz <= 0)
             return fail(c, AMH_E_UNSUPPORTED, "persistent batch: no resident workgroup fits (%d per CU)", per_cu);
         int most_tiles = 0;
@@ -581,19 +582,19 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
         // shape by a probe launch of the same kernel (residency can also be limited by scratch or reserved CUs)
         int resident = -1;
         for (const auto &r : c->persist_resident)
-            if (r[0] == c->half && r[1] == c->cfg_waves && r[2] == max_src && r[3] == p_grid) resident = r[4];
+            if (r[0] == c->half && r[1] == c->cfg_rows && r[2] == max_src && r[3] == p_grid) resident = r[4];
         if (resident < 0) {
             PersistArgs probe = pa;
             probe.probe = 1;
             HIPCHK(c, launch_zero_u64(d_psync, (int)n_psync, c->stream));
             HIPCHK(c, hipMemcpyAsync(d_pargs, &probe, sizeof probe, hipMemcpyHostToDevice, c->stream));
-            HIPCHK(c, launch_persist(d_pargs, c->half, c->cfg_waves, max_src, p_grid, c->stream));
+            HIPCHK(c, launch_persist(d_pargs, c->half, c->cfg_rows, max_src, p_grid, c->stream));
             unsigned peak = 0;
             HIPCHK(c, hipMemcpyAsync(&peak, reinterpret_cast<unsigned *>(d_psync) + 2, sizeof peak,
                                      hipMemcpyDeviceToHost, c->stream));
             HIPCHK(c, hipStreamSynchronize(c->stream));
             resident = (int)peak;
-            c->persist_resident.push_back({c->half, c->cfg_waves, max_src, p_grid, resident});
+            c->persist_resident.push_back({c->half, c->cfg_rows, max_src, p_grid, resident});
         }
         if (resident < p_grid) p_grid = (resident / 8) * 8;
         if (p_grid < 8)
@@ -633,14 +634,14 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
         b.colour = ph.colour;
         b.kind = ph.kind;
         b.order = c->cfg_order;
-        b.waves = c->cfg_waves;
+        b.rows = c->cfg_rows;
         b.conf_min = c->p.conf_min;
         b.counters = c->d_bcount;
         b.tiles_done = tiles_done;
         b.job_end = clocks;
         e = launch_batch(b, c->half, ph.max_src, c->cap_stream);
     }
-    if (e == hipSuccess && n_pp > 0) e = launch_persist(d_pargs, c->half, c->cfg_waves, max_src, p_grid, c->cap_stream);
+    if (e == hipSuccess && n_pp > 0) e = launch_persist(d_pargs, c->half, c->cfg_rows, max_src, p_grid, c->cap_stream);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(c->cap_stream, &g);
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -1105,7 +1106,7 @@ static amh_status run_batch_impl(amh_ctx *c, int n_jobs, const amh_job *jobs, bo
     if (proposal && !c->net) return fail(c, AMH_E_STATE, "no proposal network (amh_nn_init or amh_nn_load)");
     if (c->p.sym_prop || c->p.heuristic_views)
         return fail(c, AMH_E_UNSUPPORTED, "the ablation modes run on the single-image path only");
-    std::vector<int> key = {n_jobs, c->cfg_order, c->cfg_job_order, c->cfg_waves, c->cfg_persist, proposal ? 1 : 0};
+    std::vector<int> key = {n_jobs, c->cfg_order, c->cfg_job_order, c->cfg_rows, c->cfg_persist, proposal ? 1 : 0};
     for (int j = 0; j < n_jobs; ++j) {
         key.push_back(jobs[j].ref);
         key.push_back(jobs[j].n_src);

@@ -70,7 +70,7 @@ struct amh_ctx {
     // launch configuration (autotuned): tile order of a launch, job order of a batch
     int cfg_order = 0;
     int cfg_job_order = 1;
-    int cfg_waves = kDefaultTileRows;  // tile rows of the half-pass (2 or 4)
+    int cfg_rows = kDefaultTileRows;  // tile rows of the half-pass (2 or 4)
     int cfg_persist = 0;               // batches: every half-pass in one persistent launch (1) or one launch each
     // batch: per-job state, device tables and the captured graph of the last job list
     std::vector<JobResult> jobs;

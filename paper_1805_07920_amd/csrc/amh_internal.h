@@ -15,12 +15,20 @@ constexpr int kMaxImageSide = 16383 - 2 * kQuadPad;
 constexpr int kCounterSlots = 256;    // eval counters are spread over slots to avoid one hot atomic
 constexpr int kCounterKinds = 6;      // init, propagation, refinement evaluations; proposal fallbacks;
                                        // short evaluations (no samples taken) of the half-pass and of init
-constexpr int kGroups = 7;            // pixels per wave (7 groups x 9 lanes = 63 lanes)
-constexpr int kRows = 9;              // 8 propagated hypotheses + the pixel's own
-constexpr int kTilePix = kGroups;     // same-colour pixels per tile row
-// image rows per workgroup tile of the half-pass (one wave per row): 4 by default, 2 as the
-// autotuner's alternative tile shape
+constexpr int kPix = 8;               // half-pass: same-colour pixels per tile row (a wave: 8 pixels x 8 regions)
+constexpr int kGroups = 7;            // ablation build: pixels per wave (7 groups x 9 lanes = 63 lanes)
+constexpr int kRows = 9;              // ... 8 propagated hypotheses + the pixel's own
+constexpr int kTilePix = kGroups;     // ... same-colour pixels per tile row
+// image rows per workgroup tile of the half-pass: 4 by default, 2 as the autotuner's alternative tile shape
 constexpr int kDefaultTileRows = 4;
+// waves of a half-pass workgroup with a tile of `rows` image rows: one per row, and four for the one-row tile of small
+// references, whose evaluations they share
+constexpr int tile_waves(int rows) { return rows == 2 ? 2 : 4; }
+// A reference with at most this many 4-row tiles of a colour takes one-row tiles: fewer workgroups than the card's 256
+// CUs leave most of them idle, and a pass lasts as long as one workgroup's chain of evaluations, which four waves on
+// one row shorten (128x96, 4 sources, 192 tiles: 219 -> 174 us for 3 iterations; 200x150, 6 sources, 494 tiles: 404
+// us, one-row tiles 509).
+constexpr int kSmallTiles = 256;
 
 // One source view relative to the current reference (Sec. 3.3: plane-induced warp).
 // Homogeneous source pixel of reference pixel (x, y) on the plane with inverse
@@ -51,6 +59,9 @@ struct MethodDev {
     double q_lo, q_hi;           // inverse depths of d_max (1 + 1e-5) and d_min (1 - 1e-5): the range test
 };
 
+// the launches of these parameters run the ablation build of the half-pass
+inline bool ablation_build(const MethodDev &m) { return m.sym_prop || m.heuristic; }
+
 struct StateDev {
     float4 *planes;              // H x W (n_x, n_y, n_z, d)
     float *cost;
@@ -68,7 +79,7 @@ struct PassArgs {
     int tiles_x, n_tiles;        // tile grid of this colour
     unsigned long long *counters;  // [kCounterKinds][kCounterSlots], kinds as listed at kCounterKinds
     int order;                   // tile order: 0 XCD bands, 1 hardware order
-    int waves = kDefaultTileRows;  // tile rows = waves per workgroup (2 or 4)
+    int rows = kDefaultTileRows;  // image rows of a tile (half-pass: 1, 2 or 4; ablation build: 2 or 4)
     // initialisation from per-cell predictions (NULL: random initialisation)
     const float *prop = nullptr;  // [prop_h][prop_w][5]: depth, normal (3), confidence
     int prop_w = 0, prop_s = 0;   // cell grid width, cell size in reference pixels
@@ -107,7 +118,7 @@ struct BatchPhaseArgs {
     MethodDev m;
     int t, colour, kind;         // kind 0: init, 1: half-pass
     int order;
-    int waves;                   // tile rows = waves per workgroup (2 or 4)
+    int rows;                    // image rows of a tile (2 or 4)
     float conf_min;              // proposal initialisation threshold
     unsigned long long *counters;
     unsigned long long *tiles_done;  // [n_jobs] tiles finished in the job's last phase
@@ -182,8 +193,8 @@ hipError_t launch_pack_quads(const float *img, int W, int H, void *quads, int ha
 hipError_t launch_zero_u64(unsigned long long *p, int n, hipStream_t s);
 hipError_t launch_init(const PassArgs &a, int half, hipStream_t s);
 hipError_t launch_pass(const PassArgs &a, int half, hipStream_t s);
-hipError_t launch_persist(const PersistArgs *a, int half, int waves, int max_src, int grid, hipStream_t s);
-int persist_blocks_per_cu(int half, int waves, int max_src);
+hipError_t launch_persist(const PersistArgs *a, int half, int rows, int max_src, int grid, hipStream_t s);
+int persist_blocks_per_cu(int half, int rows, int max_src);
 hipError_t launch_pack_hypotheses(const float *depth, const float *normal, const float *conf, int64_t n, float *out,
                                   hipStream_t s);
 hipError_t launch_score(const ScoreArgs &a, int half, hipStream_t s);
@@ -192,6 +203,6 @@ hipError_t launch_outputs(const RefDev &ref, const StateDev &st, float *depth, f
 hipError_t launch_batch(const BatchPhaseArgs &b, int half, int max_src, hipStream_t s);
 hipError_t launch_stamp(unsigned long long *p, hipStream_t s);
 hipError_t launch_sweep(const SweepArgs &a, int half, hipStream_t s);
-size_t pass_lds_bytes(int n_src, int waves, int rb = 1);
+size_t pass_lds_bytes(int n_src, int rows);
 
 }  // namespace amh

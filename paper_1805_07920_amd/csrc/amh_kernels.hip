@@ -1,16 +1,14 @@
 // gfx950 kernels of the checkerboard PatchMatch pass (Xu & Tao, arXiv 1805.07920).
 //
-// Work mapping of the pass (Sec. 3.1-3.3): a wave64 holds 7 pixels of one
-// colour on one image row, 9 lanes each.  Lane r < 8 owns the hypothesis
-// propagated from asymmetric region r, lane 8 the pixel's own plane; the
-// 64th lane idles.  All lanes of a wave warp into the same source view at the
-// same time, so their bilinear gathers hit neighbouring texels.  A workgroup
-// (4 waves) covers a tile of 4 rows x 7 same-colour pixels; its reference
-// window (tile + 5 px halo) is staged once in LDS.  The 9 x N cost matrix of a
-// pixel lives in LDS, one column per view; view selection is split over the
-// 9 lanes of the pixel and the final argmin is a 9-lane reduction.  MFMA is
-// not used: the work is per-sample gathers and scalar arithmetic, bounded by
-// the vector ALU.
+// Work mapping of the pass (Sec. 3.1-3.3): a workgroup covers a tile of 4 rows
+// x 8 same-colour pixels, 8 lanes per pixel, lane r picking the candidate of
+// asymmetric region r.  The tile's distinct hypotheses are listed and scored
+// 64 at a time, all lanes of a wave warping into the same source view, so that
+// their bilinear gathers hit neighbouring texels; the reference window (tile +
+// 5 px halo) is staged once in LDS, where the 8 x N cost matrix of a pixel
+// lives too; view selection and the final argmin are split over the pixel's
+// lanes.  MFMA is not used: the work is per-sample gathers and scalar
+// arithmetic, bounded by the vector ALU and the texture path.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -526,6 +524,20 @@ __device__ __forceinline__ float ncc_cost_win(const ViewDev &vw, const Win &rw, 
     return cost_from_moments(ws, m2, cab);
 }
 
+// The constants of view j, j the same in the whole wave, by scalar loads (nothing writes the table during a launch)
+__device__ __forceinline__ ViewDev uniform_view(const ViewDev *views, int j) {
+    const auto *v = (const __attribute__((address_space(4))) ViewDev *)views + j;
+    ViewDev r;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) r.A[i] = v->A[i];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r.b[i] = v->b[i];
+    r.quads = v->quads;
+    r.W = v->W;
+    r.H = v->H;
+    return r;
+}
+
 template <int HALF, bool SPLIT = true>
 __device__ __forceinline__ float ncc_cost_raw(const ViewDev &vw, const float2 *__restrict__ rw, const WinStats &ws,
                                               int x, int y, double q0, float qu, float qv) {
@@ -764,7 +776,7 @@ __host__ __device__ inline size_t lds_layout(int n_src, int waves, size_t off[13
     return o;
 }
 
-size_t pass_lds_bytes(int n_src, int waves, int rb) {
+size_t ablation_lds_bytes(int n_src, int waves, int rb) {
     size_t off[13];
     return lds_layout(n_src, waves, off, rb);
 }
@@ -790,16 +802,17 @@ __device__ __forceinline__ PassLds carve(unsigned char *smem, int n_src, int wav
 }
 
 // reference tile of a workgroup: rows y0-5 .. y0+WAVES+4, cols x0-5 .. x0+2*kTilePix+4, clamped
-template <int WAVES>
+template <int ROWS, int WAVES, int TW>
 __device__ __forceinline__ void stage_tile(const RefDev &ref, float *tile, int y0, int x0, int tid) {
-    for (int i = tid; i < (WAVES + 10) * kTileW; i += 64 * WAVES) {
-        const int ty = i / kTileW, tx = i - ty * kTileW;
+    for (int i = tid; i < (ROWS + 10) * TW; i += 64 * WAVES) {
+        const int ty = i / TW, tx = i - ty * TW;
         const int gy = min(max(y0 - 5 + ty, 0), ref.H - 1);
         const int gx = min(max(x0 - 5 + tx, 0), ref.W - 1);
         tile[i] = glob(ref.img)[(size_t)gy * ref.W + gx];
     }
 }
 
+template <int TW>
 struct TileReader {
     const float *tile;
     int cy, cx;  // pixel position inside the tile
@@ -808,7 +821,7 @@ struct TileReader {
     __device__ __forceinline__ float operator()(int du, int dv) const {
         // clamp to the image exactly like the global reader: positions are clamped in image space
         const int gx = min(max(x + du, 0), ref->W - 1), gy = min(max(y + dv, 0), ref->H - 1);
-        return tile[(cy + (gy - y)) * kTileW + (cx + (gx - x))];
+        return tile[(cy + (gy - y)) * TW + (cx + (gx - x))];
     }
 };
 
@@ -1015,7 +1028,8 @@ __device__ __forceinline__ void std_offset(int R, int &dx, int &dy) {
 }
 constexpr int kStdRows = 20;  // propagated rows of the standard symmetric pattern; row 20 is the own plane
 
-// ABL: the ablation build of the pass, with the two switches of Sec. 4 read at run
+// The ablation build of the pass: 9 lanes per pixel (8 rows and the own plane) every one of which scores its own
+// plane on every view, with the two switches of Sec. 4 read at run
 // time: m.sym_prop (symmetric checkerboard propagation: 1, region r holds the one
 // neighbour at distance 1 (r < 4) or 5 (r >= 4) up/down/left/right, the fast
 // pattern of Fig. 2(c); 2, the 20 neighbours of the standard pattern of
@@ -1025,10 +1039,10 @@ constexpr int kStdRows = 20;  // propagated rows of the standard symmetric patte
 // candidate, costs the mean of its own k lowest per-view costs; no selection memory).
 // tid: threadIdx.x (the persistent launch passes it through an opaque copy, so that nothing derived from
 // it is kept live across its tiles)
-template <int HALF, int WAVES, bool ABL = false>
-__device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned char *smem, int tid) {
+template <int HALF, int WAVES>
+__device__ __forceinline__ void ablation_body(const PassArgs &a, int L, unsigned char *smem, int tid) {
     // row blocks: 3 in the standard symmetric pattern (ablation build only), else 1
-    const bool stdp = ABL && a.m.sym_prop == 2;
+    const bool stdp = a.m.sym_prop == 2;
     const int RB = stdp ? 3 : 1;
     PassLds S = carve(smem, a.n_src, WAVES, RB);
     constexpr int WL = 64 * WAVES;  // entries per row block of pl, valid, mf
@@ -1045,7 +1059,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
     const int N = a.n_src;
     const MethodDev &m = a.m;
 
-    stage_tile<WAVES>(a.ref, S.tile, y0, x0, tid);
+    stage_tile<WAVES, WAVES, kTileW>(a.ref, S.tile, y0, x0, tid);
 
     // (1) asymmetric propagation: lane r < 8 takes the lowest-cost candidate of region r
     float4 pl = make_float4(0.f, 0.f, -1.f, 1.f);
@@ -1071,7 +1085,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             S.valid[b * WL + tid] = vb ? 1 : 0;
         }
     } else if (pix_ok) {
-        if (ABL && m.sym_prop && row < 8) {
+        if (m.sym_prop && row < 8) {
             const int u = row < 4 ? 1 : 5, dir = row & 3;
             const int nx = x + (dir == 2 ? -u : (dir == 3 ? u : 0));
             const int ny = y + (dir == 0 ? -u : (dir == 1 ? u : 0));
@@ -1122,7 +1136,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
     float2 *rw = S.rw + (wave * kGroups + g) * kWinStride;
     WinStats ws = {1.f, 0.f};
     if (pix_ok) {
-        TileReader rd{S.tile, 5 + wave, 5 + (x - x0), &a.ref, x, y};
+        TileReader<kTileW> rd{S.tile, 5 + wave, 5 + (x - x0), &a.ref, x, y};
         ws = build_window(rd, m, rw, row, kRows);
     }
     __syncthreads();
@@ -1162,7 +1176,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
     //     good view: more than n1 costs below tau and fewer than n2 above tau_up;
     //     importance: mean confidence exp(-m^2 / (2 beta^2)) over the valid rows
     float *psi = S.psi + (wave * kGroups + g) * kMaxSrc;
-    const bool heur = ABL && m.heuristic;  // uniform over the launch
+    const bool heur = m.heuristic != 0;  // uniform over the launch
     int nv = 0;
     if (stdp) {
         // 20 propagated rows: row i in block i / 9, lane row i % 9; counts against n R / 8
@@ -1370,9 +1384,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
         __syncthreads();
         // The (candidate, active view) pairs of a wave's 7 pixels, numbered pixel by pixel, spread over all 64
         // lanes (pixels with more active views no longer hold the wave for extra rounds); results go to the
-        // pixel's area of its wave's cost-matrix LDS (7 * 6N <= 64N).  Float32 sources (the method's build): each
-        // wave runs its own full rounds of 64; the pairs of the waves' last, partial rounds are pooled over the workgroup and
-        // taken 64 at a time, wave w taking the w-th chunk, so that the partial rounds do not each cost a round.
+        // pixel's area of its wave's cost-matrix LDS (7 * 6N <= 64N).
         const auto ref_pair = [&](int w2, int h, int loc, int yrow) {
             const int base = w2 * kGroups + h;
             const int nwh = S.gnw[w2 * 8 + h];
@@ -1393,78 +1405,17 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             *dst = wj * cost;
             ++n_ref;
         };
-        if constexpr (HALF || ABL) {
-            // float16 sources and the ablation build: each wave takes its own pairs, its last round partial
-            // (pooling measured slower in both: with many sources and candidates the waves' last rounds are
-            // nearly full already, and the ablation build's code generation suffers)
-            int start[kGroups + 1];
-            start[0] = 0;
-#pragma unroll
-            for (int h = 0; h < kGroups; ++h)
-                start[h + 1] = start[h] + ncand * __builtin_amdgcn_readfirstlane(S.gnw[wave * 8 + h]);
-            const int yrow = __builtin_amdgcn_readfirstlane(y);
-            for (int qi = lane; qi < start[kGroups]; qi += 64) {
-                int h = 0;
-#pragma unroll
-                for (int k = 1; k < kGroups; ++k) h += qi >= start[k];
-                ref_pair(wave, h, qi - start[h], yrow);
-            }
-        } else {
-        // pair counts of every wave's pixels (wave-uniform), and the pool of the waves' partial rounds
-        int tot[WAVES], pool[WAVES + 1];
-        pool[0] = 0;
-#pragma unroll
-        for (int w2 = 0; w2 < WAVES; ++w2) {
-            int acc = 0;
-#pragma unroll
-            for (int h = 0; h < kGroups; ++h) acc += ncand * __builtin_amdgcn_readfirstlane(S.gnw[w2 * 8 + h]);
-            tot[w2] = acc;
-            pool[w2 + 1] = pool[w2] + (acc & 63);
-        }
-        // this wave's prefix of pair counts over its pixels (wave-uniform), for the decode of its own rounds
         int start[kGroups + 1];
         start[0] = 0;
 #pragma unroll
         for (int h = 0; h < kGroups; ++h)
             start[h + 1] = start[h] + ncand * __builtin_amdgcn_readfirstlane(S.gnw[wave * 8 + h]);
-        const int own_full = start[kGroups] >> 6;
-        // rounds of this wave: its own full rounds, then pool chunks wave, wave + WAVES, ...
-        const int nchunks = (pool[WAVES] + 63) >> 6;
-        const int rounds = own_full + (nchunks > wave ? (nchunks - wave + WAVES - 1) / WAVES : 0);
-        for (int rd = 0; rd < rounds; ++rd) {
-            int w2 = wave, h = 0, loc;
-            if (rd < own_full) {
-                const int qi = rd * 64 + lane;
+        const int yrow = __builtin_amdgcn_readfirstlane(y);
+        for (int qi = lane; qi < start[kGroups]; qi += 64) {
+            int h = 0;
 #pragma unroll
-                for (int k = 1; k < kGroups; ++k) h += qi >= start[k];
-                loc = qi - start[h];
-            } else {
-                // pair pi of the pool belongs to wave w2, at its index (full rounds of w2) + (pi - pool[w2]);
-                // the pixel h of wave w2 whose pairs hold that index, from w2's pair counts
-                const int pi = (wave + (rd - own_full) * WAVES) * 64 + lane;
-                if (pi >= pool[WAVES]) continue;
-                int first = 0, fullw = 0;
-#pragma unroll
-                for (int k = 0; k < WAVES; ++k)
-                    if (pi >= pool[k]) {
-                        w2 = k;
-                        first = pool[k];
-                        fullw = tot[k] & ~63;
-                    }
-                const int qi = fullw + (pi - first);
-                int hs = 0, acc = 0;
-#pragma unroll
-                for (int k = 0; k < kGroups; ++k) {
-                    acc += ncand * S.gnw[w2 * 8 + k];
-                    if (qi >= acc) {
-                        h = k + 1;
-                        hs = acc;
-                    }
-                }
-                loc = qi - hs;
-            }
-            ref_pair(w2, h, loc, y0 + w2);
-        }
+            for (int k = 1; k < kGroups; ++k) h += qi >= start[k];
+            ref_pair(wave, h, qi - start[h], yrow);
         }
         __syncthreads();
         if (pix_ok) {
@@ -1511,15 +1462,889 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
 }
 
 // ---------------------------------------------------------------------------
+// The method's half-pass.  A workgroup holds a tile of ROWS image rows of 8
+// same-colour pixels; lane 8 g + r of wave w < ROWS belongs to pixel g of row
+// w and picks the candidate of region r; all its waves share the evaluations.
+//
+// What is scored, and why not more: the half-pass is bound by the evaluations
+// (vector ALU and texture path each ~75 % busy), so every cost that is known
+// already or that nothing reads is left out -- the results stay the same bit
+// for bit.  1920x1280, 10 sources, 3 iterations: 3.90 ms (9 lanes per pixel,
+// each scoring its plane on every view) -> 3.3 ms mean, 4.97 ms on random
+// planes and 2.8 ms in the last; depth map 24.5 -> 21.0 ms; 3200x2130, 20
+// float16 sources: 23.9 -> 22.2 ms.
+//   - Regions that hold the same plane (the best planes spread: 10 % of the
+//     candidates in the second half-pass, 25 % in the sixth at 1920x1280)
+//     share one evaluation: the distinct (pixel, plane) hypotheses of the
+//     workgroup are listed and taken 64 at a time, a lane each.
+//   - The pixel's own plane takes no part in the view selection, so it waits
+//     for the weights and is scored on the views that carry weight (about 4),
+//     not at all when a region holds the same plane.
+//   - A refinement candidate is scored on the pixel's most important view
+//     first; the weighted costs are not negative, so a candidate whose cost on
+//     that view alone reaches the kept plane's is out (rounding is monotone:
+//     the sum in view order cannot come out below one of its terms).
+//
+// Work items.  A full chunk of 64 hypotheses is scored view by view, the
+// view's constants in scalar registers and its texels addressed from a scalar
+// base; the (chunk, view) items go round the waves.  What is left, fewer
+// hypotheses than kFullChunk, goes by (hypothesis, view) pairs with the view
+// per lane, as do the own planes and the refinement candidates: a pair costs
+// ~20 % more than a lane of a full chunk (per-lane constants, 64-bit
+// addresses), which a chunk with more than kFullChunk of 64 lanes in use
+// beats.  One piece of code scores every kind of pair (stages 0..3), so that
+// the evaluation is in the instruction cache twice, not five times.
+//
+// The counters report every region's plane and the pixel's own on every view,
+// shared or left out evaluations included, and of the refinement what was
+// scored.
+// ---------------------------------------------------------------------------
+constexpr int kFullChunk = 53;
+// Up to this many views the own planes are listed with the propagated ones: at most k = 4 views carry weight, so with
+// 4 nearly every view does and scoring them later would only add a stage (8 views: the same time either way; 10 views:
+// later is 1.5 % faster).
+constexpr int kOwnFirst = 4;
+constexpr int kPassTileW = 2 * kPix + 10;
+constexpr int kNoRow = 0xff;
+// a pair: pixel of the workgroup (6 bits), view (5), candidate (3)
+constexpr int kPairPix = 63, kPairView = 6, kPairCand = 11;
+
+// Inverse-depth terms of a hypothesis in LDS; q0 < 0 marks one whose depth or window fails the range test.
+struct QLds {
+    double q0;
+    float qu, qv;
+};
+
+struct HalfLds {
+    float *tile;          // [ROWS + 10][kPassTileW] reference intensities; then the rows' aggregated costs
+    float2 *rw;           // [pixel][kWinStride] window blocks
+    gf4 *pl;              // [pixel][8] the rows' planes; then [pixel][7] of QLds, cand's inverse-depth terms
+    QLds *q;              // [pixel][8] their inverse-depth terms; then cand
+    gf4 *cand;            // [pixel][7] refinement candidates, and in slot 6 the own, then the best plane
+    float *ms;            // [view][pixel][8] costs, with own_first [view][pixel] after each view's; own costs
+                          // [pixel][N]; refinement [pixel][6 N], and its list of pairs
+    float *psi;           // [pixel][N] importance, < 0 outside S_t; then the wave's pair list
+    float *wgt;           // [pixel][N] view weights
+    unsigned short *hyp;  // the listed hypotheses: pixel * 8 + row
+    unsigned char *rep;   // [pixel][8] the row whose costs serve this one, kNoRow without a candidate
+    float2 *ws;           // [pixel] 1 / sum w, weighted reference variance
+    uint32_t *sel;        // [pixel] S_t
+    int *vt;              // [pixel] most important view
+    uint32_t *act;        // [pixel] the views that carry weight
+    float *wsum;          // [pixel] their sum
+    int *count;           // [ROWS] distinct hypotheses of each row; [2][ROWS] its pairs in the stage, scored and counted
+    unsigned *nshort;     // [ROWS] evaluations that took no samples
+    unsigned char *own;   // [pixel] the row that holds the pixel's own plane, or kNoRow
+    gf4 *u;               // [2][pixel] the refinement's draws: perturbation, random (t >= 3)
+};
+
+// Offsets for a tile of `rows` image rows and n views.  The refinement's pair list of a row (6 candidates x 8
+// pixels x N views, 2 bytes each) takes the end of ms past the results and the psi block after it.
+__host__ __device__ inline size_t half_layout(int n, int rows, size_t off[18]) {
+    const size_t P = (size_t)kPix * rows, H = 8 * P;
+    const size_t nl = n < 3 ? 3 : n;
+    size_t o = 0;
+    off[0] = o; o = align16(o + sizeof(float) * (rows + 10) * kPassTileW);
+    off[1] = o; o = align16(o + sizeof(float2) * P * kWinStride);
+    off[2] = o; o = align16(o + sizeof(float4) * H);
+    off[3] = o; o = align16(o + sizeof(QLds) * H);
+    off[4] = o; o = align16(o + sizeof(float) * (n <= kOwnFirst ? H + P : H) * nl);
+    off[5] = o; o = align16(o + sizeof(float) * P * nl);
+    off[6] = o; o = align16(o + sizeof(float) * P * nl);
+    off[7] = o; o = align16(o + sizeof(unsigned short) * (H + P));
+    off[8] = o; o = align16(o + H);
+    off[9] = o; o = align16(o + sizeof(float2) * P);
+    off[10] = o; o = align16(o + sizeof(uint32_t) * P);
+    off[11] = o; o = align16(o + sizeof(int) * P);
+    off[12] = o; o = align16(o + sizeof(uint32_t) * P);
+    off[13] = o; o = align16(o + sizeof(float) * P);
+    off[14] = o; o = align16(o + sizeof(int) * 3 * rows);
+    off[15] = o; o = align16(o + sizeof(unsigned) * rows);
+    off[16] = o; o = align16(o + P);
+    off[17] = o; o = align16(o + sizeof(float4) * 2 * P);
+    return o;
+}
+
+// enough for every view count up to n_src (the own planes' rows make the layout of kOwnFirst views larger than that
+// of one more)
+size_t pass_lds_bytes(int n_src, int rows) {
+    size_t off[18];
+    const size_t a = half_layout(n_src, rows, off), b = half_layout(n_src < kOwnFirst ? n_src : kOwnFirst, rows, off);
+    return a > b ? a : b;
+}
+
+__device__ __forceinline__ HalfLds carve_half(unsigned char *smem, int n_src, int rows) {
+    size_t off[18];
+    half_layout(n_src, rows, off);
+    HalfLds L;
+    L.tile = reinterpret_cast<float *>(smem + off[0]);
+    L.rw = reinterpret_cast<float2 *>(smem + off[1]);
+    L.pl = reinterpret_cast<gf4 *>(smem + off[2]);
+    L.q = reinterpret_cast<QLds *>(smem + off[3]);
+    L.cand = reinterpret_cast<gf4 *>(smem + off[3]);
+    L.ms = reinterpret_cast<float *>(smem + off[4]);
+    L.psi = reinterpret_cast<float *>(smem + off[5]);
+    L.wgt = reinterpret_cast<float *>(smem + off[6]);
+    L.hyp = reinterpret_cast<unsigned short *>(smem + off[7]);
+    L.rep = smem + off[8];
+    L.ws = reinterpret_cast<float2 *>(smem + off[9]);
+    L.sel = reinterpret_cast<uint32_t *>(smem + off[10]);
+    L.vt = reinterpret_cast<int *>(smem + off[11]);
+    L.act = reinterpret_cast<uint32_t *>(smem + off[12]);
+    L.wsum = reinterpret_cast<float *>(smem + off[13]);
+    L.count = reinterpret_cast<int *>(smem + off[14]);
+    L.nshort = reinterpret_cast<unsigned *>(smem + off[15]);
+    L.own = smem + off[16];
+    L.u = reinterpret_cast<gf4 *>(smem + off[17]);
+    return L;
+}
+
+// Orders a wave's own LDS writes before its later reads (LDS operations of a wave complete in order, so only the
+// compiler has to keep them).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ gf4 to_gf4(float4 v) {
+    gf4 r;
+    r.x = v.x;
+    r.y = v.y;
+    r.z = v.z;
+    r.w = v.w;
+    return r;
+}
+__device__ __forceinline__ float4 to_float4(gf4 v) { return make_float4(v.x, v.y, v.z, v.w); }
+
+// the value of the lane N below in a row of 16 lanes (the pixel's lanes: row r gets row r - N)
+template <int N>
+__device__ __forceinline__ int lane_below(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x110 | N, 0xF, 0xF, true);
+}
+
+// Row of the same pixel, the lowest of those below this one, that holds the same plane bit for bit; r if none.
+template <int N>
+__device__ __forceinline__ void same_below(const int (&p)[4], int ok, int r, int &rep) {
+    const int d = (lane_below<N>(p[0]) ^ p[0]) | (lane_below<N>(p[1]) ^ p[1]) | (lane_below<N>(p[2]) ^ p[2]) |
+                  (lane_below<N>(p[3]) ^ p[3]);
+    const int there = lane_below<N>(ok);
+    if (r >= N && there && d == 0) rep = r - N;  // called from N = 1 upwards: the lowest row is last
+}
+
+// A cost as stored: negative (kShort, weighted or not) where no sample was taken and the cost is 2.
+__device__ __forceinline__ float stored_cost(float c) { return c < 0.f ? 2.f : c; }
+
+// distance of window sample s from the centre, the square roots correctly rounded
+constexpr float kR2 = 1.4142135623730951f, kR10 = 3.1622776601683795f, kR18 = 4.242640687119285f,
+                kR26 = 5.0990195135927845f, kR34 = 5.830951894845301f, kR50 = 7.0710678118654755f;
+__constant__ const float kWinDist[36] = {
+    kR50, kR34, kR26, kR26, kR34, kR50,
+    kR34, kR18, kR10, kR10, kR18, kR34,
+    kR26, kR10, kR2, kR2, kR10, kR26,
+    kR26, kR10, kR2, kR2, kR10, kR26,
+    kR34, kR18, kR10, kR10, kR18, kR34,
+    kR50, kR34, kR26, kR26, kR34, kR50};
+
+// min over the 8 lanes of a pixel
+__device__ __forceinline__ float pixel_min(float v) {
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false)));  // xor 1
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false)));  // xor 2
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false)));  // 7 - i
+    return v;
+}
+
+// build_window on the pixel's 8 lanes, the same bits: lane r takes the weights of samples r, r + 8, ..., every lane
+// the sums that run over the samples in order, lane r < 6 the entries and constants of window row r.  (One lane's
+// work on every lane, as build_window does it, is 830 vector instructions; this is ~400.)
+template <typename Reader>
+__device__ __forceinline__ WinStats build_window8(const Reader &rd, const MethodDev &m, float2 *rw, int r) {
+#pragma clang fp contract(off)
+    gf4 *rw4 = reinterpret_cast<gf4 *>(rw);
+    const float ac = rd(0, 0);
+    float e[5], as[5];
+    float emin = __builtin_inff();
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const int s = min(r + 8 * k, 35);  // lanes past the last sample repeat it
+        const int sv = (s * 43) >> 8, du = -5 + 2 * (s - 6 * sv), dv = -5 + 2 * sv;
+        as[k] = rd(du, dv);
+        const float dc = fabsf(as[k] - ac);
+        const float dist = m.bil_sq ? (float)(du * du + dv * dv) : kWinDist[s];
+        const float col = m.bil_sq ? dc * dc : dc;
+        e[k] = fmaf(col, m.inv_2sc2, dist * m.inv_2sx2);
+        emin = fminf(emin, e[k]);
+    }
+    emin = pixel_min(emin);
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+        if (k < 4 || r < 4) rw[r + 8 * k] = make_float2(__expf(emin - e[k]), as[k]);
+    wave_sync();
+    gf4 p[18];  // (w, a) of two samples each
+#pragma unroll
+    for (int k = 0; k < 18; ++k) p[k] = rw4[k];
+    float sw = 0.f, swa = 0.f;
+#pragma unroll
+    for (int k = 0; k < 18; ++k) {
+        sw += p[k].x;
+        swa = fmaf(p[k].x, p[k].y, swa);
+        sw += p[k].z;
+        swa = fmaf(p[k].z, p[k].w, swa);
+    }
+    const float invW = 1.f / sw;
+    const float mean = swa * invW;
+    float saa = 0.f, wcum = 0.f;
+    float wr = 0.f, ar = 0.f, wprev = 0.f, wend = 0.f;  // of the lane's window row
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        float wq = 0.f, aq = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            gf4 &v = p[q * 3 + k];
+            const float ap0 = v.y - mean, wap0 = v.x * ap0;
+            saa = fmaf(wap0, ap0, saa);
+            wq += v.x;
+            aq += wap0;
+            const float ap1 = v.w - mean, wap1 = v.z * ap1;
+            saa = fmaf(wap1, ap1, saa);
+            wq += v.z;
+            aq += wap1;
+            v.y = wap0;
+            v.w = wap1;
+        }
+        const float before = wcum;
+        wcum += wq;
+        if (r == q) {
+            wr = wq;
+            ar = aq;
+            wprev = before;
+            wend = wcum;
+            rw4[q * 3] = p[q * 3];
+            rw4[q * 3 + 1] = p[q * 3 + 1];
+            rw4[q * 3 + 2] = p[q * 3 + 2];
+        }
+    }
+    if (r < 6) {
+        // a row whose weights all underflow adds nothing (its constants are 0)
+        const bool any = wr > 0.f;
+        gf4 c;
+        c.x = any ? 1.f / wr : 0.f;
+        c.y = any ? wr / wend : 0.f;
+        c.z = any ? wprev * wr / wend : 0.f;
+        c.w = any ? ar : 0.f;
+        rw4[18 + r] = c;
+    }
+    WinStats ws;
+    ws.invW = invW;
+    ws.var_a = saa * invW;
+    return ws;
+}
+
+__device__ __forceinline__ QLds q_lds(const PlaneQ &q) { return QLds{q.ok ? q.q0 : -1.0, q.qu, q.qv}; }
+
+// tid: threadIdx.x (the persistent launch passes it through an opaque copy, so that nothing derived from
+// it is kept live across its tiles)
+template <int HALF, int ROWS>
+__device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned char *smem, int tid) {
+    constexpr int WAVES = tile_waves(ROWS);
+    static_assert(ROWS <= WAVES && ROWS <= 4, "a wave per row, 32 pixels at most");
+    const int N = a.n_src;
+    const HalfLds S = carve_half(smem, N, ROWS);
+    constexpr int P = kPix * ROWS, H = 8 * P;  // pixels, propagated hypotheses
+    const bool own_first = N <= kOwnFirst;
+    const int HV = own_first ? H + P : H;      // costs of a view
+    const int NL = N < 3 ? 3 : N;              // row length of psi (room for the pair lists)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ty = L / a.tiles_x, tx = L - ty * a.tiles_x;
+    const int y0 = ty * ROWS, x0 = tx * 2 * kPix;
+    const int W = a.ref.W, Hh = a.ref.H;
+    const MethodDev &m = a.m;
+    // column of a pixel of the workgroup (on image row y0 + pixel / 8)
+    const auto col_of = [&](int pix) { return x0 + 2 * (pix & 7) + ((y0 + (pix >> 3) + a.colour) & 1); };
+
+    stage_tile<ROWS, WAVES, kPassTileW>(a.ref, S.tile, y0, x0, tid);
+
+    if (wave < ROWS) {
+        const int lane = tid & 63, g = lane >> 3, row = lane & 7, pi = tid >> 3;
+        const int y = y0 + wave, x = col_of(pi);
+        const bool pix_ok = y < Hh && x < W;
+        // (1) asymmetric propagation: lane r takes the lowest-cost candidate of region r, in table order (the first
+        //     of a region is the nearest, so it is inside the image if any is).  A candidate lies f pixels forward
+        //     in the region's direction and s to its side; those outside the image read the pixel's own entry.
+        //     The loads are all in flight together.
+        bool valid = false;
+        float4 pl = make_float4(0.f, 0.f, -1.f, 1.f), own = pl;
+        if (pix_ok) {
+            const unsigned p = (unsigned)y * (unsigned)W + (unsigned)x;
+            own = load_plane(a.st.planes, p);
+            const int dir = row & 3;  // up, down, left, right
+            const bool near = row < 4, vert = dir < 2;
+            const int fstep = (vert ? W : 1) * ((dir & 1) ? 1 : -1), sstep = vert ? 1 : W;
+            // pixels ahead, and on the negative and positive side (far candidates have no side offset)
+            const int ahead = dir == 0 ? y : dir == 1 ? Hh - 1 - y : dir == 2 ? x : W - 1 - x;
+            const int neg = near ? (vert ? x : y) : 64, pos = near ? (vert ? W - 1 - x : Hh - 1 - y) : 64;
+            const int ahead_far = near ? -1 : ahead;  // near regions have 7 candidates
+            unsigned at[11];
+            bool in[11];
+            float cr[11];
+#pragma unroll
+            for (int e = 0; e < 11; ++e) {
+                const int lvl = (e + 1) >> 1;
+                const int f = near ? lvl + 1 : 3 + 2 * e;
+                const int s = near ? ((e & 1) ? -lvl : lvl) : 0;
+                in[e] = f <= (e < 7 ? ahead : ahead_far) && (e == 0 || e >= 7 || lvl <= ((e & 1) ? neg : pos));
+                at[e] = p + (in[e] ? (unsigned)(__mul24(f, fstep) + __mul24(s, sstep)) : 0u);
+                cr[e] = glob(a.st.cost)[at[e]];
+            }
+            unsigned best = at[0];
+            float bc = cr[0];
+#pragma unroll
+            for (int e = 1; e < 11; ++e)
+                if (in[e] && cr[e] < bc) {
+                    best = at[e];
+                    bc = cr[e];
+                }
+            valid = in[0];
+            if (valid) pl = load_plane(a.st.planes, best);
+        }
+        const int pb[4] = {__float_as_int(pl.x), __float_as_int(pl.y), __float_as_int(pl.z), __float_as_int(pl.w)};
+        const int ok = valid ? 1 : 0;
+        int rep = row;
+        same_below<1>(pb, ok, row, rep);
+        same_below<2>(pb, ok, row, rep);
+        same_below<3>(pb, ok, row, rep);
+        same_below<4>(pb, ok, row, rep);
+        same_below<5>(pb, ok, row, rep);
+        same_below<6>(pb, ok, row, rep);
+        same_below<7>(pb, ok, row, rep);
+        const bool is_own = valid && __float_as_int(own.x) == pb[0] && __float_as_int(own.y) == pb[1] &&
+                            __float_as_int(own.z) == pb[2] && __float_as_int(own.w) == pb[3];
+        const uint32_t ob = (uint32_t)(__ballot(is_own) >> (8 * g)) & 0xFFu;
+        if (row == 0) S.own[pi] = (unsigned char)(ob ? __builtin_ctz(ob) : kNoRow);
+        S.pl[tid] = to_gf4(pl);
+        S.rep[tid] = (unsigned char)(valid ? rep : kNoRow);
+        // the row's hypotheses: the distinct planes and, with own_first, the own planes no region holds
+        const bool lists = valid && rep == row;
+        const bool lists_own = own_first && m.include_self && pix_ok && row == 0 && !ob;
+        if (lists) S.q[tid] = q_lds(plane_q(a.ref, m, pl, x, y));
+        const unsigned long long listed = __ballot(lists), listed_own = __ballot(lists_own);
+        if (lane == 0) {
+            S.count[wave] = __popcll(listed) + __popcll(listed_own);
+            S.nshort[wave] = 0u;
+        }
+        __syncthreads();
+        int base = 0;
+#pragma unroll
+        for (int w = 0; w < ROWS; ++w)
+            if (w < wave) base += S.count[w];
+        const unsigned long long below = (1ull << lane) - 1ull;
+        if (lists) S.hyp[base + __popcll(listed & below)] = (unsigned short)tid;
+        if (lists_own) S.hyp[base + __popcll(listed) + __popcll(listed_own & below)] = (unsigned short)(H + pi);
+
+        // (2) reference window
+        if (pix_ok) {
+            TileReader<kPassTileW> rd{S.tile, 5 + wave, 5 + (x - x0), &a.ref, x, y};
+            const WinStats ws = build_window8(rd, m, S.rw + pi * kWinStride, row);
+            if (row == 0) S.ws[pi] = make_float2(ws.invW, ws.var_a);
+        }
+    } else {
+        __syncthreads();
+    }
+    __syncthreads();
+
+    // (3) costs of the listed hypotheses on every view (Eq. 1), at [view][pixel][row]
+    int n_hyp = 0;
+#pragma unroll
+    for (int w = 0; w < ROWS; ++w) n_hyp += __builtin_amdgcn_readfirstlane(S.count[w]);
+    const int n_chunks = (n_hyp + 63 - kFullChunk) >> 6;
+    // a listed hypothesis: propagated (pixel * 8 + row), or H + pixel for an own plane
+    const auto pixel_of = [&](int slot) { return slot < H ? slot >> 3 : slot - H; };
+    const auto terms_of = [&](int slot) {
+        if (slot < H) return S.q[slot];
+        const int hp = slot - H, hx = col_of(hp), hy = y0 + (hp >> 3);
+        return q_lds(plane_q(a.ref, m, load_plane(a.st.planes, (size_t)hy * W + hx), hx, hy));
+    };
+    {
+        int lane = tid & 63, slot = 0, hp = 0;
+        bool live = false;
+        QLds q = {-1.0, 0.f, 0.f};
+        WinStats ws = {1.f, 0.f};
+        int chunk = 0, have = -1, j = wave;
+        while (j >= N) {
+            j -= N;
+            ++chunk;
+        }
+        while (chunk < n_chunks) {
+            if (chunk != have) {
+                have = chunk;
+                const int h = chunk * 64 + lane;
+                live = h < n_hyp;
+                slot = live ? S.hyp[h] : 0;
+                hp = pixel_of(slot);
+                if (live) q = terms_of(slot);
+                const float2 s = S.ws[hp];
+                ws.invW = s.x;
+                ws.var_a = s.y;
+            }
+            const ViewDev vw = uniform_view(a.views, j);
+            if (live)
+                S.ms[j * HV + slot] = q.q0 >= 0.0 ? ncc_cost_raw<HALF>(vw, S.rw + hp * kWinStride, ws, col_of(hp),
+                                                                       y0 + (hp >> 3), q.q0, q.qu, q.qv)
+                                                  : kShort;
+            j += WAVES;
+            while (j >= N) {
+                j -= N;
+                ++chunk;
+            }
+        }
+    }
+
+    // (4)-(8): pairs of a hypothesis and a view, the view per lane.  Stage 0: the hypotheses past the last chunk;
+    // 1: the own planes on the views that carry weight; 2: the refinement candidates on the most important view;
+    // 3: those still in the running on the others.  A pair of stages 1..3 lies in the list of the wave that
+    // owns the pixel.
+    const int rest0 = n_chunks * 64, n_rest = max(n_hyp - rest0, 0);
+    const uint32_t div_rest = n_rest ? ((1u << 18) + n_rest - 1) / n_rest : 0u;  // exact: i n_rest < 2^18
+    const int ncand = a.t >= 3 ? 6 : 3;
+    float bcost = 0.f;  // cost of the kept hypothesis
+    int bcand = 6;      // its slot in cand
+    int n_ref = 0;      // refinement pairs
+    for (int stage = 0; stage < 4; ++stage) {
+        // the lane's place, derived anew in every stage from a copy the compiler cannot see through: what follows
+        // from it (the random draws among it) is not computed ahead of the loop and held in scratch
+        int tid_s = tid;
+        asm volatile("" : "+v"(tid_s));
+        const int lane = tid_s & 63, g = lane >> 3, row = lane & 7, pi = tid_s >> 3;
+        const int y = y0 + wave, x = col_of(pi);
+        const bool pix_ok = y < Hh && x < W;
+        const size_t p = pix_ok ? (size_t)y * W + x : 0;
+        // pairs of the stage, and where they lie
+        int upto[ROWS];  // ends of the rows' shares
+        int total = 0;
+        if (stage == 0) {
+            total = n_rest * N;
+        } else {
+#pragma unroll
+            for (int w = 0; w < ROWS; ++w) {
+                total += __builtin_amdgcn_readfirstlane(S.count[ROWS + w]);
+                upto[w] = total;
+            }
+        }
+        // stage 0 goes on where the chunks' items ended
+        const int first = stage == 0 ? (wave + WAVES - (n_chunks * N) % WAVES) % WAVES : wave;
+        for (int i = first * 64 + lane; i < total; i += 64 * WAVES) {
+            int hp, j, dst;
+            QLds q;
+            if (stage == 0) {
+                j = (int)(((uint32_t)i * div_rest) >> 18);
+                const int slot = S.hyp[rest0 + (i - j * n_rest)];
+                hp = pixel_of(slot);
+                dst = j * HV + slot;
+                q = terms_of(slot);
+            } else {
+                int w = 0, lo = 0;
+#pragma unroll
+                for (int k = 0; k + 1 < ROWS; ++k)
+                    if (i >= upto[k]) {
+                        w = k + 1;
+                        lo = upto[k];
+                    }
+                const unsigned short *list =
+                    stage < 3 ? reinterpret_cast<const unsigned short *>(S.psi + w * kPix * NL)
+                              : reinterpret_cast<const unsigned short *>(S.ms + 6 * N * P) + w * 6 * kPix * N;
+                const int d = list[i - lo];
+                hp = d & kPairPix;
+                j = (d >> kPairView) & 31;
+                const int c = stage == 1 ? 6 : d >> kPairCand;
+                // own costs at [pixel][k], candidates' weighted costs at [pixel][candidate][k], k the view's place
+                // among those that carry weight
+                const uint32_t act = S.act[hp];
+                const int k = __popc(act & ((1u << j) - 1u));
+                dst = stage == 1 ? hp * N + k : (hp * 6 + c) * N + k;
+                q = stage == 1 ? q_lds(plane_q(a.ref, m, to_float4(S.cand[hp * 7 + 6]), col_of(hp), y0 + (hp >> 3)))
+                               : reinterpret_cast<const QLds *>(S.pl + hp * 8)[c];
+            }
+            const float2 s = S.ws[hp];
+            const WinStats ws = {s.x, s.y};
+            const float cost = q.q0 >= 0.0 ? ncc_cost_raw<HALF>(a.views[j], S.rw + hp * kWinStride, ws, col_of(hp),
+                                                                y0 + (hp >> 3), q.q0, q.qu, q.qv)
+                                           : kShort;
+            S.ms[dst] = stage >= 2 ? S.wgt[hp * N + j] * cost : cost;
+        }
+        if (stage == 1) {
+            // the own planes' evaluations on the views without weight, which nothing reads: short or not
+            unsigned ns = 0;
+            total = 0;
+#pragma unroll
+            for (int w = 0; w < ROWS; ++w) {
+                total += __builtin_amdgcn_readfirstlane(S.count[2 * ROWS + w]);
+                upto[w] = total;
+            }
+            for (int i = (WAVES - 1 - wave) * 64 + lane; i < total; i += 64 * WAVES) {
+                int w = 0, lo = 0;
+#pragma unroll
+                for (int k = 0; k + 1 < ROWS; ++k)
+                    if (i >= upto[k]) {
+                        w = k + 1;
+                        lo = upto[k];
+                    }
+                const int d = reinterpret_cast<const unsigned short *>(S.psi + w * kPix * NL)[8 * N - 1 - (i - lo)];
+                const int hp = d & kPairPix, hx = col_of(hp), hy = y0 + (hp >> 3);
+                const PlaneQ q = plane_q(a.ref, m, to_float4(S.cand[hp * 7 + 6]), hx, hy);
+                SrcWarp sw;
+                if (!q.ok || !src_warp<HALF>(a.views[d >> kPairView], hx, hy, q.q0, q.qu, q.qv, sw)) ++ns;
+            }
+            if (ns) atomicAdd(&S.nshort[0], ns);
+        } else if (stage >= 2) {
+            n_ref += total;
+        } else if (m.refine && wave == (n_chunks * N + ((n_rest * N + 63) >> 6)) % WAVES) {
+            // the refinement's draws, one per pixel and stream, by the wave whose turn it is (Philox is ~700 issue
+            // slots: too many for every lane of every wave)
+            const int pix = lane % P, str = lane / P;
+            if (str < (a.t >= 3 ? 2 : 1)) {
+                const int hx = col_of(pix), hy = y0 + (pix >> 3);
+                float u[4];
+                philox((uint64_t)((size_t)hy * W + hx), (uint64_t)a.t, str + 1, m.seed, u);
+                gf4 v;
+                v.x = u[0];
+                v.y = u[1];
+                v.z = u[2];
+                v.w = u[3];
+                S.u[str * P + pix] = v;
+            }
+        }
+        __syncthreads();
+
+        // every pixel's own lanes take the results; the phases of a stage stay within the wave
+        if (wave >= ROWS) {
+            if (stage == 1 && !m.refine) break;
+            if (stage == 0 && own_first) {
+                if (!m.refine) break;
+                ++stage;
+            }
+            __syncthreads();
+            continue;
+        }
+        unsigned short *list = reinterpret_cast<unsigned short *>(S.psi + wave * kPix * NL);
+        if (stage == 0) {
+            // (4) view inference, part 1 (Sec. 3.2): lane r judges views r, r + 8, ...
+            //     good view: more than n1 costs below tau and fewer than n2 above tau_up;
+            //     importance: mean confidence exp(-m^2 / (2 beta^2)) over the valid rows
+            float *psi = S.psi + pi * NL, *wgt = S.wgt + pi * N;
+            unsigned ns = 0;
+            const int r_own = S.own[pi];  // row that holds the pixel's own plane
+            const uint2 reps = reinterpret_cast<const uint2 *>(S.rep)[pi];
+            const int r_me = S.rep[tid_s];
+            const int nv = __popcll((__ballot(r_me != kNoRow) >> (8 * g)) & 0xFFull);
+            if (pix_ok) {
+                for (int j = row; j < N; j += 8) {
+                    int lt = 0, gt = 0;
+                    float sc = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int r = ((i < 4 ? reps.x : reps.y) >> (8 * (i & 3))) & 0xFF;
+                        if (r == kNoRow) continue;
+                        const float raw = S.ms[j * HV + pi * 8 + r];
+                        ns += raw < 0.f;
+                        const float c = stored_cost(raw);
+                        lt += c < m.tau;
+                        gt += c > m.tau_up;
+                        sc += __expf(-c * c * m.inv_2b2);
+                    }
+                    if (m.include_self && own_first && r_own == kNoRow) ns += S.ms[j * HV + H + pi] < 0.f;
+                    if (m.include_self && r_own != kNoRow) ns += S.ms[j * HV + pi * 8 + r_own] < 0.f;
+                    psi[j] = (nv > 0 && lt > m.n1 && gt < m.n2) ? sc / (float)nv : -1.f;
+                }
+            }
+            wave_sync();
+
+            // (5) view inference, part 2 (Eq. 4-6).  Lane r of the pixel holds views r, r + 8, r + 16, r + 24.  S_t
+            //     comes from one ballot per view slot.  Each lane ranks its views of S_t against the pixel's others
+            //     (psi in LDS, the same address for the pixel's lanes): a view keeps its modified importance (x2 for
+            //     v_{t-1}) when fewer than k views of S_t rank above it by modified importance (larger, or equal and
+            //     a lower index), a view of S_{t-1} that left the selection weighs 0.2, every other view 0; the view
+            //     no other outranks by importance itself is v_t = argmax psi (ties to the lower index), found by a
+            //     ballot
+            uint32_t Sm = 0, Sprev = 0;
+            int vt = -1, vprev = -1;
+            if (pix_ok) {
+                vprev = glob(a.st.v)[p];
+                Sprev = glob(a.st.S)[p];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = row + 8 * i;
+                const bool in = pix_ok && j < N && psi[j] >= 0.f;
+                Sm |= (uint32_t)((__ballot(in) >> (8 * g)) & 0xFFull) << (8 * i);
+            }
+            uint32_t top = 0, mine = 0;  // bit i: the lane's view slot i is v_t; carries weight
+            if (pix_ok) {
+                for (int i = 0, j = row; j < N; ++i, j += 8) {
+                    const float pj = psi[j];
+                    float w;
+                    if (pj >= 0.f) {  // j in S_t
+                        const float mj = (j == vprev ? 2.f : 1.f) * pj;
+                        int rank = 0, rpsi = 0;
+                        for (uint32_t rest = Sm; rest; rest &= rest - 1u) {  // the views of S_t
+                            const int q = __builtin_ctz(rest);
+                            const float pq = psi[q];
+                            const float mq = (q == vprev ? 2.f : 1.f) * pq;
+                            rank += (mq > mj || (mq == mj && q < j)) ? 1 : 0;
+                            rpsi += (pq > pj || (pq == pj && q < j)) ? 1 : 0;
+                        }
+                        if (rpsi == 0) top |= 1u << i;
+                        w = rank < m.k ? mj : 0.f;
+                    } else {
+                        w = ((Sprev >> j) & 1u) ? 0.2f : 0.f;
+                    }
+                    wgt[j] = w;
+                    mine |= (w > 0.f ? 1u : 0u) << i;
+                }
+            }
+            uint32_t act = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t bits = (uint32_t)((__ballot((top >> i) & 1u) >> (8 * g)) & 0xFFull);
+                if (bits) vt = 8 * i + __builtin_ctz(bits);
+                act |= (uint32_t)((__ballot((mine >> i) & 1u) >> (8 * g)) & 0xFFull) << (8 * i);
+            }
+            // all weights 0: the plain mean over all views (weights 1)
+            if (act == 0) {
+                act = N >= 32 ? 0xFFFFFFFFu : (1u << N) - 1u;
+                if (pix_ok)
+                    for (int j = row; j < N; j += 8) wgt[j] = 1.f;
+            }
+            wave_sync();
+            // the pixel's weight sum in view order, and the unified cost of the lane's hypothesis (Eq. 7): the views
+            // of weight 0 would add exactly nothing
+            float mfin = __builtin_inff();
+            if (pix_ok) {
+                float wsum = 0.f, acc = 0.f;
+                for (uint32_t rest = act; rest; rest &= rest - 1u) {
+                    const int j = __builtin_ctz(rest);
+                    const float w = wgt[j];
+                    wsum += w;
+                    if (r_me != kNoRow) acc = fmaf(w, stored_cost(S.ms[j * HV + pi * 8 + r_me]), acc);
+                }
+                if (r_me != kNoRow) mfin = acc / wsum;
+                if (row == 0) {
+                    S.sel[pi] = Sm;
+                    S.vt[pi] = vt;
+                    S.act[pi] = act;
+                    S.wsum[pi] = wsum;
+                    // the own plane (cand takes the place of q, read no more)
+                    S.cand[pi * 7 + 6] = to_gf4(load_plane(a.st.planes, p));
+                }
+            }
+            S.tile[tid_s] = mfin;
+            // the own plane's pairs: scored on the views that carry weight, only counted (short or not) on the others
+            const bool own_scored = pix_ok && m.include_self && r_own == kNoRow && !own_first;
+            const unsigned long long own_pix = __ballot(own_scored && row == 0);
+            const int n_own = own_scored ? __popc(act) : 0;
+            int before = 0, n_pairs = 0;
+#pragma unroll
+            for (int k = 0; k < kPix; ++k) {
+                const int nk = __builtin_amdgcn_readlane(n_own, 8 * k);
+                before += k < g ? nk : 0;
+                n_pairs += nk;
+            }
+            wave_sync();  // psi is read no more: the list takes its place
+            if (own_scored) {
+                // scored from the front of the list, only counted from the back
+                const int back = 8 * N - 1 - (N * __popcll(own_pix & ((1ull << (8 * g)) - 1ull)) - before);
+                for (int j = row; j < N; j += 8) {
+                    const int k = __popc(act & ((1u << j) - 1u));
+                    list[(act >> j) & 1u ? before + k : back - (j - k)] = (unsigned short)(pi | (j << kPairView));
+                }
+            }
+            if (lane == 0) {
+                S.count[ROWS + wave] = n_pairs;
+                S.count[2 * ROWS + wave] = N * __popcll(own_pix) - n_pairs;
+            }
+            if (ns) atomicAdd(&S.nshort[wave], ns);
+            if (own_first) {
+                ++stage;  // the own planes are scored: on within the wave
+                wave_sync();
+            }
+        }
+        if (stage == 1) {
+            // (6) the own plane's unified cost, (7) best hypothesis: own plane first, then region order; strictly
+            //     lower wins
+            const uint32_t act = S.act[pi];
+            if (pix_ok) {
+                float own = __builtin_inff();
+                if (m.include_self) {
+                    const int r_own = S.own[pi];
+                    if (r_own != kNoRow) {
+                        own = S.tile[pi * 8 + r_own];
+                    } else {
+                        float acc = 0.f;
+                        unsigned ns = 0;
+                        int k = 0;
+                        for (uint32_t rest = act; rest; rest &= rest - 1u, ++k) {
+                            const int j = __builtin_ctz(rest);
+                            const float raw = own_first ? S.ms[j * HV + H + pi] : S.ms[pi * N + k];
+                            ns += raw < 0.f;
+                            acc = fmaf(S.wgt[pi * N + j], stored_cost(raw), acc);
+                        }
+                        own = acc / S.wsum[pi];
+                        if (ns && row == 0 && !own_first) atomicAdd(&S.nshort[wave], ns);
+                    }
+                }
+                int br = m.include_self ? 8 : -1;
+                float bc = own;
+                for (int r = 0; r < 8; ++r) {
+                    if (S.rep[pi * 8 + r] == kNoRow) continue;
+                    const float c = S.tile[pi * 8 + r];
+                    if (br < 0 || c < bc) {
+                        br = r;
+                        bc = c;
+                    }
+                }
+                bcost = bc;
+                // no valid row at all (1-pixel image, no self): the own plane
+                const float4 best = to_float4(br < 0 || br == 8 ? S.cand[pi * 7 + 6] : S.pl[pi * 8 + br]);
+                if (!m.refine) {
+                    if (row == 0) S.cand[pi * 7 + 6] = to_gf4(best);
+                } else if (row < ncand) {
+                    // (8) refinement (Sec. 3.3): perturbed (and, from t = 3, random) depth/normal candidates, scored
+                    //     with the same weights on the views that carry weight; strictly lower wins.  Lane r builds
+                    //     candidate r: (dprt, n), (d, nprt), (dprt, nprt) [, (drnd, n), (d, nrnd), (drnd, nrnd)];
+                    //     the perturbation draws come from stream 1, the random ones from stream 2, one draw per lane
+                    const bool rnd = row >= 3;
+                    const int kind = rnd ? row - 3 : row;  // 0: (new depth, n), 1: (d, new normal), 2: both new
+                    const float2 rr = ref_ray(a.ref, x, y);
+                    const float dcur = plane_depth(rr, best);
+                    const gf4 u = S.u[(rnd ? P : 0) + pi];
+                    float dnew, qx, qy, qz;
+                    if (!rnd) {
+                        const float rho = ldexpf(1.f, -(a.t + 2));
+                        dnew = dcur + (2.f * u.x - 1.f) * rho * (m.d_max - m.d_min);
+                        dnew = fminf(fmaxf(dnew, m.d_min), m.d_max);
+                        qx = best.x + 2.f * rho * (2.f * u.y - 1.f);
+                        qy = best.y + 2.f * rho * (2.f * u.z - 1.f);
+                        qz = best.z + 2.f * rho * (2.f * u.w - 1.f);
+                        const float inv = 1.f / sqrtf(qx * qx + qy * qy + qz * qz);
+                        qx *= inv; qy *= inv; qz *= inv;
+                    } else {
+                        dnew = m.d_min + u.x * (m.d_max - m.d_min);
+                        normal_from_uniforms(u.y, u.z, qx, qy, qz);
+                    }
+                    const float4 cp = kind == 0 ? plane_from(rr, dnew, best.x, best.y, best.z)
+                                                : plane_from(rr, kind == 1 ? dcur : dnew, qx, qy, qz);
+                    S.cand[pi * 7 + row] = to_gf4(cp);
+                    // the pixel's rows are read no more (best is in registers): their place takes the terms
+                    reinterpret_cast<QLds *>(S.pl + pi * 8)[row] = q_lds(plane_q(a.ref, m, cp, x, y));
+                }
+                if (m.refine && row == 6) S.cand[pi * 7 + 6] = to_gf4(best);
+            }
+            if (!m.refine) break;
+            const unsigned long long has = __ballot(pix_ok && row < ncand);
+            if (pix_ok && row < ncand) {
+                const int vt = S.vt[pi];
+                const int j = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
+                list[__popcll(has & ((1ull << lane) - 1ull))] = (unsigned short)(pi | (j << kPairView) | (row << kPairCand));
+            }
+            if (lane == 0) S.count[ROWS + wave] = __popcll(has);
+        } else if (stage == 2) {
+            // candidates still in the running: their pairs with the pixel's other views
+            const uint32_t act = S.act[pi];
+            unsigned short *list3 = reinterpret_cast<unsigned short *>(S.ms + 6 * N * P) + wave * 6 * kPix * N;
+            int n_mine = 0, j0 = 0;
+            if (pix_ok && row < ncand) {
+                const int vt = S.vt[pi];
+                j0 = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
+                const float r0 = S.ms[(pi * 6 + row) * N + __popc(act & ((1u << j0) - 1u))];
+                if (weighted_cost(r0) / S.wsum[pi] < bcost) {
+                    n_mine = __popc(act) - 1;
+                } else {
+                    if (r0 < 0.f) atomicAdd(&S.nshort[wave], 1u);
+                    n_mine = -1;
+                }
+            }
+            if (row < ncand && n_mine < 0) S.ms[(pi * 6 + row) * N] = __builtin_nanf("");  // out
+            // exclusive prefix of the wave's pair counts
+            int pre = max(n_mine, 0);
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int u = __shfl_up(pre, o, 64);
+                if (lane >= o) pre += u;
+            }
+            if (lane == 63) S.count[ROWS + wave] = pre;
+            pre -= max(n_mine, 0);
+            if (n_mine > 0)
+                for (uint32_t rest = act & ~(1u << j0); rest; rest &= rest - 1u)
+                    list3[pre++] = (unsigned short)(pi | (__builtin_ctz(rest) << kPairView) | (row << kPairCand));
+        } else if (stage == 3 && pix_ok) {
+            const uint32_t act = S.act[pi];
+            const int nw = __popc(act);
+            const float wsum = S.wsum[pi];
+            unsigned ns = 0;
+            for (int c = 0; c < ncand; ++c) {
+                const float *res = S.ms + (pi * 6 + c) * N;
+                if (__builtin_isnan(res[0])) continue;
+                float acc = 0.f;
+                for (int i = 0; i < nw; ++i) {
+                    const float r = res[i];
+                    ns += r < 0.f;
+                    acc += weighted_cost(r);
+                }
+                const float cc = acc / wsum;
+                if (cc < bcost) {
+                    bcost = cc;
+                    bcand = c;
+                }
+            }
+            if (ns && row == 0) atomicAdd(&S.nshort[wave], ns);
+        }
+        __syncthreads();
+    }
+
+    // (9) write the pixel
+    if (wave >= ROWS) return;
+    int tid_e = tid;
+    asm volatile("" : "+v"(tid_e));
+    {
+        const int pi = tid_e >> 3, x = col_of(pi), y = y0 + wave, lane = tid_e & 63;
+        const bool first = (tid_e & 7) == 0 && y < Hh && x < W;  // the pixel's first lane
+        if (first) {
+            const size_t p = (size_t)y * W + x;
+            store_plane(a.st.planes, p, to_float4(S.cand[pi * 7 + bcand]));
+            glob(a.st.cost)[p] = bcost;
+            glob(a.st.S)[p] = S.sel[pi];
+            glob(a.st.v)[p] = S.vt[pi];
+        }
+        const int rows = __popcll(__ballot(S.rep[tid_e] != kNoRow)) + (m.include_self ? __popcll(__ballot(first)) : 0);
+        // the wave's own LDS atomics are complete before this read (LDS operations of a wave are in order)
+        const unsigned ns = S.nshort[wave];
+        if (lane == 0) {
+            const int at = (blockIdx.x * ROWS + wave) % kCounterSlots;
+            atomicAdd(&a.counters[1 * kCounterSlots + at], (unsigned long long)(rows * N));
+            if (wave == 0 && n_ref) atomicAdd(&a.counters[2 * kCounterSlots + at], (unsigned long long)n_ref);
+            if (ns) atomicAdd(&a.counters[4 * kCounterSlots + at], (unsigned long long)ns);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Single-image half-pass: one workgroup per tile of the colour.
 // ---------------------------------------------------------------------------
-template <int HALF, int WAVES, bool ABL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ABL ? AMH_BATCH_WAVES_PER_EU : AMH_PASS_WAVES_PER_EU)))
+template <int HALF, int ROWS>
+__global__ __launch_bounds__(64 * tile_waves(ROWS)) __attribute__((amdgpu_waves_per_eu(AMH_PASS_WAVES_PER_EU)))
 void pass_kernel(PassArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = tile_of_block(a.n_tiles, a.order);
     if (L < 0) return;
-    pass_body<HALF, WAVES, ABL>(a, L, smem, (int)threadIdx.x);
+    pass_body<HALF, ROWS>(a, L, smem, (int)threadIdx.x);
+}
+
+template <int HALF, int ROWS>
+__global__ __launch_bounds__(64 * ROWS) __attribute__((amdgpu_waves_per_eu(AMH_BATCH_WAVES_PER_EU)))
+void ablation_kernel(PassArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int L = tile_of_block(a.n_tiles, a.order);
+    if (L < 0) return;
+    ablation_body<HALF, ROWS>(a, L, smem, (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1580,7 +2405,7 @@ __device__ __forceinline__ bool batch_locate(const BatchPhaseArgs &b, int &lo, i
 // The single-image arguments of job J in a batched phase, in scalar registers (the job's arguments are the
 // same for the whole workgroup; the source table as an offset from the argument's pointer, so that the
 // per-view constants are read like the single-image kernels read theirs: scalar loads)
-__device__ __forceinline__ PassArgs batch_pass_args(const BatchPhaseArgs &b, const BatchJobDev &J, int waves) {
+__device__ __forceinline__ PassArgs batch_pass_args(const BatchPhaseArgs &b, const BatchJobDev &J, int rows) {
     PassArgs a;
     a.ref = J.ref;
     a.n_src = J.n_src;
@@ -1592,7 +2417,7 @@ __device__ __forceinline__ PassArgs batch_pass_args(const BatchPhaseArgs &b, con
     a.n_tiles = J.n_tiles;
     a.counters = b.counters;
     a.order = b.order;
-    a.waves = waves;
+    a.rows = rows;
     a.prop = J.prop;
     a.prop_w = J.prop_w;
     a.prop_s = kCell;
@@ -1614,16 +2439,16 @@ __device__ __forceinline__ void batch_stamp(const BatchPhaseArgs &b, int lo, int
 }
 
 // Batched half-pass: one tile per workgroup.
-template <int HALF, int WAVES>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AMH_PASS_WAVES_PER_EU)))
+template <int HALF, int ROWS>
+__global__ __launch_bounds__(64 * tile_waves(ROWS)) __attribute__((amdgpu_waves_per_eu(AMH_PASS_WAVES_PER_EU)))
 void batch_kernel(BatchPhaseArgs b) {
     extern __shared__ __align__(16) unsigned char smem[];
     int lo, L;
     if (!batch_locate(b, lo, L)) return;
     const int j = b.job_of[lo];
     const BatchJobDev &J = b.jobs[j];
-    const PassArgs a = batch_pass_args(b, J, WAVES);
-    pass_body<HALF, WAVES>(a, __builtin_amdgcn_readfirstlane(L), smem, (int)threadIdx.x);
+    const PassArgs a = batch_pass_args(b, J, ROWS);
+    pass_body<HALF, ROWS>(a, __builtin_amdgcn_readfirstlane(L), smem, (int)threadIdx.x);
     batch_stamp(b, lo, j, J.n_tiles);
 }
 
@@ -1680,8 +2505,8 @@ __device__ __forceinline__ const PersistArgs *opaque(const PersistArgs *p) {
     return p;
 }
 
-template <int HALF, int WAVES>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AMH_PASS_WAVES_PER_EU)))
+template <int HALF, int ROWS>
+__global__ __launch_bounds__(64 * tile_waves(ROWS)) __attribute__((amdgpu_waves_per_eu(AMH_PASS_WAVES_PER_EU)))
 void persist_kernel(const PersistArgs *__restrict__ Pg) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_item, s_ok;
@@ -1738,7 +2563,7 @@ void persist_kernel(const PersistArgs *__restrict__ Pg) {
             a.n_tiles = J.n_tiles;
             a.counters = P->counters;
             a.order = 0;
-            a.waves = WAVES;
+            a.rows = ROWS;
             a.prop = J.prop;
             a.prop_w = J.prop_w;
             a.prop_s = kCell;
@@ -1747,7 +2572,7 @@ void persist_kernel(const PersistArgs *__restrict__ Pg) {
             a.views = P->views + __builtin_amdgcn_readfirstlane(J.view_off);
             int tid = (int)threadIdx.x;
             asm volatile("" : "+v"(tid));
-            pass_body<HALF, WAVES>(a, L, smem, tid);
+            pass_body<HALF, ROWS>(a, L, smem, tid);
             // per-job completion stamp of the job's last half-pass
             const PersistArgs *P2 = opaque(Pg);
             if (P2->phases[ph].is_last[lo]) {
@@ -2002,28 +2827,32 @@ hipError_t launch_init(const PassArgs &a, int half, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int ROWS>
+static void launch_pass_rows(const PassArgs &a, int half, hipStream_t s) {
+    const dim3 grid(grid_for(a.n_tiles)), block(64 * tile_waves(ROWS));
+    const size_t lds = pass_lds_bytes(a.n_src, ROWS);
+    if (half) AMH_LAUNCH((pass_kernel<1, ROWS>), grid, block, lds, s, a);
+    else AMH_LAUNCH((pass_kernel<0, ROWS>), grid, block, lds, s, a);
+}
+
+template <int ROWS>
+static void launch_ablation_rows(const PassArgs &a, int half, hipStream_t s) {
+    const dim3 grid(grid_for(a.n_tiles)), block(64 * ROWS);
+    const size_t lds = ablation_lds_bytes(a.n_src, ROWS, a.m.sym_prop == 2 ? 3 : 1);
+    if (half) AMH_LAUNCH((ablation_kernel<1, ROWS>), grid, block, lds, s, a);
+    else AMH_LAUNCH((ablation_kernel<0, ROWS>), grid, block, lds, s, a);
+}
+
 hipError_t launch_pass(const PassArgs &a, int half, hipStream_t s) {
-    const size_t lds = pass_lds_bytes(a.n_src, a.waves, a.m.sym_prop == 2 ? 3 : 1);
-    const dim3 grid(grid_for(a.n_tiles)), block(64 * a.waves);
-    const bool abl = a.m.sym_prop || a.m.heuristic;
-    if (a.waves == 2) {
-        if (abl) {
-            if (half) AMH_LAUNCH((pass_kernel<1, 2, true>), grid, block, lds, s, a);
-            else AMH_LAUNCH((pass_kernel<0, 2, true>), grid, block, lds, s, a);
-        } else {
-            if (half) AMH_LAUNCH((pass_kernel<1, 2, false>), grid, block, lds, s, a);
-            else AMH_LAUNCH((pass_kernel<0, 2, false>), grid, block, lds, s, a);
-        }
-    } else if (a.waves == 4) {
-        if (abl) {
-            if (half) AMH_LAUNCH((pass_kernel<1, 4, true>), grid, block, lds, s, a);
-            else AMH_LAUNCH((pass_kernel<0, 4, true>), grid, block, lds, s, a);
-        } else {
-            if (half) AMH_LAUNCH((pass_kernel<1, 4, false>), grid, block, lds, s, a);
-            else AMH_LAUNCH((pass_kernel<0, 4, false>), grid, block, lds, s, a);
-        }
+    if (ablation_build(a.m)) {
+        if (a.rows == 2) launch_ablation_rows<2>(a, half, s);
+        else if (a.rows == 4) launch_ablation_rows<4>(a, half, s);
+        else return hipErrorInvalidValue;
     } else {
-        return hipErrorInvalidValue;
+        if (a.rows == 1) launch_pass_rows<1>(a, half, s);
+        else if (a.rows == 2) launch_pass_rows<2>(a, half, s);
+        else if (a.rows == 4) launch_pass_rows<4>(a, half, s);
+        else return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
@@ -2037,12 +2866,12 @@ hipError_t launch_batch(const BatchPhaseArgs &b, int half, int max_src, hipStrea
         else AMH_LAUNCH(batch_init_kernel<0>, grid, dim3(2 * kInitBlock), lds, s, b);
         return hipGetLastError();
     }
-    const size_t lds = pass_lds_bytes(max_src, b.waves);
-    const dim3 block(64 * b.waves);
-    if (b.waves == 2) {
+    const size_t lds = pass_lds_bytes(max_src, b.rows);
+    const dim3 block(64 * tile_waves(b.rows));
+    if (b.rows == 2) {
         if (half) AMH_LAUNCH((batch_kernel<1, 2>), grid, block, lds, s, b);
         else AMH_LAUNCH((batch_kernel<0, 2>), grid, block, lds, s, b);
-    } else if (b.waves == 4) {
+    } else if (b.rows == 4) {
         if (half) AMH_LAUNCH((batch_kernel<1, 4>), grid, block, lds, s, b);
         else AMH_LAUNCH((batch_kernel<0, 4>), grid, block, lds, s, b);
     } else {
@@ -2051,26 +2880,26 @@ hipError_t launch_batch(const BatchPhaseArgs &b, int half, int max_src, hipStrea
     return hipGetLastError();
 }
 
-size_t persist_lds_bytes(int max_src, int waves) { return pass_lds_bytes(max_src, waves); }
+size_t persist_lds_bytes(int max_src, int rows) { return pass_lds_bytes(max_src, rows); }
 
-int persist_blocks_per_cu(int half, int waves, int max_src) {
-    const size_t lds = persist_lds_bytes(max_src, waves);
+int persist_blocks_per_cu(int half, int rows, int max_src) {
+    const size_t lds = persist_lds_bytes(max_src, rows);
     int nb = 0;
     hipError_t e;
-    if (waves == 2) e = half ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<1, 2>, 128, lds)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<0, 2>, 128, lds);
-    else e = half ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<1, 4>, 256, lds)
-                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<0, 4>, 256, lds);
+    if (rows == 2) e = half ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<1, 2>, 64 * tile_waves(2), lds)
+                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<0, 2>, 64 * tile_waves(2), lds);
+    else e = half ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<1, 4>, 64 * tile_waves(4), lds)
+                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, persist_kernel<0, 4>, 64 * tile_waves(4), lds);
     return e == hipSuccess ? nb : 0;
 }
 
-hipError_t launch_persist(const PersistArgs *a, int half, int waves, int max_src, int grid, hipStream_t s) {
-    const size_t lds = persist_lds_bytes(max_src, waves);
-    const dim3 g(grid), block(64 * waves);
-    if (waves == 2) {
+hipError_t launch_persist(const PersistArgs *a, int half, int rows, int max_src, int grid, hipStream_t s) {
+    const size_t lds = persist_lds_bytes(max_src, rows);
+    const dim3 g(grid), block(64 * tile_waves(rows));
+    if (rows == 2) {
         if (half) AMH_LAUNCH((persist_kernel<1, 2>), g, block, lds, s, a);
         else AMH_LAUNCH((persist_kernel<0, 2>), g, block, lds, s, a);
-    } else if (waves == 4) {
+    } else if (rows == 4) {
         if (half) AMH_LAUNCH((persist_kernel<1, 4>), g, block, lds, s, a);
         else AMH_LAUNCH((persist_kernel<0, 4>), g, block, lds, s, a);
     } else {
