@@ -208,6 +208,9 @@ void free_job(JobResult &j) {
     j = JobResult{};
 }
 
+// tile rows of the half-pass under the launch configuration: its alternative shape, or the default by view count
+int half_rows(const amh_ctx *c, int n_src) { return c->cfg_rows == 2 ? 2 : pass_tile_rows(n_src); }
+
 PassArgs pass_args(amh_ctx *c, int t, int colour) {
     PassArgs a;
     a.ref = c->refdev;
@@ -221,7 +224,7 @@ PassArgs pass_args(amh_ctx *c, int t, int colour) {
     const int per_row = (W + 1) / 2;  // same-colour pixels per row (upper bound)
     const int tile_pix = ablation_build(a.m) ? kTilePix : kPix;
     a.tiles_x = (per_row + tile_pix - 1) / tile_pix;
-    a.rows = c->cfg_rows;
+    a.rows = ablation_build(a.m) ? c->cfg_rows : half_rows(c, a.n_src);
     if (!ablation_build(a.m) && a.tiles_x * ((H + 3) / 4) <= kSmallTiles) a.rows = 1;
     a.n_tiles = a.tiles_x * ((H + a.rows - 1) / a.rows);
     a.counters = c->counters;
@@ -401,6 +404,8 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
     if ((st = dalloc(c, (void **)&c->d_jobs, sizeof(BatchJobDev) * n_jobs)) != AMH_OK) return st;
     const size_t ncount = kCounterKinds * (size_t)kCounterSlots + (size_t)n_jobs + (size_t)n_jobs + 1;
     if ((st = dalloc(c, (void **)&c->d_bcount, sizeof(unsigned long long) * ncount)) != AMH_OK) return st;
+    // tile rows of a job's half-passes (one shape for all in the persistent launch)
+    auto job_rows = [&](int n) { return c->cfg_persist ? c->cfg_rows : half_rows(c, n); };
     std::vector<ViewDev> hv(total_src);
     std::vector<BatchJobDev> hj(n_jobs);
     int so = 0;
@@ -414,7 +419,8 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
         b.n_src = jobs[j].n_src;
         b.st = StateDev{c->jobs[j].planes, c->jobs[j].cost, c->jobs[j].S, c->jobs[j].v};
         b.tiles_x = ((r.W + 1) / 2 + kPix - 1) / kPix;
-        b.n_tiles = b.tiles_x * ((r.H + c->cfg_rows - 1) / c->cfg_rows);
+        const int rows = job_rows(jobs[j].n_src);
+        b.n_tiles = b.tiles_x * ((r.H + rows - 1) / rows);
         b.n_iblocks = (int)init_blocks(r.W, r.H);
         b.prop = proposal ? c->jobs[j].pred : nullptr;
         b.prop_w = proposal ? cell_rows(r.W) : 0;
@@ -427,20 +433,23 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return hj[a].n_tiles > hj[b].n_tiles; });
     // phases and their tables
     struct Phase {
-        int kind, colour, t, n_active, total, off, grid, max_src;
+        int kind, colour, t, n_active, total, off, grid, max_src, rows;
     };
     std::vector<Phase> phases;
     std::vector<int> tab;
     // A half-pass is launched once per LDS class: workgroups whose sources need less LDS fit more of them on
     // a CU (160 KB), so the jobs of a phase are grouped by how many workgroups per CU their view count
-    // allows (capped at 4 waves per SIMD); one launch per group, largest occupancy first.
-    const int wg_cap = 16 / tile_waves(c->cfg_rows);
-    auto wg_per_cu = [&](int n) { return std::min(wg_cap, (int)((size_t)160 * 1024 / pass_lds_bytes(n, c->cfg_rows))); };
+    // allows (capped at 4 waves per SIMD) and by tile rows; one launch per group, largest occupancy first.
+    auto wg_per_cu = [&](int n) {
+        const int rows = job_rows(n);
+        return std::min(16 / tile_waves(rows), (int)(kLdsPerCu / pass_lds_bytes(n, rows)));
+    };
     auto add_group = [&](int kind, int colour, int t, const std::vector<int> &act) {
-        Phase ph{kind, colour, t, 0, 0, (int)tab.size(), 0, 0};
+        Phase ph{kind, colour, t, 0, 0, (int)tab.size(), 0, 0, c->cfg_rows};
         ph.n_active = (int)act.size();
         if (ph.n_active == 0) return;
         for (int j : act) ph.max_src = std::max(ph.max_src, jobs[j].n_src);
+        if (kind == 1) ph.rows = job_rows(jobs[act[0]].n_src);
         // work items per job: initialisation blocks or pass tiles
         auto items = [&](int j) { return kind == 0 ? hj[j].n_iblocks : hj[j].n_tiles; };
         int acc = 0;
@@ -480,12 +489,13 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
             add_group(kind, colour, t, act);
             return;
         }
-        for (int w = wg_cap; w >= 1; --w) {
-            std::vector<int> grp;
-            for (int j : act)
-                if (std::max(1, wg_per_cu(jobs[j].n_src)) == w) grp.push_back(j);
-            add_group(kind, colour, t, grp);
-        }
+        for (int rows = 4; rows >= 2; --rows)
+            for (int w = 16 / tile_waves(rows); w >= 1; --w) {
+                std::vector<int> grp;
+                for (int j : act)
+                    if (job_rows(jobs[j].n_src) == rows && std::max(1, wg_per_cu(jobs[j].n_src)) == w) grp.push_back(j);
+                add_group(kind, colour, t, grp);
+            }
     };
     add_phase(0, 0, 0);
     add_phase(0, 1, 0);
@@ -634,7 +644,7 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
         b.colour = ph.colour;
         b.kind = ph.kind;
         b.order = c->cfg_order;
-        b.rows = c->cfg_rows;
+        b.rows = ph.rows;
         b.conf_min = c->p.conf_min;
         b.counters = c->d_bcount;
         b.tiles_done = tiles_done;

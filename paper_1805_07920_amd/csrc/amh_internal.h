@@ -19,10 +19,11 @@ constexpr int kPix = 8;               // half-pass: same-colour pixels per tile 
 constexpr int kGroups = 7;            // ablation build: pixels per wave (7 groups x 9 lanes = 63 lanes)
 constexpr int kRows = 9;              // ... 8 propagated hypotheses + the pixel's own
 constexpr int kTilePix = kGroups;     // ... same-colour pixels per tile row
-// image rows per workgroup tile of the half-pass: 4 by default, 2 as the autotuner's alternative tile shape
+// image rows per workgroup tile of the half-pass: 4 by default (3 for many sources, pass_tile_rows; 1 for small
+// references, kSmallTiles), 2 as the autotuner's alternative tile shape
 constexpr int kDefaultTileRows = 4;
-// waves of a half-pass workgroup with a tile of `rows` image rows: one per row, and four for the one-row tile of small
-// references, whose evaluations they share
+// waves of a half-pass workgroup with a tile of `rows` image rows: one per row, and four for 1 and 3 rows, whose
+// evaluations they share
 constexpr int tile_waves(int rows) { return rows == 2 ? 2 : 4; }
 // A reference with at most this many 4-row tiles of a colour takes one-row tiles: fewer workgroups than the card's 256
 // CUs leave most of them idle, and a pass lasts as long as one workgroup's chain of evaluations, which four waves on
@@ -204,5 +205,11 @@ hipError_t launch_batch(const BatchPhaseArgs &b, int half, int max_src, hipStrea
 hipError_t launch_stamp(unsigned long long *p, hipStream_t s);
 hipError_t launch_sweep(const SweepArgs &a, int half, hipStream_t s);
 size_t pass_lds_bytes(int n_src, int rows);
+constexpr size_t kLdsPerCu = 160 * 1024;
+// Rows of the default tile by view count: 4 as long as four of their workgroups share a CU's LDS (12 views), else 3
+// with a fourth wave that only helps, which keep 16 waves on the CU up to 22 views.  1600x1060, 3 iterations, 4 rows
+// against 3: 12 views 15.8 and 16.9 ms, 14 views 20.0 and 19.0, 20 float16 views 30.0 and 28.5, 24 float16 views 42.5
+// and 36.8.
+int pass_tile_rows(int n_src);
 
 }  // namespace amh

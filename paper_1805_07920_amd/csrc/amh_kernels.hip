@@ -1573,6 +1573,8 @@ size_t pass_lds_bytes(int n_src, int rows) {
     return a > b ? a : b;
 }
 
+int pass_tile_rows(int n_src) { return 4 * pass_lds_bytes(n_src, 4) <= kLdsPerCu ? 4 : 3; }
+
 __device__ __forceinline__ HalfLds carve_half(unsigned char *smem, int n_src, int rows) {
     size_t off[18];
     half_layout(n_src, rows, off);
@@ -2851,6 +2853,7 @@ hipError_t launch_pass(const PassArgs &a, int half, hipStream_t s) {
     } else {
         if (a.rows == 1) launch_pass_rows<1>(a, half, s);
         else if (a.rows == 2) launch_pass_rows<2>(a, half, s);
+        else if (a.rows == 3) launch_pass_rows<3>(a, half, s);
         else if (a.rows == 4) launch_pass_rows<4>(a, half, s);
         else return hipErrorInvalidValue;
     }
@@ -2871,6 +2874,9 @@ hipError_t launch_batch(const BatchPhaseArgs &b, int half, int max_src, hipStrea
     if (b.rows == 2) {
         if (half) AMH_LAUNCH((batch_kernel<1, 2>), grid, block, lds, s, b);
         else AMH_LAUNCH((batch_kernel<0, 2>), grid, block, lds, s, b);
+    } else if (b.rows == 3) {
+        if (half) AMH_LAUNCH((batch_kernel<1, 3>), grid, block, lds, s, b);
+        else AMH_LAUNCH((batch_kernel<0, 3>), grid, block, lds, s, b);
     } else if (b.rows == 4) {
         if (half) AMH_LAUNCH((batch_kernel<1, 4>), grid, block, lds, s, b);
         else AMH_LAUNCH((batch_kernel<0, 4>), grid, block, lds, s, b);

@@ -1,5 +1,5 @@
 """The half-pass at the edges of its work split: view counts around the rule that scores the own planes with the
-propagated ones, tiles of 1, 2 and 4 rows, hypotheses that are all the same plane (one evaluation serves every row)
+propagated ones, tiles of 1, 2, 3 and 4 rows, hypotheses that are all the same plane (one evaluation serves every row)
 or all different, six candidates, no own row -- against the CPU oracle (the bars of test_gpu_parity) and, across tile
 shapes, bit for bit."""
 import numpy as np
@@ -37,7 +37,7 @@ def scene(w, h, n, dtype="f32"):
 @pytest.mark.parametrize("w,h,n,t,colour,refine,own", [
     (131, 77, 1, 1, 0, 1, 1), (131, 77, 2, 1, 1, 1, 0), (131, 77, 4, 3, 0, 1, 1), (131, 77, 5, 3, 1, 1, 1),
     (203, 165, 3, 1, 0, 1, 1), (203, 165, 4, 3, 1, 1, 0), (203, 165, 5, 1, 1, 1, 1), (203, 165, 9, 3, 0, 1, 1),
-    (203, 165, 5, 1, 0, 0, 0), (203, 165, 32, 1, 0, 1, 1),
+    (203, 165, 5, 1, 0, 0, 0), (203, 165, 13, 3, 1, 1, 1), (203, 163, 32, 1, 0, 1, 1),
 ])
 def test_pass_matches_oracle(amh, oracle_mod, w, h, n, t, colour, refine, own):
     say("case half-pass", w, h, n, t, colour, refine, own)
@@ -109,9 +109,10 @@ def test_short_counter_with_the_own_planes_scored_last(amh, oracle_mod):
 
 @pytest.mark.parametrize("w,h,n,iters,own,dtype", [(17, 9, 1, 2, 1, "f32"), (48, 37, 3, 4, 0, "f32"),
                                                    (131, 77, 4, 4, 1, "f32"), (131, 77, 5, 4, 1, "f16"),
-                                                   (131, 77, 12, 2, 1, "f32")])
+                                                   (131, 77, 12, 2, 1, "f32"), (131, 77, 13, 4, 1, "f32"),
+                                                   (131, 77, 21, 2, 1, "f16")])
 def test_tile_shapes_agree_bit_for_bit(amh, w, h, n, iters, own, dtype):
-    """One-row tiles (a small single image) against the batch's 4- and 2-row tiles."""
+    """One-row tiles (a small single image) against the batch's 4-row (3-row from 13 views) and 2-row tiles."""
     say("case tile shapes", w, h, n, iters, own, dtype)
     sc = scene(w, h, n, dtype)
     srcs = list(range(1, n + 1))
