@@ -3,10 +3,10 @@
 // matrix cores, its backward pass, the training loss and Adam.
 //
 // Convolutions are implicit GEMMs on v_mfma_f32_16x16x32_bf16:
-//   forward / input gradient: rows = 16 pixels, columns = 16 output channels,
+//   forward / input gradient: rows = 16 output channels, columns = 16 pixels,
 //     K = taps x input channels (padded to a multiple of 32 with zero weights);
-//     each lane feeds 8 consecutive channels of one tap of one pixel, so an A
-//     operand is one 16-byte load;
+//     each lane feeds 8 consecutive channels of one tap of one pixel, one
+//     16-byte LDS read;
 //   weight gradient: rows = 16 output channels, columns = 16 (tap, channel)
 //     pairs, K = pixels, split over workgroups into partial sums that a second
 //     kernel adds in a fixed order (deterministic, no atomics).
@@ -24,6 +24,7 @@ namespace nn {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 #define NN_LAUNCH(...)                   \
     do {                                 \
@@ -31,181 +32,438 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
         hipLaunchKernelGGL(__VA_ARGS__); \
     } while (0)
 
-// ---------------------------------------------------------------------------
-// convolution (forward, and input gradient with transposed weights)
-// ---------------------------------------------------------------------------
-template <int NT, int OUT_F32>
-__global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int P = a.n * a.h * a.w;
-    const int p0 = (blockIdx.x * 4 + wave) * 16;
-    if (p0 >= P) return;  // no barriers in this kernel
-    const int row = lane & 15, grp = lane >> 4;
-    const int p = p0 + row;
-    const bool pv = p < P;
-    int b = 0, y = 0, x = 0;
-    if (pv) {
-        x = p % a.w;
-        const int t = p / a.w;
-        y = t % a.h;
-        b = t / a.h;
-    }
-    f32x4 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r = a.ks >> 1;
-    const int K = a.ks * a.ks * a.cin;
-    const bf16_t *wrow = a.wgt + (size_t)row * a.kpad;
-    const size_t wstride = (size_t)16 * a.kpad;
-    for (int k0 = 0; k0 < a.kpad; k0 += 32) {
-        const int k = k0 + grp * 8;
-        u32x4 av = {0u, 0u, 0u, 0u};
-        if (pv && k < K) {
-            const int tap = k / a.cin, c = k - tap * a.cin;
-            const int ty = tap / a.ks;
-            const int yy = y + ty - r, xx = x + (tap - ty * a.ks) - r;
-            if (yy >= 0 && yy < a.h && xx >= 0 && xx < a.w)
-                av = *reinterpret_cast<const u32x4 *>(a.x + ((size_t)(b * a.h + yy) * a.w + xx) * a.cin + c);
-        }
-        const bf16x8 A = __builtin_bit_cast(bf16x8, av);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const u32x4 bv = *reinterpret_cast<const u32x4 *>(wrow + t * wstride + k);
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, bv), acc[t], 0, 0, 0);
-        }
-    }
-    // acc[t][i] holds output (pixel p0 + 4 grp + i, channel 16 t + row)
-    const int C = NT * 16;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int co = t * 16 + row;
-        const float bias = a.bias ? a.bias[co] : 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int pp = p0 + 4 * grp + i;
-            if (pp >= P) continue;
-            float v = acc[t][i] + bias;
-            if (a.relu) v = fmaxf(v, 0.f);
-            const size_t o = (size_t)pp * C + co;
-            if (a.mask && !(bf2f(a.mask[o]) > 0.f)) v = 0.f;
-            if (OUT_F32) reinterpret_cast<float *>(a.y)[o] = v;
-            else reinterpret_cast<bf16_t *>(a.y)[o] = f2bf(v);
-        }
-    }
+__device__ __forceinline__ float sigmoidf(float z) { return 1.f / (1.f + __expf(-z)); }
+
+// depth head: q = clamp(q_ref + R tanh(z0), q_far, q_near); returns q and dq/dz0 (0 where clamped)
+__device__ __forceinline__ float head_q(float z0, float q_ref, const DepthHead &dh, float &dq) {
+    const float th = tanhf(z0);
+    const float u = fmaf(dh.R, th, q_ref);
+    const bool inside = u > dh.q_far && u < dh.q_near;
+    dq = inside ? dh.R * (1.f - th * th) : 0.f;
+    return fminf(fmaxf(u, dh.q_far), dh.q_near);
+}
+
+// the value held by the other lane of the pair (lanes 2 i, 2 i + 1)
+__device__ __forceinline__ float pair_swap(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
 }
 
 // ---------------------------------------------------------------------------
-// weight gradient: part[s][co][k] = sum over the pixels of split s of
-// g[p][co] * x[p + offset(tap)][c], k = tap * cin + c;  bpart[s][co] = sum g[p][co]
+// 3x3 convolution (forward, and input gradient with transposed weights).
+//
+// A workgroup of 4 waves takes 16 x TH pixels of one image and every output
+// channel: the input tile with its one-pixel halo is staged in LDS (zeros
+// outside the image; a concatenation's two sources are read where they lie,
+// the low-resolution one at half the coordinates), and the weights are the
+// MFMA's first operand, read straight from the cache.  A lane then holds 4
+// consecutive channels of one pixel: 8-byte stores, the pooled half-resolution
+// map from the neighbouring lane and row, the head's product and decoding,
+// all in the same launch.  Pixels of the LDS tile are 2 CIN + 16 bytes apart,
+// an odd multiple of 16 bytes, so the 16 lanes of a row group read on
+// disjoint banks.
+//
+// Bound: launches and the latency of one tile's load and K / 32 dependent
+// MFMAs (8.3 GFLOP, 60 MB through the caches); the order of the sums over K is
+// fixed (steps of 32 from tap 0), whatever the tile.  Forward at 320 x 480
+// cells: 21 launches of kernels without LDS, scattered 2-byte stores and a
+// division per step took 226 us; NETFWD us with 11.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int s = blockIdx.x;
-    const int j0 = (blockIdx.y * 4 + wave) * 16;
-    const int co0 = blockIdx.z * 16;
-    if (j0 >= a.kpad) return;  // no barriers in this kernel
-    const int P = a.n * a.h * a.w;
-    const int beg = s * a.chunk, end = min(P, beg + a.chunk);
-    const int i16 = lane & 15, grp = lane >> 4;
-    const int co = co0 + i16;
-    const int j = j0 + i16;
-    const int K = a.ks * a.ks * a.cin;
-    const int r = a.ks >> 1;
-    const bool jv = j < K;
-    int c = 0, dy = 0, dx = 0;
-    if (jv) {
-        const int tap = j / a.cin;
-        c = j - tap * a.cin;
-        dy = tap / a.ks - r;
-        dx = tap - (tap / a.ks) * a.ks - r;
-    }
-    const bool do_bias = blockIdx.y == 0 && wave == 0;
-    float bsum = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int pb = beg; pb < end; pb += 32) {
-        const int q0 = pb + grp * 8;
-        int x = 0, y = 0, b = 0;
-        if (q0 < end) {
-            x = q0 % a.w;
-            const int t = q0 / a.w;
-            y = t % a.h;
-            b = t / a.h;
-        }
-        bf16_t av[8], bv[8];
+constexpr int kTileX = 16;
+
+// CIN input channels, the first C1 of them from the half-resolution source (0: one source); COUT output channels; WN
+// of the 4 waves split the output channels, the others the rows, NG rows each; POOL: also the 2 x 2 means; HEAD: also
+// the 1x1 head and its decoding
+template <int CIN, int COUT, int C1, int WN, int NG, bool POOL, bool HEAD>
+__global__ __launch_bounds__(256) void conv3_kernel(Conv3Args a) {
+    constexpr int NT = COUT / 16, NTW = (NT + WN - 1) / WN, TH = 4 / WN * NG;
+    constexpr int SW = kTileX + 2, SH = TH + 2, PXS = CIN * 2 + 16, C8 = CIN / 8;
+    constexpr int K = 9 * CIN, STEPS = (K + 31) / 32, KPAD = STEPS * 32;
+    static_assert(!POOL || NG == 2, "a wave pools its own two rows");
+    static_assert(!HEAD || (COUT == 16 && WN == 1), "the head reads a pixel's 16 channels");
+    __shared__ __align__(16) unsigned char tile[SH * SW * PXS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per = a.tiles_x * a.tiles_y;
+    const int b = blockIdx.x / per, tl = blockIdx.x - b * per;
+    const int y0 = tl / a.tiles_x * TH, x0 = (tl - tl / a.tiles_x * a.tiles_x) * kTileX;
+    const int h = a.h, w = a.w;
+
+    // input tile
+    constexpr int U = SH * SW * C8, LOADS = (U + 255) / 256;
+    u32x4 v[LOADS];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int q = q0 + e;
-            bf16_t ga = 0, xb = 0;
-            if (q < end) {
-                ga = a.g[(size_t)q * a.cout_pad + co];
-                const int yy = y + dy, xx = x + dx;
-                if (jv && yy >= 0 && yy < a.h && xx >= 0 && xx < a.w)
-                    xb = a.x[((size_t)(b * a.h + yy) * a.w + xx) * a.cin + c];
+    for (int l = 0; l < LOADS; ++l) {
+        const int i = tid + l * 256, px = i / C8, c = (i - px * C8) * 8;
+        const int sy = px / SW, sx = px - sy * SW, yy = y0 + sy - 1, xx = x0 + sx - 1;
+        v[l] = u32x4{0u, 0u, 0u, 0u};
+        if (i < U && yy >= 0 && yy < h && xx >= 0 && xx < w) {
+            const bf16_t *src =
+                c < C1 ? a.low + ((size_t)(b * (h / 2) + yy / 2) * (w / 2) + xx / 2) * C1 + c
+                       : a.x + ((size_t)(b * h + yy) * w + xx) * (CIN - C1) + (c - C1);
+            v[l] = *reinterpret_cast<const u32x4 *>(src);
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < LOADS; ++l) {
+        const int i = tid + l * 256, px = i / C8, c = (i - px * C8) * 8;
+        if (i < U) *reinterpret_cast<u32x4 *>(tile + px * PXS + c * 2) = v[l];
+        if (C1 == 0 && a.xcopy) {  // the kept copy of the input: each tile its own pixels
+            const int sy = px / SW, sx = px - sy * SW, yy = y0 + sy - 1, xx = x0 + sx - 1;
+            if (i < U && sy >= 1 && sy <= TH && sx >= 1 && sx <= kTileX && yy < h && xx < w)
+                *reinterpret_cast<u32x4 *>(a.xcopy + ((size_t)(b * h + yy) * w + xx) * CIN + c) = v[l];
+        }
+    }
+    __syncthreads();
+
+    const int px = lane & 15, grp = lane >> 4;
+    const int wn = wave % WN, row0 = wave / WN * NG;
+    f32x4 acc[NTW][NG];
+#pragma unroll
+    for (int t = 0; t < NTW; ++t)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[t][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned char *lb = tile + (row0 * SW + px) * PXS + (grp & 1) * 16;
+    const bf16_t *wb = a.wgt + (size_t)(wn * NTW * 16 + px) * KPAD + grp * 8;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        // lane groups 0, 1 hold channels k .. k + 15 of the step, groups 2, 3 the next 16: each within one tap
+        const int kA = 32 * s, kB = kA + 16;
+        const int tA = kA / CIN, tB = kB < K ? kB / CIN : 0;
+        const int offA = (tA / 3 * SW + tA % 3) * PXS + (kA - tA * CIN) * 2;
+        const int offB = kB < K ? (tB / 3 * SW + tB % 3) * PXS + (kB - tB * CIN) * 2 : 0;
+        const int off = grp < 2 ? offA : offB;
+        u32x4 bv[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            bv[g] = *reinterpret_cast<const u32x4 *>(lb + g * SW * PXS + off);
+            if (kB >= K && grp >= 2) bv[g] = u32x4{0u, 0u, 0u, 0u};  // past the last tap
+        }
+#pragma unroll
+        for (int t = 0; t < NTW; ++t) {
+            if (NT % WN != 0 && wn * NTW + t >= NT) continue;
+            const u32x4 av = *reinterpret_cast<const u32x4 *>(wb + (size_t)t * 16 * KPAD + kA);
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                acc[t][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
+                                                                    __builtin_bit_cast(bf16x8, bv[g]), acc[t][g], 0, 0, 0);
+        }
+    }
+
+    // acc[t][g][i]: output channel 16 (wn NTW + t) + 4 grp + i of pixel (x0 + px, y0 + row0 + g)
+    const int x = x0 + px;
+    if (HEAD) __syncthreads();  // the tile is read no more: each wave keeps its output rows there
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+        const int co = (wn * NTW + t) * 16 + 4 * grp;
+        if (NT % WN != 0 && wn * NTW + t >= NT) continue;
+        float bias[4] = {0.f, 0.f, 0.f, 0.f};
+        if (a.bias) {
+            const f32x4 bb = *reinterpret_cast<const f32x4 *>(a.bias + co);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bias[i] = bb[i];
+        }
+        float r[NG][4];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int y = y0 + row0 + g;
+            const bool in = y < h && x < w;
+            const size_t o = ((size_t)(b * h + y) * w + x) * COUT + co;
+            u32x2 m = {0u, 0u};
+            if (a.mask && in) m = *reinterpret_cast<const u32x2 *>(a.mask + o);
+            bf16_t q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float u = acc[t][g][i] + bias[i];
+                if (a.relu) u = fmaxf(u, 0.f);
+                if (a.mask && !(bf2f((bf16_t)(m[i >> 1] >> (16 * (i & 1)))) > 0.f)) u = 0.f;
+                q[i] = f2bf(u);
+                r[g][i] = bf2f(q[i]);
             }
-            av[e] = ga;
-            bv[e] = xb;
-            if (do_bias) bsum += bf2f(ga);
-            if (++x == a.w) {
-                x = 0;
-                if (++y == a.h) {
-                    y = 0;
-                    ++b;
+            const u32x2 st = {(uint32_t)q[0] | ((uint32_t)q[1] << 16), (uint32_t)q[2] | ((uint32_t)q[3] << 16)};
+            if (in) *reinterpret_cast<u32x2 *>(a.y + o) = st;
+            if (HEAD) *reinterpret_cast<u32x2 *>(tile + ((wave * NG + g) * 16 + px) * 48 + grp * 8) = st;
+        }
+        if constexpr (POOL) {
+            // means of the stored values over 2 x 2 pixels: this lane's, the next lane's, then the row below
+            float m[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float n0 = pair_swap(r[0][i]), n1 = pair_swap(r[1][i]);
+                m[i] = ((((0.f + r[0][i]) + n0) + r[1][i]) + n1) * 0.25f;
+            }
+            const int y = y0 + row0;
+            if ((px & 1) == 0 && y < h && x < w) {
+                const u32x2 st = {(uint32_t)f2bf(m[0]) | ((uint32_t)f2bf(m[1]) << 16),
+                                  (uint32_t)f2bf(m[2]) | ((uint32_t)f2bf(m[3]) << 16)};
+                *reinterpret_cast<u32x2 *>(a.pool + ((size_t)(b * (h / 2) + y / 2) * (w / 2) + x / 2) * COUT + co) = st;
+            }
+        }
+    }
+    if constexpr (HEAD) {
+        // the 1x1 head on the stored values: one MFMA, channels 16 .. 31 of its K zero
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const u32x4 hw = *reinterpret_cast<const u32x4 *>(a.head_w + px * 32 + grp * 8);
+        const f32x4 hb = *reinterpret_cast<const f32x4 *>(a.head_b + 4 * grp);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            u32x4 dv = {0u, 0u, 0u, 0u};
+            if (grp < 2) dv = *reinterpret_cast<const u32x4 *>(tile + ((wave * NG + g) * 16 + px) * 48 + grp * 16);
+            f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hw), __builtin_bit_cast(bf16x8, dv), z,
+                                                        0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] += hb[i];
+            const float z4 = __shfl(z[0], lane + 16, 64);  // lane group 1 holds outputs 4 .. 7
+            const int y = y0 + row0 + g;
+            if (y < h && x < w && grp < 2) {
+                const size_t p = (size_t)(b * h + y) * w + x;
+                *reinterpret_cast<f32x4 *>(a.z + p * kHeadPitch + 4 * grp) = z;
+                if (grp == 0) {
+                    const float qr = a.q_ref[p];
+                    a.q_copy[p] = qr;
+                    if (a.out) {
+                        const float nx = z[1], ny = z[2], nz = z[3];
+                        const float inv = 1.f / __builtin_sqrtf(nx * nx + ny * ny + nz * nz);
+                        float dq;
+                        float *o = a.out + p * 5;
+                        o[0] = 1.f / head_q(z[0], qr, a.dh, dq);
+                        o[1] = nx * inv;
+                        o[2] = ny * inv;
+                        o[3] = nz * inv;
+                        o[4] = sigmoidf(z4);
+                    }
                 }
             }
         }
-        u32x4 au, bu;
+    }
+}
+
+// Input gradient of the 1x1 head: g [P][16] (the loss's) x W' [16][32], masked by the layer below.
+__global__ __launch_bounds__(256) void head_grad_kernel(const bf16_t *g, const bf16_t *wgt, const bf16_t *mask, int P,
+                                                        bf16_t *out) {
+    const int lane = threadIdx.x & 63, px = lane & 15, grp = lane >> 4;
+    const long long p = ((long long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 + px;
+    const bool in = p < P;
+    const u32x4 av = *reinterpret_cast<const u32x4 *>(wgt + px * 32 + grp * 8);
+    u32x4 bv = {0u, 0u, 0u, 0u};
+    if (in && grp < 2) bv = *reinterpret_cast<const u32x4 *>(g + p * 16 + grp * 8);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc, 0,
+                                                  0, 0);
+    if (!in) return;
+    const u32x2 m = *reinterpret_cast<const u32x2 *>(mask + p * 16 + 4 * grp);
+    bf16_t q[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            au[e] = (uint32_t)av[2 * e] | ((uint32_t)av[2 * e + 1] << 16);
-            bu[e] = (uint32_t)bv[2 * e] | ((uint32_t)bv[2 * e + 1] << 16);
+    for (int i = 0; i < 4; ++i) {
+        float u = acc[i] + 0.f;
+        if (!(bf2f((bf16_t)(m[i >> 1] >> (16 * (i & 1)))) > 0.f)) u = 0.f;
+        q[i] = f2bf(u);
+    }
+    *reinterpret_cast<u32x2 *>(out + p * 16 + 4 * grp) =
+        u32x2{(uint32_t)q[0] | ((uint32_t)q[1] << 16), (uint32_t)q[2] | ((uint32_t)q[3] << 16)};
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradient: part[s][co][k] = sum over the pixels of split s of
+// g[p][co] * x[p + offset(tap)][c], k = tap * cin + c;  bpart[s][co] = sum g[p][co].
+//
+// The product's K is the pixel, but memory holds a pixel's channels together:
+// the operands come through the LDS transpose read (4 pixels x 16 channels per
+// 16 lanes, each lane naming the pixel row it reads), so a tap's shift, the
+// image borders and the split's end are only a choice of row -- a row of
+// zeros where the tap falls outside.  A workgroup takes one split, one group
+// of 16 input channels and one row of taps, a wave one tap and every output
+// channel; blocks of kWgBlock pixels are staged while the next one's loads are
+// in flight.  Sums run over 32 pixels per MFMA in pixel order, as before.
+//
+// Bound: LDS reads and the staging (a tap reads its 32 pixels x 16 channels
+// once per MFMA).  16 x 120 x 160 cells, all layers: 12 launches with 16
+// two-byte loads per lane and MFMA took 1490 us; WGRAD us.
+// ---------------------------------------------------------------------------
+constexpr int kWgBlock = 256;
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+__device__ __forceinline__ s16x4 lds_read_tr(const bf16_t *p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+}
+__device__ __forceinline__ bf16x8 join8(s16x4 lo, s16x4 hi) {
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// NCO: output channels / 16; TAPS: 3 (3x3, blockIdx.z the row of taps) or 1 (1x1)
+template <int NCO, int TAPS>
+__global__ __launch_bounds__(64 * TAPS) void wgrad_kernel(WgradArgs a) {
+    constexpr int COUT = NCO * 16, NTHR = 64 * TAPS, B = kWgBlock;
+    constexpr int XU = (B + 2) * 2, GU = B * COUT / 8;                       // 16-byte units of a block
+    constexpr int XL = (XU + NTHR - 1) / NTHR, GL = (GU + NTHR - 1) / NTHR;  // ... per thread
+    __shared__ __align__(16) bf16_t xs[(B + 2 + 1) * 16];  // pixels lin0 .. lin0 + B + 1, and a row of zeros
+    __shared__ __align__(16) bf16_t gs[B * COUT];
+    __shared__ unsigned char flags[B];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s = blockIdx.x, cg = blockIdx.y;
+    const int dy = TAPS == 3 ? (int)blockIdx.z - 1 : 0, dx = TAPS == 3 ? wave - 1 : 0;
+    const int w = a.w, h = a.h;
+    const int P = a.n * h * w;
+    const int beg = s * a.chunk, end = min(P, beg + a.chunk);
+    // the channel group's source: the half-resolution one, or the other at its own channel offset
+    const int c0 = cg * 16;
+    const bool from_low = c0 < a.c1;
+    const bf16_t *src = from_low ? a.low + c0 : a.x + (c0 - a.c1);
+    const int cs = from_low ? a.c1 : a.cin - a.c1;  // channels of that source
+    if (tid < 16) xs[(B + 2) * 16 + tid] = 0;
+
+    const auto load_x = [&](int pb, int u) {  // unit u: half a pixel's 16 channels
+        u32x4 v = {0u, 0u, 0u, 0u};
+        const int lin = pb + dy * w - 1 + (u >> 1);
+        if (u < XU && lin >= 0 && lin < P) {
+            size_t q = lin;
+            if (from_low) {
+                const int x = lin % w, t = lin / w, y = t % h, b = t / h;
+                q = (size_t)(b * (h / 2) + y / 2) * (w / 2) + x / 2;
+            }
+            v = *reinterpret_cast<const u32x4 *>(src + q * cs + (u & 1) * 8);
         }
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, au), __builtin_bit_cast(bf16x8, bu),
-                                                      acc, 0, 0, 0);
-    }
-    // acc[i] = dW[co0 + 4 grp + i][j0 + i16]
-    float *dst = a.part + (size_t)s * a.cout_pad * a.kpad;
+        return v;
+    };
+    const auto load_g = [&](int pb, int u) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        const int q = pb + u / (COUT / 8);
+        if (u < GU && q < end) v = *reinterpret_cast<const u32x4 *>(a.g + (size_t)q * COUT + (u % (COUT / 8)) * 8);
+        return v;
+    };
+    u32x4 xv[XL], gv[GL];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dst[(size_t)(co0 + 4 * grp + i) * a.kpad + j0 + i16] = acc[i];
-    if (do_bias) {
-        bsum += __shfl_xor(bsum, 16, 64);
-        bsum += __shfl_xor(bsum, 32, 64);
-        if (grp == 0) a.bpart[(size_t)s * a.cout_pad + co] = bsum;
+    for (int l = 0; l < XL; ++l) xv[l] = load_x(beg, tid + l * NTHR);
+#pragma unroll
+    for (int l = 0; l < GL; ++l) gv[l] = load_g(beg, tid + l * NTHR);
+
+    f32x4 acc[NCO];
+    float bsum[NCO];
+#pragma unroll
+    for (int t = 0; t < NCO; ++t) {
+        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bsum[t] = 0.f;
+    }
+    const bool do_bias = cg == 0 && (TAPS == 1 || blockIdx.z == 0) && wave == 0;
+    // what a pixel must satisfy for this tap: inside the split, and the neighbour inside the image
+    const int need = 16 | (dx < 0 ? 1 : dx > 0 ? 2 : 0) | (dy < 0 ? 4 : dy > 0 ? 8 : 0);
+    const int l16 = lane & 15, grp = lane >> 4, sub = l16 >> 2, c4 = 4 * (l16 & 3);
+    for (int pb = beg; pb < end; pb += B) {
+        __syncthreads();  // the last block's reads
+#pragma unroll
+        for (int l = 0; l < XL; ++l)
+            if (tid + l * NTHR < XU) *reinterpret_cast<u32x4 *>(xs + (tid + l * NTHR) * 8) = xv[l];
+#pragma unroll
+        for (int l = 0; l < GL; ++l)
+            if (tid + l * NTHR < GU) *reinterpret_cast<u32x4 *>(gs + (tid + l * NTHR) * 8) = gv[l];
+        for (int i = tid; i < B; i += NTHR) {
+            const int q = pb + i, x = q % w, y = q / w % h;
+            flags[i] = (unsigned char)((x > 0 ? 1 : 0) | (x + 1 < w ? 2 : 0) | (y > 0 ? 4 : 0) | (y + 1 < h ? 8 : 0) |
+                                       (q < end ? 16 : 0));
+        }
+        __syncthreads();
+        if (pb + B < end) {
+#pragma unroll
+            for (int l = 0; l < XL; ++l) xv[l] = load_x(pb + B, tid + l * NTHR);
+#pragma unroll
+            for (int l = 0; l < GL; ++l) gv[l] = load_g(pb + B, tid + l * NTHR);
+        }
+        const int steps = min(B, end - pb + 31) / 32;
+#pragma unroll 2
+        for (int st = 0; st < steps; ++st) {
+            const int i0 = st * 32 + grp * 8 + sub, i1 = i0 + 4;  // the lane's pixel rows of the block
+            const int r0 = (flags[i0] & need) == need ? i0 + 1 + dx : B + 2;
+            const int r1 = (flags[i1] & need) == need ? i1 + 1 + dx : B + 2;
+            const bf16x8 bx = join8(lds_read_tr(xs + r0 * 16 + c4), lds_read_tr(xs + r1 * 16 + c4));
+#pragma unroll
+            for (int t = 0; t < NCO; ++t) {
+                const s16x4 g0 = lds_read_tr(gs + i0 * COUT + t * 16 + c4);
+                const s16x4 g1 = lds_read_tr(gs + i1 * COUT + t * 16 + c4);
+                if (do_bias) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bsum[t] += bf2f((bf16_t)g0[e]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bsum[t] += bf2f((bf16_t)g1[e]);
+                }
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(join8(g0, g1), bx, acc[t], 0, 0, 0);
+            }
+        }
+    }
+    // acc[t][i] = dW[16 t + 4 grp + i][tap cin + 16 cg + l16]
+    const int tap = TAPS == 3 ? (dy + 1) * 3 + dx + 1 : 0;
+    float *dst = a.part + (size_t)s * COUT * a.kpad + tap * a.cin + c0 + l16;
+#pragma unroll
+    for (int t = 0; t < NCO; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dst[(size_t)(t * 16 + 4 * grp + i) * a.kpad] = acc[t][i];
+        if (do_bias) {
+            bsum[t] += __shfl_xor(bsum[t], 16, 64);
+            bsum[t] += __shfl_xor(bsum[t], 32, 64);
+            if (grp == 0) a.bpart[(size_t)s * COUT + t * 16 + l16] = bsum[t];
+        }
     }
 }
 
-// grad[e] = sum_s part[s][e] for e < n_w (weights), then the biases
-__global__ void wgrad_reduce_kernel(const float *part, const float *bpart, int splits, int n_w, int n_b, float *gw,
-                                    float *gb) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n_w) {
-        float s = 0.f;
-        for (int k = 0; k < splits; ++k) s += part[(size_t)k * n_w + e];
-        gw[e] = s;
-    } else if (e < n_w + n_b) {
-        const int o = e - n_w;
-        float s = 0.f;
-        for (int k = 0; k < splits; ++k) s += bpart[(size_t)k * n_b + o];
-        gb[o] = s;
+// The gradient of every parameter from the splits' partial sums, in split order (one launch for the network; the
+// loads of 16 splits are in flight together).  Padding gets 0.
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(LayerTable tab, const float *part, int n_pad, float *grad) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= n_pad) return;
+    int li = 0;
+    for (int l = 1; l < tab.n; ++l) li = e >= tab.l[l].w_off ? l : li;
+    const LayerDims d = tab.l[li];
+    const int n_w = d.cout_pad * d.kpad;
+    const int o = e - d.w_off;
+    bool live;
+    const float *src;
+    int stride;
+    if (o < n_w) {
+        live = o % d.kpad < d.taps * d.cin;
+        src = part + (size_t)kMaxSplits * d.w_off + o;
+        stride = n_w;
+    } else {
+        live = e - d.b_off < d.cout_pad;
+        src = part + (size_t)kMaxSplits * d.b_off + (e - d.b_off);
+        stride = d.cout_pad;
     }
+    float sum = 0.f;
+    if (live) {
+        int k = 0;
+        for (; k + 16 <= d.splits; k += 16) {
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = src[(size_t)(k + i) * stride];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum += v[i];
+        }
+        for (; k < d.splits; ++k) sum += src[(size_t)k * stride];
+    }
+    grad[e] = sum;
 }
 
-// W'[ci][tap' * cout_pad + co] = W[co][(ks^2 - 1 - tap') * cin + ci]   (zero beyond ks^2 * cout_pad)
-__global__ void transpose_w_kernel(const bf16_t *w, int cin, int cout_pad, int kpad, int ks, bf16_t *wt,
-                                   int kpad_t) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= cin * kpad_t) return;
-    const int ci = e / kpad_t, k = e - ci * kpad_t;
+// Transposed, tap-mirrored weights of every layer for the input gradients, in one launch:
+// W'[ci][tap' * cout_pad + co] = W[co][(taps - 1 - tap') * cin + ci]   (zero beyond taps * cout_pad)
+__global__ __launch_bounds__(256) void transpose_w_kernel(LayerTable tab, const bf16_t *w, int n, bf16_t *wt) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= n) return;
+    int li = 0;
+    for (int l = 1; l < tab.n; ++l) li = e >= tab.l[l].t_off ? l : li;
+    const LayerDims d = tab.l[li];
+    const int o = e - d.t_off, ci = o / d.kpad_t, k = o - ci * d.kpad_t;
     bf16_t v = 0;
-    if (k < ks * ks * cout_pad) {
-        const int tp = k / cout_pad, co = k - tp * cout_pad;
-        const int tap = ks * ks - 1 - tp;
-        v = w[(size_t)co * kpad + tap * cin + ci];
+    if (ci < d.cin && k < d.taps * d.cout_pad) {
+        const int tp = k / d.cout_pad, co = k - tp * d.cout_pad;
+        v = w[d.w_off + (size_t)co * d.kpad + (d.taps - 1 - tp) * d.cin + ci];
     }
     wt[e] = v;
 }
 
 // ---------------------------------------------------------------------------
-// pooling, upsampling + concatenation, and their gradients (8 channels/thread)
+// gradients of the pooling and of the upsampling + concatenation (8 channels/thread)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void load8(const bf16_t *p, float v[8]) {
     const u32x4 u = *reinterpret_cast<const u32x4 *>(p);
@@ -221,37 +479,6 @@ __device__ __forceinline__ void store8(bf16_t *p, const float v[8]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) u[e] = (uint32_t)f2bf(v[2 * e]) | ((uint32_t)f2bf(v[2 * e + 1]) << 16);
     *reinterpret_cast<u32x4 *>(p) = u;
-}
-
-// y[b][i][j] = mean of x over the 2 x 2 block (h, w: output size)
-__global__ void pool_kernel(const bf16_t *x, int n, int h, int w, int C, bf16_t *y) {
-    const int C8 = C / 8;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * h * w * C8) return;
-    const int c = (e % C8) * 8, q = e / C8;
-    const int j = q % w, t = q / w, i = t % h, b = t / h;
-    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0}, v[8];
-    for (int dy = 0; dy < 2; ++dy)
-        for (int dx = 0; dx < 2; ++dx) {
-            load8(x + ((size_t)(b * 2 * h + 2 * i + dy) * 2 * w + 2 * j + dx) * C + c, v);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) s[k] += v[k];
-        }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s[k] *= 0.25f;
-    store8(y + (size_t)q * C + c, s);
-}
-
-// out[b][y][x] = [low[b][y/2][x/2] (C1 channels), skip[b][y][x] (C2)]  (h, w: output size)
-__global__ void upcat_kernel(const bf16_t *low, int C1, const bf16_t *skip, int C2, int n, int h, int w, bf16_t *out) {
-    const int C = C1 + C2, C8 = C / 8;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * h * w * C8) return;
-    const int c = (e % C8) * 8, q = e / C8;
-    const int x = q % w, t = q / w, y = t % h, b = t / h;
-    const bf16_t *src = c < C1 ? low + ((size_t)(b * (h / 2) + y / 2) * (w / 2) + x / 2) * C1 + c
-                               : skip + (size_t)q * C2 + (c - C1);
-    *reinterpret_cast<u32x4 *>(out + (size_t)q * C + c) = *reinterpret_cast<const u32x4 *>(src);
 }
 
 // gradient of an encoder output e that feeds both the pooling below and the
@@ -295,35 +522,8 @@ __global__ void up_grad_kernel(const bf16_t *dcat, int Ccat, const bf16_t *act, 
 }
 
 // ---------------------------------------------------------------------------
-// head decoding, loss and its gradient
+// loss and its gradient
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float sigmoidf(float z) { return 1.f / (1.f + __expf(-z)); }
-
-// depth head: q = clamp(q_ref + R tanh(z0), q_far, q_near); returns q and dq/dz0 (0 where clamped)
-__device__ __forceinline__ float head_q(float z0, float q_ref, const DepthHead &dh, float &dq) {
-    const float th = tanhf(z0);
-    const float u = fmaf(dh.R, th, q_ref);
-    const bool inside = u > dh.q_far && u < dh.q_near;
-    dq = inside ? dh.R * (1.f - th * th) : 0.f;
-    return fminf(fmaxf(u, dh.q_far), dh.q_near);
-}
-
-// z: [P][16] head output (channels 0..4 used) -> out [P][5]: depth, unit normal, confidence
-__global__ void decode_kernel(const float *z, const float *q_ref, int P, DepthHead dh, float *out) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const float *zp = z + (size_t)p * 16;
-    const float nx = zp[1], ny = zp[2], nz = zp[3];
-    const float inv = 1.f / __builtin_sqrtf(nx * nx + ny * ny + nz * nz);
-    float dq;
-    float *o = out + (size_t)p * 5;
-    o[0] = 1.f / head_q(zp[0], q_ref[p], dh, dq);
-    o[1] = nx * inv;
-    o[2] = ny * inv;
-    o[3] = nz * inv;
-    o[4] = sigmoidf(zp[4]);
-}
-
 // per pixel: w (|s - t_d| + 1 - n_hat . n_t) + softplus(z4) - t_c z4, and dL/dz / P
 __global__ __launch_bounds__(256) void loss_kernel(const float *z, const float *q_ref, const float *target, int P,
                                                    DepthHead dh, bf16_t *dz, float *part) {
@@ -331,7 +531,7 @@ __global__ __launch_bounds__(256) void loss_kernel(const float *z, const float *
     const int p = blockIdx.x * 256 + threadIdx.x;
     float L = 0.f;
     if (p < P) {
-        const float *zp = z + (size_t)p * 16;
+        const float *zp = z + (size_t)p * kHeadPitch;
         const float *tp = target + (size_t)p * 6;
         const float invP = 1.f / (float)P;
         const float span = dh.d_max - dh.d_min;
@@ -442,53 +642,83 @@ __global__ void to_bf16_kernel(const float *src, int n, bf16_t *dst) {
 // ---------------------------------------------------------------------------
 static inline dim3 grid1(long long n, int bs = 256) { return dim3((unsigned)((n + bs - 1) / bs)); }
 
-template <int NT>
-static void launch_conv_nt(const ConvArgs &a, hipStream_t s) {
-    const int P = a.n * a.h * a.w;
-    const dim3 grid((P + 63) / 64);
-    if (a.out_f32) NN_LAUNCH((conv_kernel<NT, 1>), grid, dim3(256), 0, s, a);
-    else NN_LAUNCH((conv_kernel<NT, 0>), grid, dim3(256), 0, s, a);
+template <int CIN, int COUT, int C1, int WN, int NG, bool POOL = false, bool HEAD = false>
+static hipError_t run_conv3(Conv3Args a, hipStream_t s) {
+    constexpr int TH = 4 / WN * NG;
+    a.tiles_x = (a.w + kTileX - 1) / kTileX;
+    a.tiles_y = (a.h + TH - 1) / TH;
+    const long long blocks = (long long)a.n * a.tiles_x * a.tiles_y;
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
+    NN_LAUNCH((conv3_kernel<CIN, COUT, C1, WN, NG, POOL, HEAD>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
-hipError_t launch_conv(const ConvArgs &a, hipStream_t s) {
-    if (a.n * a.h * a.w == 0) return hipSuccess;
+// Tile shapes: two rows per wave (8-row tiles) where an image has enough tiles for that, one row, or waves split over
+// the output channels, on the quarter- and eighth-resolution levels, whose few pixels would leave CUs idle.
+hipError_t launch_conv3(int cin, int cout, const Conv3Args &a, hipStream_t s) {
+    if (a.head_w) return cin == 48 && cout == 16 && a.low ? run_conv3<48, 16, 32, 1, 2, false, true>(a, s) : hipErrorInvalidValue;
+    if (a.low) {
+        if (cin == 112 && cout == 48) return run_conv3<112, 48, 64, 1, 1>(a, s);
+        if (cin == 80 && cout == 32) return run_conv3<80, 32, 48, 1, 2>(a, s);
+        return hipErrorInvalidValue;
+    }
+    if (a.pool) {
+        if (cin == 16 && cout == 16) return run_conv3<16, 16, 0, 1, 2, true>(a, s);
+        if (cin == 32 && cout == 32) return run_conv3<32, 32, 0, 1, 2, true>(a, s);
+        if (cin == 48 && cout == 48) return run_conv3<48, 48, 0, 1, 2, true>(a, s);
+        return hipErrorInvalidValue;
+    }
+    if (cin == 16) {
+        if (cout == 16) return run_conv3<16, 16, 0, 1, 2>(a, s);
+        if (cout == 32) return run_conv3<16, 32, 0, 1, 2>(a, s);
+        if (cout == 48) return run_conv3<16, 48, 0, 1, 2>(a, s);
+    } else if (cin == 32) {
+        if (cout == 16) return run_conv3<32, 16, 0, 1, 2>(a, s);
+        if (cout == 32) return run_conv3<32, 32, 0, 1, 2>(a, s);
+        if (cout == 48) return run_conv3<32, 48, 0, 1, 1>(a, s);
+        if (cout == 80) return run_conv3<32, 80, 0, 1, 2>(a, s);
+    } else if (cin == 48) {
+        if (cout == 32) return run_conv3<48, 32, 0, 1, 1>(a, s);
+        if (cout == 48) return run_conv3<48, 48, 0, 1, 1>(a, s);
+        if (cout == 64) return run_conv3<48, 64, 0, 4, 2>(a, s);
+        if (cout == 112) return run_conv3<48, 112, 0, 1, 1>(a, s);
+    } else if (cin == 64) {
+        if (cout == 48) return run_conv3<64, 48, 0, 1, 1>(a, s);
+        if (cout == 64) return run_conv3<64, 64, 0, 4, 2>(a, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_head_grad(const bf16_t *g, const bf16_t *wgt, const bf16_t *mask, int P, bf16_t *out, hipStream_t s) {
+    NN_LAUNCH(head_grad_kernel, grid1(P, 64), dim3(256), 0, s, g, wgt, mask, P, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_wgrad(const WgradArgs &a, int splits, hipStream_t s) {
+    const dim3 grid(splits, a.cin / 16, a.ks);
+    if (a.ks == 1) {
+        if (a.cout_pad != 16) return hipErrorInvalidValue;
+        NN_LAUNCH((wgrad_kernel<1, 1>), grid, dim3(64), 0, s, a);
+        return hipGetLastError();
+    }
     switch (a.cout_pad / 16) {
-        case 1: launch_conv_nt<1>(a, s); break;
-        case 2: launch_conv_nt<2>(a, s); break;
-        case 3: launch_conv_nt<3>(a, s); break;
-        case 4: launch_conv_nt<4>(a, s); break;
-        case 5: launch_conv_nt<5>(a, s); break;
-        case 6: launch_conv_nt<6>(a, s); break;
-        case 7: launch_conv_nt<7>(a, s); break;
+        case 1: NN_LAUNCH((wgrad_kernel<1, 3>), grid, dim3(192), 0, s, a); break;
+        case 2: NN_LAUNCH((wgrad_kernel<2, 3>), grid, dim3(192), 0, s, a); break;
+        case 3: NN_LAUNCH((wgrad_kernel<3, 3>), grid, dim3(192), 0, s, a); break;
+        case 4: NN_LAUNCH((wgrad_kernel<4, 3>), grid, dim3(192), 0, s, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_wgrad(const WgradArgs &a, float *gw, float *gb, int splits, hipStream_t s) {
-    const dim3 grid(splits, (a.kpad / 16 + 3) / 4, a.cout_pad / 16);
-    NN_LAUNCH(wgrad_kernel, grid, dim3(256), 0, s, a);
-    const int n_w = a.cout_pad * a.kpad, n_b = a.cout_pad;
-    NN_LAUNCH(wgrad_reduce_kernel, grid1(n_w + n_b), dim3(256), 0, s, a.part, a.bpart, splits, n_w, n_b, gw, gb);
+hipError_t launch_wgrad_reduce(const LayerTable &tab, const float *part, int n_pad, float *grad, hipStream_t s) {
+    NN_LAUNCH(wgrad_reduce_kernel, grid1(n_pad), dim3(256), 0, s, tab, part, n_pad, grad);
     return hipGetLastError();
 }
 
-hipError_t launch_transpose_w(const bf16_t *w, int cin, int cout_pad, int kpad, int ks, bf16_t *wt, int kpad_t,
-                              hipStream_t s) {
-    NN_LAUNCH(transpose_w_kernel, grid1((long long)cin * kpad_t), dim3(256), 0, s, w, cin, cout_pad, kpad, ks, wt,
-              kpad_t);
-    return hipGetLastError();
-}
-
-hipError_t launch_pool(const bf16_t *x, int n, int h, int w, int C, bf16_t *y, hipStream_t s) {
-    NN_LAUNCH(pool_kernel, grid1((long long)n * h * w * (C / 8)), dim3(256), 0, s, x, n, h, w, C, y);
-    return hipGetLastError();
-}
-
-hipError_t launch_upcat(const bf16_t *low, int C1, const bf16_t *skip, int C2, int n, int h, int w, bf16_t *out,
-                        hipStream_t s) {
-    NN_LAUNCH(upcat_kernel, grid1((long long)n * h * w * ((C1 + C2) / 8)), dim3(256), 0, s, low, C1, skip, C2, n, h,
-              w, out);
+hipError_t launch_transpose_w(const LayerTable &tab, const bf16_t *w, int n, bf16_t *wt, hipStream_t s) {
+    NN_LAUNCH(transpose_w_kernel, grid1(n), dim3(256), 0, s, tab, w, n, wt);
     return hipGetLastError();
 }
 
@@ -503,11 +733,6 @@ hipError_t launch_up_grad(const bf16_t *dcat, int Ccat, const bf16_t *act, int n
                           hipStream_t s) {
     NN_LAUNCH(up_grad_kernel, grid1((long long)n * h * w * (C1 / 8)), dim3(256), 0, s, dcat, Ccat, act, n, h, w, C1,
               g);
-    return hipGetLastError();
-}
-
-hipError_t launch_decode(const float *z, const float *q_ref, int P, const DepthHead &dh, float *out, hipStream_t s) {
-    NN_LAUNCH(decode_kernel, grid1(P), dim3(256), 0, s, z, q_ref, P, dh, out);
     return hipGetLastError();
 }
 

@@ -54,10 +54,10 @@ struct NetState {
     size_t n_pad = 0;                    // padded parameter count
     float *p32 = nullptr, *g32 = nullptr, *m = nullptr, *v = nullptr;
     bf16_t *pb = nullptr;                // bf16 copy of p32 (weights read from here)
-    bf16_t *wt = nullptr;                // transposed weights of one layer
-    size_t wt_cap = 0;
-    float *part = nullptr, *bpart = nullptr;  // weight-gradient partial sums
-    size_t part_cap = 0, bpart_cap = 0;
+    bf16_t *wt = nullptr;                // transposed weights of every layer
+    int n_wt = 0;                        // ... their elements
+    float *part = nullptr;               // weight-gradient partial sums of every layer (made by the first backward pass)
+    LayerTable tab{};
     float *loss_part = nullptr, *loss_dev = nullptr;
     size_t loss_cap = 0;
     int step = 0;
@@ -65,7 +65,7 @@ struct NetState {
     size_t cap_px = 0;
     std::vector<void *> bufs;
     float *qref;                         // depth base of the kept forward pass
-    bf16_t *x, *e0a, *e0, *p0, *e1a, *e1, *p1, *e2a, *e2, *p2, *e3a, *e3, *c2, *d2, *c1, *d1, *c0, *d0;
+    bf16_t *x, *e0a, *e0, *p0, *e1a, *e1, *p1, *e2a, *e2, *p2, *e3a, *e3, *d2, *d1, *d0;
     float *z;
     bf16_t *dz, *g_d0, *dc0, *g_d1, *dc1, *g_d2, *dc2, *g_e3, *g_e3a, *dp2, *g_e2, *g_e2a, *dp1, *g_e1, *g_e1a, *dp0,
         *g_e0, *g_e0a;
@@ -77,7 +77,7 @@ void free_net(amh_ctx *c) {
     NetState *N = c->net;
     if (!N) return;
     for (void *p : {(void *)N->p32, (void *)N->g32, (void *)N->m, (void *)N->v, (void *)N->pb, (void *)N->wt,
-                    (void *)N->part, (void *)N->bpart, (void *)N->loss_part, (void *)N->loss_dev})
+                    (void *)N->part, (void *)N->loss_part, (void *)N->loss_dev})
         if (p) (void)hipFree(p);
     for (void *p : N->bufs)
         if (p) (void)hipFree(p);
@@ -124,13 +124,10 @@ amh_status ensure_acts(amh_ctx *c, size_t P0) {
     N->p2 = get(P3, 48);
     N->e3a = get(P3, 64);
     N->e3 = get(P3, 64);
-    N->c2 = get(P2, 112);
     N->d2 = get(P2, 48);
-    N->c1 = get(P1, 80);
     N->d1 = get(P1, 32);
-    N->c0 = get(P0, 48);
     N->d0 = get(P0, 16);
-    N->z = reinterpret_cast<float *>(get(P0, 32));  // 16 floats per cell
+    N->z = reinterpret_cast<float *>(get(P0, 2 * kHeadPitch));
     N->dz = get(P0, 16);
     N->g_d0 = get(P0, 16);
     N->dc0 = get(P0, 48);
@@ -164,7 +161,9 @@ amh_status create_net(amh_ctx *c) {
     if (!N) return fail(c, AMH_E_OOM, "host allocation failed");
     c->net = N;
     size_t off = 0;
-    size_t wt_max = 0;
+    int t_off = 0;
+    static_assert(kLayers <= kMaxLayers, "layer table");
+    N->tab.n = kLayers;
     for (int i = 0; i < kLayers; ++i) {
         Layer &l = N->L[i];
         l.cin = kSpec[i].cin;
@@ -176,7 +175,17 @@ amh_status create_net(amh_ctx *c) {
         off += (size_t)l.cout_pad * l.kpad;
         l.b_off = off;
         off += (size_t)round_up(l.cout_pad, 64);
-        wt_max = std::max(wt_max, (size_t)l.cin * round_up(l.ks * l.ks * l.cout_pad, 32));
+        LayerDims &d = N->tab.l[i];
+        d.cin = l.cin;
+        d.cout_pad = l.cout_pad;
+        d.kpad = l.kpad;
+        d.kpad_t = round_up(l.ks * l.ks * l.cout_pad, 32);
+        d.taps = l.ks * l.ks;
+        d.w_off = (int)l.w_off;
+        d.b_off = (int)l.b_off;
+        d.t_off = t_off;
+        d.splits = 0;
+        t_off += l.cin * d.kpad_t;
     }
     N->n_pad = off;
     amh_status st = AMH_OK;
@@ -185,7 +194,7 @@ amh_status create_net(amh_ctx *c) {
     if (st == AMH_OK) st = dalloc(c, (void **)&N->m, off * 4);
     if (st == AMH_OK) st = dalloc(c, (void **)&N->v, off * 4);
     if (st == AMH_OK) st = dalloc(c, (void **)&N->pb, off * 2);
-    if (st == AMH_OK) st = dalloc(c, (void **)&N->wt, wt_max * 2);
+    if (st == AMH_OK) st = dalloc(c, (void **)&N->wt, (size_t)t_off * 2);
     if (st == AMH_OK) st = dalloc(c, (void **)&N->loss_dev, 64);
     if (st == AMH_OK && hipMemsetAsync(N->g32, 0, off * 4, c->stream) != hipSuccess)
         st = fail(c, AMH_E_HIP, "hipMemsetAsync of the gradient buffer failed");
@@ -193,7 +202,7 @@ amh_status create_net(amh_ctx *c) {
         free_net(c);  // no half-built network stays on the context
         return st;
     }
-    N->wt_cap = wt_max;
+    N->n_wt = t_off;
     return AMH_OK;
 }
 
@@ -251,94 +260,64 @@ struct HostNormal {
     }
 };
 
-ConvArgs conv_args(const Layer &l, const bf16_t *x, const bf16_t *w, const float *b, void *y, int n, int h, int wd,
-                   int relu, int out_f32) {
-    ConvArgs a;
+Conv3Args fwd_args(const NetState *N, int li, const bf16_t *x, const bf16_t *low, bf16_t *y, int n, int h, int w) {
+    Conv3Args a;
     a.x = x;
-    a.wgt = w;
-    a.bias = b;
-    a.mask = nullptr;
+    a.low = low;
+    a.wgt = N->pb + N->L[li].w_off;
+    a.bias = N->p32 + N->L[li].b_off;
     a.y = y;
     a.n = n;
     a.h = h;
-    a.w = wd;
-    a.cin = l.cin;
-    a.cout_pad = l.cout_pad;
-    a.kpad = l.kpad;
-    a.ks = l.ks;
-    a.relu = relu;
-    a.out_f32 = out_f32;
+    a.w = w;
+    a.relu = 1;
     return a;
 }
 
-amh_status conv_fwd(amh_ctx *c, int li, const bf16_t *x, void *y, int n, int h, int w, bool head, hipStream_t s) {
-    NetState *N = c->net;
-    const Layer &l = N->L[li];
-    const ConvArgs a = conv_args(l, x, N->pb + l.w_off, N->p32 + l.b_off, y, n, h, w, head ? 0 : 1, head ? 1 : 0);
-    HIPCHK(c, launch_conv(a, s));
-    return AMH_OK;
-}
-
-// gradient of layer li with pre-activation gradient g (bf16 [P][cout_pad]) and input x:
-// weight and bias gradients into g32; if dx != NULL the input gradient, masked by (mask > 0) if given
-amh_status conv_bwd(amh_ctx *c, int li, const bf16_t *x, const bf16_t *g, bf16_t *dx, const bf16_t *mask, int n, int h,
-                    int w) {
+// partial weight and bias gradients of layer li with pre-activation gradient g (bf16 [P][cout_pad]) and input x (its
+// first c1 channels from low at half the resolution)
+amh_status wgrad(amh_ctx *c, int li, const bf16_t *x, const bf16_t *low, int c1, const bf16_t *g, int n, int h, int w) {
     NetState *N = c->net;
     const Layer &l = N->L[li];
     const int P = n * h * w;
-    // weight gradient: splits of at least 256 cells, at most 64 splits
-    int splits = std::max(1, std::min(64, (P + 255) / 256));
-    int chunk = round_up((P + splits - 1) / splits, 32);
+    // splits of at least 256 cells, at most kMaxSplits
+    int splits = std::max(1, std::min(kMaxSplits, (P + 255) / 256));
+    const int chunk = round_up((P + splits - 1) / splits, 32);
     splits = (P + chunk - 1) / chunk;
-    const size_t need = (size_t)splits * l.cout_pad * l.kpad, needb = (size_t)splits * l.cout_pad;
-    if (need > N->part_cap || needb > N->bpart_cap) {
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        if (N->part) (void)hipFree(N->part);
-        if (N->bpart) (void)hipFree(N->bpart);
-        N->part = N->bpart = nullptr;
-        N->part_cap = N->bpart_cap = 0;
-        const size_t cap = std::max(need, (size_t)64 * 48 * 1024), capb = std::max(needb, (size_t)64 * 128);
-        amh_status st;
-        if ((st = dalloc(c, (void **)&N->part, cap * 4)) != AMH_OK) return st;
-        if ((st = dalloc(c, (void **)&N->bpart, capb * 4)) != AMH_OK) return st;
-        N->part_cap = cap;
-        N->bpart_cap = capb;
-    }
+    N->tab.l[li].splits = splits;
     WgradArgs wa;
     wa.x = x;
+    wa.low = low;
     wa.g = g;
-    wa.part = N->part;
-    wa.bpart = N->bpart;
+    wa.part = N->part + (size_t)kMaxSplits * l.w_off;
+    wa.bpart = N->part + (size_t)kMaxSplits * l.b_off;
     wa.n = n;
     wa.h = h;
     wa.w = w;
     wa.cin = l.cin;
+    wa.c1 = c1;
     wa.cout_pad = l.cout_pad;
     wa.kpad = l.kpad;
     wa.ks = l.ks;
     wa.chunk = chunk;
-    HIPCHK(c, launch_wgrad(wa, N->g32 + l.w_off, N->g32 + l.b_off, splits, c->stream));
-    if (dx) {
-        // input gradient = convolution of g with the transposed, mirrored weights
-        const int kpad_t = round_up(l.ks * l.ks * l.cout_pad, 32);
-        HIPCHK(c, launch_transpose_w(N->pb + l.w_off, l.cin, l.cout_pad, l.kpad, l.ks, N->wt, kpad_t, c->stream));
-        ConvArgs a;
-        a.x = g;
-        a.wgt = N->wt;
-        a.bias = nullptr;
-        a.mask = mask;
-        a.y = dx;
-        a.n = n;
-        a.h = h;
-        a.w = w;
-        a.cin = l.cout_pad;
-        a.cout_pad = l.cin;
-        a.kpad = kpad_t;
-        a.ks = l.ks;
-        a.relu = 0;
-        a.out_f32 = 0;
-        HIPCHK(c, launch_conv(a, c->stream));
-    }
+    HIPCHK(c, launch_wgrad(wa, splits, c->stream));
+    return AMH_OK;
+}
+
+// input gradient of the 3x3 layer li: a convolution of g with the transposed, mirrored weights, masked by (mask > 0)
+// if given
+amh_status dgrad(amh_ctx *c, int li, const bf16_t *g, bf16_t *dx, const bf16_t *mask, int n, int h, int w) {
+    NetState *N = c->net;
+    const Layer &l = N->L[li];
+    Conv3Args a;
+    a.x = g;
+    a.wgt = N->wt + N->tab.l[li].t_off;
+    a.mask = mask;
+    a.y = dx;
+    a.n = n;
+    a.h = h;
+    a.w = w;
+    HIPCHK(c, launch_conv3(l.cout_pad, l.cin, a, c->stream));
     return AMH_OK;
 }
 
@@ -372,32 +351,35 @@ amh_status nn_forward_stream(amh_ctx *c, const void *feats, const float *q_ref, 
     if (!N) return fail(c, AMH_E_STATE, "no proposal network (amh_nn_init or amh_nn_load)");
     const size_t P0 = (size_t)n * h * w;
     if (P0 > N->cap_px) return fail(c, AMH_E_STATE, "network activations not reserved for %zu cells", P0);
-    amh_status st;
-    HIPCHK(c, hipMemcpyAsync(N->x, feats, P0 * kIn * sizeof(bf16_t), hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(N->qref, q_ref, P0 * sizeof(float), hipMemcpyDeviceToDevice, s));
     const int h1 = h / 2, w1 = w / 2, h2 = h / 4, w2 = w / 4, h3 = h / 8, w3 = w / 8;
-#define FWD(li, in, outb, hh, ww)                                                \
-    if ((st = conv_fwd(c, li, in, outb, n, hh, ww, false, s)) != AMH_OK) return st
-    FWD(ENC0A, N->x, N->e0a, h, w);
-    FWD(ENC0B, N->e0a, N->e0, h, w);
-    HIPCHK(c, launch_pool(N->e0, n, h1, w1, 16, N->p0, s));
-    FWD(ENC1A, N->p0, N->e1a, h1, w1);
-    FWD(ENC1B, N->e1a, N->e1, h1, w1);
-    HIPCHK(c, launch_pool(N->e1, n, h2, w2, 32, N->p1, s));
-    FWD(ENC2A, N->p1, N->e2a, h2, w2);
-    FWD(ENC2B, N->e2a, N->e2, h2, w2);
-    HIPCHK(c, launch_pool(N->e2, n, h3, w3, 48, N->p2, s));
-    FWD(ENC3A, N->p2, N->e3a, h3, w3);
-    FWD(ENC3B, N->e3a, N->e3, h3, w3);
-    HIPCHK(c, launch_upcat(N->e3, 64, N->e2, 48, n, h2, w2, N->c2, s));
-    FWD(DEC2, N->c2, N->d2, h2, w2);
-    HIPCHK(c, launch_upcat(N->d2, 48, N->e1, 32, n, h1, w1, N->c1, s));
-    FWD(DEC1, N->c1, N->d1, h1, w1);
-    HIPCHK(c, launch_upcat(N->d1, 32, N->e0, 16, n, h, w, N->c0, s));
-    FWD(DEC0, N->c0, N->d0, h, w);
-#undef FWD
-    if ((st = conv_fwd(c, HEAD, N->d0, N->z, n, h, w, true, s)) != AMH_OK) return st;
-    if (out) HIPCHK(c, launch_decode(N->z, N->qref, (int)P0, depth_head(c->p), out, s));
+    // the input is copied by the first layer, pooling is part of the layer above it, the concatenations are read where
+    // their sources lie, and the last layer applies and decodes the head
+    const auto layer = [&](int li, const bf16_t *x, const bf16_t *low, bf16_t *y, bf16_t *pool, int hh, int ww) {
+        Conv3Args a = fwd_args(N, li, x, low, y, n, hh, ww);
+        a.pool = pool;
+        if (li == ENC0A) a.xcopy = N->x;
+        if (li == DEC0) {
+            a.head_w = N->pb + N->L[HEAD].w_off;
+            a.head_b = N->p32 + N->L[HEAD].b_off;
+            a.q_ref = q_ref;
+            a.q_copy = N->qref;
+            a.z = N->z;
+            a.out = out;
+            a.dh = depth_head(c->p);
+        }
+        return launch_conv3(N->L[li].cin, N->L[li].cout_pad, a, s);
+    };
+    HIPCHK(c, layer(ENC0A, static_cast<const bf16_t *>(feats), nullptr, N->e0a, nullptr, h, w));
+    HIPCHK(c, layer(ENC0B, N->e0a, nullptr, N->e0, N->p0, h, w));
+    HIPCHK(c, layer(ENC1A, N->p0, nullptr, N->e1a, nullptr, h1, w1));
+    HIPCHK(c, layer(ENC1B, N->e1a, nullptr, N->e1, N->p1, h1, w1));
+    HIPCHK(c, layer(ENC2A, N->p1, nullptr, N->e2a, nullptr, h2, w2));
+    HIPCHK(c, layer(ENC2B, N->e2a, nullptr, N->e2, N->p2, h2, w2));
+    HIPCHK(c, layer(ENC3A, N->p2, nullptr, N->e3a, nullptr, h3, w3));
+    HIPCHK(c, layer(ENC3B, N->e3a, nullptr, N->e3, nullptr, h3, w3));
+    HIPCHK(c, layer(DEC2, N->e2, N->e3, N->d2, nullptr, h2, w2));
+    HIPCHK(c, layer(DEC1, N->e1, N->d2, N->d1, nullptr, h1, w1));
+    HIPCHK(c, layer(DEC0, N->e0, N->d1, N->d0, nullptr, h, w));
     N->n = n;
     N->h = h;
     N->w = w;
@@ -501,28 +483,48 @@ amh_status amh_nn_backward(amh_ctx *c, const float *target, float *loss) {
         if ((st = dalloc(c, (void **)&N->loss_part, (size_t)nb * 4)) != AMH_OK) return st;
         N->loss_cap = nb;
     }
+    if (!N->part && (st = dalloc(c, (void **)&N->part, (size_t)kMaxSplits * N->n_pad * sizeof(float))) != AMH_OK) {
+        N->part = nullptr;
+        return st;
+    }
     HIPCHK(c, launch_loss(N->z, N->qref, target, P0, depth_head(c->p), N->dz, N->loss_part, N->loss_dev, s));
-#define BWD(li, x, g, dx, mask, hh, ww)                                          \
-    if ((st = conv_bwd(c, li, x, g, dx, mask, n, hh, ww)) != AMH_OK) return st
-    BWD(HEAD, N->d0, N->dz, N->g_d0, N->d0, h, w);          // dL/d(d0 pre-activation)
-    BWD(DEC0, N->c0, N->g_d0, N->dc0, nullptr, h, w);        // dL/d(concat [up(d1), e0])
+    HIPCHK(c, launch_transpose_w(N->tab, N->pb, N->n_wt, N->wt, s));
+#define WGRAD(li, x, low, c1, g, hh, ww)                                      \
+    if ((st = wgrad(c, li, x, low, c1, g, n, hh, ww)) != AMH_OK) return st
+#define DGRAD(li, g, dx, mask, hh, ww)                                        \
+    if ((st = dgrad(c, li, g, dx, mask, n, hh, ww)) != AMH_OK) return st
+    WGRAD(HEAD, N->d0, nullptr, 0, N->dz, h, w);
+    HIPCHK(c, launch_head_grad(N->dz, N->wt + N->tab.l[HEAD].t_off, N->d0, P0, N->g_d0, s));  // dL/d(d0 pre-activation)
+    WGRAD(DEC0, N->e0, N->d1, 32, N->g_d0, h, w);
+    DGRAD(DEC0, N->g_d0, N->dc0, nullptr, h, w);        // dL/d(concat [up(d1), e0])
     HIPCHK(c, launch_up_grad(N->dc0, 48, N->d1, n, h1, w1, 32, N->g_d1, s));
-    BWD(DEC1, N->c1, N->g_d1, N->dc1, nullptr, h1, w1);      // [up(d2), e1]
+    WGRAD(DEC1, N->e1, N->d2, 48, N->g_d1, h1, w1);
+    DGRAD(DEC1, N->g_d1, N->dc1, nullptr, h1, w1);      // [up(d2), e1]
     HIPCHK(c, launch_up_grad(N->dc1, 80, N->d2, n, h2, w2, 48, N->g_d2, s));
-    BWD(DEC2, N->c2, N->g_d2, N->dc2, nullptr, h2, w2);      // [up(e3), e2]
+    WGRAD(DEC2, N->e2, N->e3, 64, N->g_d2, h2, w2);
+    DGRAD(DEC2, N->g_d2, N->dc2, nullptr, h2, w2);      // [up(e3), e2]
     HIPCHK(c, launch_up_grad(N->dc2, 112, N->e3, n, h3, w3, 64, N->g_e3, s));
-    BWD(ENC3B, N->e3a, N->g_e3, N->g_e3a, N->e3a, h3, w3);
-    BWD(ENC3A, N->p2, N->g_e3a, N->dp2, nullptr, h3, w3);
+    WGRAD(ENC3B, N->e3a, nullptr, 0, N->g_e3, h3, w3);
+    DGRAD(ENC3B, N->g_e3, N->g_e3a, N->e3a, h3, w3);
+    WGRAD(ENC3A, N->p2, nullptr, 0, N->g_e3a, h3, w3);
+    DGRAD(ENC3A, N->g_e3a, N->dp2, nullptr, h3, w3);
     HIPCHK(c, launch_enc_grad(N->dp2, N->dc2, 112, 64, N->e2, n, h2, w2, 48, N->g_e2, s));
-    BWD(ENC2B, N->e2a, N->g_e2, N->g_e2a, N->e2a, h2, w2);
-    BWD(ENC2A, N->p1, N->g_e2a, N->dp1, nullptr, h2, w2);
+    WGRAD(ENC2B, N->e2a, nullptr, 0, N->g_e2, h2, w2);
+    DGRAD(ENC2B, N->g_e2, N->g_e2a, N->e2a, h2, w2);
+    WGRAD(ENC2A, N->p1, nullptr, 0, N->g_e2a, h2, w2);
+    DGRAD(ENC2A, N->g_e2a, N->dp1, nullptr, h2, w2);
     HIPCHK(c, launch_enc_grad(N->dp1, N->dc1, 80, 48, N->e1, n, h1, w1, 32, N->g_e1, s));
-    BWD(ENC1B, N->e1a, N->g_e1, N->g_e1a, N->e1a, h1, w1);
-    BWD(ENC1A, N->p0, N->g_e1a, N->dp0, nullptr, h1, w1);
+    WGRAD(ENC1B, N->e1a, nullptr, 0, N->g_e1, h1, w1);
+    DGRAD(ENC1B, N->g_e1, N->g_e1a, N->e1a, h1, w1);
+    WGRAD(ENC1A, N->p0, nullptr, 0, N->g_e1a, h1, w1);
+    DGRAD(ENC1A, N->g_e1a, N->dp0, nullptr, h1, w1);
     HIPCHK(c, launch_enc_grad(N->dp0, N->dc0, 48, 32, N->e0, n, h, w, 16, N->g_e0, s));
-    BWD(ENC0B, N->e0a, N->g_e0, N->g_e0a, N->e0a, h, w);
-    BWD(ENC0A, N->x, N->g_e0a, nullptr, nullptr, h, w);
-#undef BWD
+    WGRAD(ENC0B, N->e0a, nullptr, 0, N->g_e0, h, w);
+    DGRAD(ENC0B, N->g_e0, N->g_e0a, N->e0a, h, w);
+    WGRAD(ENC0A, N->x, nullptr, 0, N->g_e0a, h, w);
+#undef WGRAD
+#undef DGRAD
+    HIPCHK(c, launch_wgrad_reduce(N->tab, N->part, (int)N->n_pad, N->g32, s));
     N->have_grad = true;
     if (loss) {
         HIPCHK(c, hipMemcpyAsync(loss, N->loss_dev, 4, hipMemcpyDeviceToHost, s));
