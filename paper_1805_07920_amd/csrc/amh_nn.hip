@@ -66,7 +66,7 @@ __device__ __forceinline__ float pair_swap(float v) {
 // MFMAs (8.3 GFLOP, 60 MB through the caches); the order of the sums over K is
 // fixed (steps of 32 from tap 0), whatever the tile.  Forward at 320 x 480
 // cells: 21 launches of kernels without LDS, scattered 2-byte stores and a
-// division per step took 226 us; NETFWD us with 11.
+// division per step took 221 us; 85 us with 11.
 // ---------------------------------------------------------------------------
 constexpr int kTileX = 16;
 
@@ -74,7 +74,7 @@ constexpr int kTileX = 16;
 // of the 4 waves split the output channels, the others the rows, NG rows each; POOL: also the 2 x 2 means; HEAD: also
 // the 1x1 head and its decoding
 template <int CIN, int COUT, int C1, int WN, int NG, bool POOL, bool HEAD>
-__global__ __launch_bounds__(256) void conv3_kernel(Conv3Args a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HEAD ? 5 : 1))) void conv3_kernel(Conv3Args a) {
     constexpr int NT = COUT / 16, NTW = (NT + WN - 1) / WN, TH = 4 / WN * NG;
     constexpr int SW = kTileX + 2, SH = TH + 2, PXS = CIN * 2 + 16, C8 = CIN / 8;
     constexpr int K = 9 * CIN, STEPS = (K + 31) / 32, KPAD = STEPS * 32;
@@ -102,6 +102,18 @@ __global__ __launch_bounds__(256) void conv3_kernel(Conv3Args a) {
             v[l] = *reinterpret_cast<const u32x4 *>(src);
         }
     }
+    // the weights of the first steps, loaded while the tile arrives
+    constexpr int PREW = HEAD ? 8 : 16 / NTW, PRE = PREW < STEPS ? PREW : STEPS;
+    const int px = lane & 15, grp = lane >> 4;
+    const int wn = wave % WN, row0 = wave / WN * NG;
+    const bf16_t *wb = a.wgt + (size_t)(wn * NTW * 16 + px) * KPAD + grp * 8;
+    u32x4 wpre[PRE][NTW];
+#pragma unroll
+    for (int s = 0; s < PRE; ++s)
+#pragma unroll
+        for (int t = 0; t < NTW; ++t)
+            if (NT % WN == 0 || wn * NTW + t < NT)
+                wpre[s][t] = *reinterpret_cast<const u32x4 *>(wb + (size_t)t * 16 * KPAD + 32 * s);
 #pragma unroll
     for (int l = 0; l < LOADS; ++l) {
         const int i = tid + l * 256, px = i / C8, c = (i - px * C8) * 8;
@@ -114,15 +126,25 @@ __global__ __launch_bounds__(256) void conv3_kernel(Conv3Args a) {
     }
     __syncthreads();
 
-    const int px = lane & 15, grp = lane >> 4;
-    const int wn = wave % WN, row0 = wave / WN * NG;
     f32x4 acc[NTW][NG];
 #pragma unroll
     for (int t = 0; t < NTW; ++t)
 #pragma unroll
         for (int g = 0; g < NG; ++g) acc[t][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // what the end of the kernel reads, loaded here
+    float qr[NG];
+    u32x4 hw = {0u, 0u, 0u, 0u};
+    f32x4 hb = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (HEAD) {
+        hw = *reinterpret_cast<const u32x4 *>(a.head_w + px * 32 + grp * 8);
+        hb = *reinterpret_cast<const f32x4 *>(a.head_b + 4 * grp);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int y = y0 + row0 + g, x = x0 + px;
+            qr[g] = y < h && x < w ? a.q_ref[(size_t)(b * h + y) * w + x] : 1.f;
+        }
+    }
     const unsigned char *lb = tile + (row0 * SW + px) * PXS + (grp & 1) * 16;
-    const bf16_t *wb = a.wgt + (size_t)(wn * NTW * 16 + px) * KPAD + grp * 8;
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
         // lane groups 0, 1 hold channels k .. k + 15 of the step, groups 2, 3 the next 16: each within one tap
@@ -140,7 +162,8 @@ __global__ __launch_bounds__(256) void conv3_kernel(Conv3Args a) {
 #pragma unroll
         for (int t = 0; t < NTW; ++t) {
             if (NT % WN != 0 && wn * NTW + t >= NT) continue;
-            const u32x4 av = *reinterpret_cast<const u32x4 *>(wb + (size_t)t * 16 * KPAD + kA);
+            const u32x4 av =
+                s < PRE ? wpre[s < PRE ? s : 0][t] : *reinterpret_cast<const u32x4 *>(wb + (size_t)t * 16 * KPAD + kA);
 #pragma unroll
             for (int g = 0; g < NG; ++g)
                 acc[t][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
@@ -203,8 +226,6 @@ __global__ __launch_bounds__(256) void conv3_kernel(Conv3Args a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const u32x4 hw = *reinterpret_cast<const u32x4 *>(a.head_w + px * 32 + grp * 8);
-        const f32x4 hb = *reinterpret_cast<const f32x4 *>(a.head_b + 4 * grp);
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             u32x4 dv = {0u, 0u, 0u, 0u};
@@ -220,14 +241,13 @@ __global__ __launch_bounds__(256) void conv3_kernel(Conv3Args a) {
                 const size_t p = (size_t)(b * h + y) * w + x;
                 *reinterpret_cast<f32x4 *>(a.z + p * kHeadPitch + 4 * grp) = z;
                 if (grp == 0) {
-                    const float qr = a.q_ref[p];
-                    a.q_copy[p] = qr;
+                    a.q_copy[p] = qr[g];
                     if (a.out) {
                         const float nx = z[1], ny = z[2], nz = z[3];
                         const float inv = 1.f / __builtin_sqrtf(nx * nx + ny * ny + nz * nz);
                         float dq;
                         float *o = a.out + p * 5;
-                        o[0] = 1.f / head_q(z[0], qr, a.dh, dq);
+                        o[0] = 1.f / head_q(z[0], qr[g], a.dh, dq);
                         o[1] = nx * inv;
                         o[2] = ny * inv;
                         o[3] = nz * inv;
@@ -274,15 +294,13 @@ __global__ __launch_bounds__(256) void head_grad_kernel(const bf16_t *g, const b
 // image borders and the split's end are only a choice of row -- a row of
 // zeros where the tap falls outside.  A workgroup takes one split, one group
 // of 16 input channels and one row of taps, a wave one tap and every output
-// channel; blocks of kWgBlock pixels are staged while the next one's loads are
-// in flight.  Sums run over 32 pixels per MFMA in pixel order, as before.
+// channel; blocks of B pixels are staged while the next one's loads are in
+// flight (few workgroups: large blocks, so that few loads are waited for).  Sums run over 32 pixels per MFMA in pixel order, as before.
 //
 // Bound: LDS reads and the staging (a tap reads its 32 pixels x 16 channels
 // once per MFMA).  16 x 120 x 160 cells, all layers: 12 launches with 16
-// two-byte loads per lane and MFMA took 1490 us; WGRAD us.
+// two-byte loads per lane and MFMA took 1490 us; 195 us.
 // ---------------------------------------------------------------------------
-constexpr int kWgBlock = 256;
-
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -294,10 +312,11 @@ __device__ __forceinline__ bf16x8 join8(s16x4 lo, s16x4 hi) {
     return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// NCO: output channels / 16; TAPS: 3 (3x3, blockIdx.z the row of taps) or 1 (1x1)
-template <int NCO, int TAPS>
-__global__ __launch_bounds__(64 * TAPS) void wgrad_kernel(WgradArgs a) {
-    constexpr int COUT = NCO * 16, NTHR = 64 * TAPS, B = kWgBlock;
+// NCO: output channels / 16; TAPS: 3 (3x3, blockIdx.z the row of taps) or 1 (1x1); B: pixels of a block.  The fourth
+// wave (and with one tap the second and third) stages, and sums the bias gradient.
+template <int NCO, int TAPS, int B>
+__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
+    constexpr int COUT = NCO * 16, NTHR = 256;
     constexpr int XU = (B + 2) * 2, GU = B * COUT / 8;                       // 16-byte units of a block
     constexpr int XL = (XU + NTHR - 1) / NTHR, GL = (GU + NTHR - 1) / NTHR;  // ... per thread
     __shared__ __align__(16) bf16_t xs[(B + 2 + 1) * 16];  // pixels lin0 .. lin0 + B + 1, and a row of zeros
@@ -348,7 +367,7 @@ __global__ __launch_bounds__(64 * TAPS) void wgrad_kernel(WgradArgs a) {
         acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         bsum[t] = 0.f;
     }
-    const bool do_bias = cg == 0 && (TAPS == 1 || blockIdx.z == 0) && wave == 0;
+    const bool do_bias = cg == 0 && blockIdx.z == 0 && wave == 3;
     // what a pixel must satisfy for this tap: inside the split, and the neighbour inside the image
     const int need = 16 | (dx < 0 ? 1 : dx > 0 ? 2 : 0) | (dy < 0 ? 4 : dy > 0 ? 8 : 0);
     const int l16 = lane & 15, grp = lane >> 4, sub = l16 >> 2, c4 = 4 * (l16 & 3);
@@ -372,27 +391,58 @@ __global__ __launch_bounds__(64 * TAPS) void wgrad_kernel(WgradArgs a) {
 #pragma unroll
             for (int l = 0; l < GL; ++l) gv[l] = load_g(pb + B, tid + l * NTHR);
         }
-        const int steps = min(B, end - pb + 31) / 32;
-#pragma unroll 2
-        for (int st = 0; st < steps; ++st) {
-            const int i0 = st * 32 + grp * 8 + sub, i1 = i0 + 4;  // the lane's pixel rows of the block
-            const int r0 = (flags[i0] & need) == need ? i0 + 1 + dx : B + 2;
-            const int r1 = (flags[i1] & need) == need ? i1 + 1 + dx : B + 2;
-            const bf16x8 bx = join8(lds_read_tr(xs + r0 * 16 + c4), lds_read_tr(xs + r1 * 16 + c4));
+        // U steps together, so that their reads are in flight at once; those past the end meet zeros
+        constexpr int U = NCO <= 2 ? 4 : 2;
+        const int steps = (min(B, end - pb) + 31) / 32;
+        if (wave < TAPS) {
+            for (int st = 0; st < steps; st += U) {
+                int r0[U], r1[U];
 #pragma unroll
-            for (int t = 0; t < NCO; ++t) {
-                const s16x4 g0 = lds_read_tr(gs + i0 * COUT + t * 16 + c4);
-                const s16x4 g1 = lds_read_tr(gs + i1 * COUT + t * 16 + c4);
-                if (do_bias) {
+                for (int u = 0; u < U; ++u) {
+                    const int i0 = (st + u) * 32 + grp * 8 + sub;  // the lane's pixel rows: i0, i0 + 4
+                    r0[u] = (flags[i0] & need) == need ? i0 + 1 + dx : B + 2;
+                    r1[u] = (flags[i0 + 4] & need) == need ? i0 + 5 + dx : B + 2;
+                }
+                bf16x8 bx[U], ga[U][NCO];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i0 = (st + u) * 32 + grp * 8 + sub;
+                    bx[u] = join8(lds_read_tr(xs + r0[u] * 16 + c4), lds_read_tr(xs + r1[u] * 16 + c4));
+#pragma unroll
+                    for (int t = 0; t < NCO; ++t)
+                        ga[u][t] = join8(lds_read_tr(gs + i0 * COUT + t * 16 + c4),
+                                         lds_read_tr(gs + (i0 + 4) * COUT + t * 16 + c4));
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int t = 0; t < NCO; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga[u][t], bx[u], acc[t], 0, 0, 0);
+            }
+        } else if (do_bias) {
+            for (int st = 0; st < steps; ++st) {
+                const int i0 = st * 32 + grp * 8 + sub;
+#pragma unroll
+                for (int t = 0; t < NCO; ++t) {
+                    const s16x4 g0 = lds_read_tr(gs + i0 * COUT + t * 16 + c4);
+                    const s16x4 g1 = lds_read_tr(gs + (i0 + 4) * COUT + t * 16 + c4);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) bsum[t] += bf2f((bf16_t)g0[e]);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) bsum[t] += bf2f((bf16_t)g1[e]);
                 }
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(join8(g0, g1), bx, acc[t], 0, 0, 0);
             }
         }
     }
+    if (do_bias) {
+#pragma unroll
+        for (int t = 0; t < NCO; ++t) {
+            bsum[t] += __shfl_xor(bsum[t], 16, 64);
+            bsum[t] += __shfl_xor(bsum[t], 32, 64);
+            if (grp == 0) a.bpart[(size_t)s * COUT + t * 16 + l16] = bsum[t];
+        }
+    }
+    if (wave >= TAPS) return;
     // acc[t][i] = dW[16 t + 4 grp + i][tap cin + 16 cg + l16]
     const int tap = TAPS == 3 ? (dy + 1) * 3 + dx + 1 : 0;
     float *dst = a.part + (size_t)s * COUT * a.kpad + tap * a.cin + c0 + l16;
@@ -400,11 +450,6 @@ __global__ __launch_bounds__(64 * TAPS) void wgrad_kernel(WgradArgs a) {
     for (int t = 0; t < NCO; ++t) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) dst[(size_t)(t * 16 + 4 * grp + i) * a.kpad] = acc[t][i];
-        if (do_bias) {
-            bsum[t] += __shfl_xor(bsum[t], 16, 64);
-            bsum[t] += __shfl_xor(bsum[t], 32, 64);
-            if (grp == 0) a.bpart[(size_t)s * COUT + t * 16 + l16] = bsum[t];
-        }
     }
 }
 
@@ -659,14 +704,14 @@ static hipError_t run_conv3(Conv3Args a, hipStream_t s) {
 hipError_t launch_conv3(int cin, int cout, const Conv3Args &a, hipStream_t s) {
     if (a.head_w) return cin == 48 && cout == 16 && a.low ? run_conv3<48, 16, 32, 1, 2, false, true>(a, s) : hipErrorInvalidValue;
     if (a.low) {
-        if (cin == 112 && cout == 48) return run_conv3<112, 48, 64, 1, 1>(a, s);
-        if (cin == 80 && cout == 32) return run_conv3<80, 32, 48, 1, 2>(a, s);
+        if (cin == 112 && cout == 48) return run_conv3<112, 48, 64, 4, 2>(a, s);
+        if (cin == 80 && cout == 32) return run_conv3<80, 32, 48, 2, 2>(a, s);
         return hipErrorInvalidValue;
     }
     if (a.pool) {
         if (cin == 16 && cout == 16) return run_conv3<16, 16, 0, 1, 2, true>(a, s);
         if (cin == 32 && cout == 32) return run_conv3<32, 32, 0, 1, 2, true>(a, s);
-        if (cin == 48 && cout == 48) return run_conv3<48, 48, 0, 1, 2, true>(a, s);
+        if (cin == 48 && cout == 48) return run_conv3<48, 48, 0, 4, 2, true>(a, s);
         return hipErrorInvalidValue;
     }
     if (cin == 16) {
@@ -699,14 +744,14 @@ hipError_t launch_wgrad(const WgradArgs &a, int splits, hipStream_t s) {
     const dim3 grid(splits, a.cin / 16, a.ks);
     if (a.ks == 1) {
         if (a.cout_pad != 16) return hipErrorInvalidValue;
-        NN_LAUNCH((wgrad_kernel<1, 1>), grid, dim3(64), 0, s, a);
+        NN_LAUNCH((wgrad_kernel<1, 1, 1024>), grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
-    switch (a.cout_pad / 16) {
-        case 1: NN_LAUNCH((wgrad_kernel<1, 3>), grid, dim3(192), 0, s, a); break;
-        case 2: NN_LAUNCH((wgrad_kernel<2, 3>), grid, dim3(192), 0, s, a); break;
-        case 3: NN_LAUNCH((wgrad_kernel<3, 3>), grid, dim3(192), 0, s, a); break;
-        case 4: NN_LAUNCH((wgrad_kernel<4, 3>), grid, dim3(192), 0, s, a); break;
+    switch (a.cout_pad / 16) {  // blocks as large as 64 KB of LDS allow
+        case 1: NN_LAUNCH((wgrad_kernel<1, 3, 512>), grid, dim3(256), 0, s, a); break;
+        case 2: NN_LAUNCH((wgrad_kernel<2, 3, 512>), grid, dim3(256), 0, s, a); break;
+        case 3: NN_LAUNCH((wgrad_kernel<3, 3, 256>), grid, dim3(256), 0, s, a); break;
+        case 4: NN_LAUNCH((wgrad_kernel<4, 3, 256>), grid, dim3(256), 0, s, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
