@@ -39,6 +39,8 @@ struct JobResult {
 
 using namespace amh;  // private header: the library's own translation units only
 
+constexpr size_t kStageHalf = (size_t)1024 << 10;
+
 struct amh_ctx {
     amh_params p;
     int alloc_count = 0;      // device allocations made by this context
@@ -104,6 +106,10 @@ struct amh_ctx {
     std::vector<hipEvent_t> fuse_ev;  // timing = 1: a start/stop pair per fusion kernel launch
     float fuse_ms = 0.f;               // their total device time in the last amh_fuse
     int fuse_n = 0;
+    // fixed hypotheses in host memory: pinned memory of 2 kStageHalf bytes, made with the context (NULL: none to be
+    // had, such calls copy to and from pageable memory), and an event for each half
+    unsigned char *stage = nullptr;
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};
 };
 
 namespace amh {
