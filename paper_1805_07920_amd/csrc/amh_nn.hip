@@ -298,8 +298,12 @@ __global__ __launch_bounds__(256) void head_grad_kernel(const bf16_t *g, const b
 // flight (few workgroups: large blocks, so that few loads are waited for).  Sums run over 32 pixels per MFMA in pixel order, as before.
 //
 // Bound: LDS reads and the staging (a tap reads its 32 pixels x 16 channels
-// once per MFMA).  16 x 120 x 160 cells, all layers: 12 launches with 16
-// two-byte loads per lane and MFMA took 1490 us; 195 us.
+// once per MFMA), and in a split the chain of products.  16 x 120 x 160 cells,
+// all layers: 12 launches with 16 two-byte loads per lane and MFMA took 1490
+// us; staged, 195 us; a block's loads all in flight and their places advanced
+// by carries (a division per unit and pixel before), 174 us.  (Not better:
+// two blocks' loads in flight, the next round's operands read ahead -- the
+// registers cost the second workgroup of a CU.)
 // ---------------------------------------------------------------------------
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -311,6 +315,26 @@ __device__ __forceinline__ bf16x8 join8(s16x4 lo, s16x4 hi) {
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
+
+// A pixel's place in the batch, advanced by a fixed step: carries instead of the divisions of its linear index.
+struct Place {
+    int x, y, b;
+    __device__ __forceinline__ static Place of(int lin, int w, int h) {
+        const int t = lin / w;
+        return {lin - t * w, t % h, t / h};
+    }
+    __device__ __forceinline__ Place plus(const Place &d, int w, int h) const {
+        Place r;
+        r.x = x + d.x;
+        const int cx = r.x >= w;
+        r.x -= cx ? w : 0;
+        r.y = y + d.y + cx;
+        const int cy = r.y >= h;
+        r.y -= cy ? h : 0;
+        r.b = b + d.b + cy;
+        return r;
+    }
+};
 
 // NCO: output channels / 16; TAPS: 3 (3x3, blockIdx.z the row of taps) or 1 (1x1); B: pixels of a block.  The fourth
 // wave (and with one tap the second and third) stages, and sums the bias gradient.
@@ -335,30 +359,37 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
     const int cs = from_low ? a.c1 : a.cin - a.c1;  // channels of that source
     if (tid < 16) xs[(B + 2) * 16 + tid] = 0;
 
-    const auto load_x = [&](int pb, int u) {  // unit u: half a pixel's 16 channels
-        u32x4 v = {0u, 0u, 0u, 0u};
-        const int lin = pb + dy * w - 1 + (u >> 1);
-        if (u < XU && lin >= 0 && lin < P) {
-            size_t q = lin;
-            if (from_low) {
-                const int x = lin % w, t = lin / w, y = t % h, b = t / h;
-                q = (size_t)(b * (h / 2) + y / 2) * (w / 2) + x / 2;
-            }
-            v = *reinterpret_cast<const u32x4 *>(src + q * cs + (u & 1) * 8);
-        }
-        return v;
-    };
-    const auto load_g = [&](int pb, int u) {
-        u32x4 v = {0u, 0u, 0u, 0u};
-        const int q = pb + u / (COUT / 8);
-        if (u < GU && q < end) v = *reinterpret_cast<const u32x4 *>(a.g + (size_t)q * COUT + (u % (COUT / 8)) * 8);
-        return v;
-    };
+    // a block's places: of the thread's flags (pixels pb + tid, + NTHR, ...) and, where the source is the half-resolution
+    // one, of its units (two to a pixel)
+    const Place d_blk = Place::of(B, w, h), d_thr = Place::of(NTHR, w, h), d_unit = Place::of(NTHR / 2, w, h);
+    Place fp = Place::of(beg + tid, w, h);
+    // the units start up to w + 1 pixels before the split: two images are added and taken off again
+    Place up = Place::of(beg + dy * w - 1 + (tid >> 1) + 2 * w * h, w, h);
+    up.b -= 2;
+    // no load is under a condition, so that all of a block are in flight: places outside the batch and pixels past the
+    // split's end read its last ones (the flags send every tap of theirs to the row of zeros; g is cleared on its way to LDS)
     u32x4 xv[XL], gv[GL];
+    const auto load = [&](int pb) {
+        Place at = up;
 #pragma unroll
-    for (int l = 0; l < XL; ++l) xv[l] = load_x(beg, tid + l * NTHR);
+        for (int l = 0; l < XL; ++l) {  // half a pixel's 16 channels each
+            const int u = tid + l * NTHR;
+            const int lin = pb + dy * w - 1 + (u >> 1);
+            int q = min(max(lin, 0), P - 1);
+            if (from_low) {
+                q = min(max((at.b * (h / 2) + at.y / 2) * (w / 2) + at.x / 2, 0), P / 4 - 1);
+                at = at.plus(d_unit, w, h);
+            }
+            xv[l] = *reinterpret_cast<const u32x4 *>(src + (size_t)q * cs + (u & 1) * 8);
+        }
+        if (from_low) up = up.plus(d_blk, w, h);
 #pragma unroll
-    for (int l = 0; l < GL; ++l) gv[l] = load_g(beg, tid + l * NTHR);
+        for (int l = 0; l < GL; ++l) {
+            const int u = tid + l * NTHR, q = min(pb + u / (COUT / 8), end - 1);
+            gv[l] = *reinterpret_cast<const u32x4 *>(a.g + (size_t)q * COUT + (u % (COUT / 8)) * 8);
+        }
+    };
+    load(beg);
 
     f32x4 acc[NCO];
     float bsum[NCO];
@@ -378,19 +409,20 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
             if (tid + l * NTHR < XU) *reinterpret_cast<u32x4 *>(xs + (tid + l * NTHR) * 8) = xv[l];
 #pragma unroll
         for (int l = 0; l < GL; ++l)
-            if (tid + l * NTHR < GU) *reinterpret_cast<u32x4 *>(gs + (tid + l * NTHR) * 8) = gv[l];
-        for (int i = tid; i < B; i += NTHR) {
-            const int q = pb + i, x = q % w, y = q / w % h;
-            flags[i] = (unsigned char)((x > 0 ? 1 : 0) | (x + 1 < w ? 2 : 0) | (y > 0 ? 4 : 0) | (y + 1 < h ? 8 : 0) |
-                                       (q < end ? 16 : 0));
+            if (tid + l * NTHR < GU)
+                *reinterpret_cast<u32x4 *>(gs + (tid + l * NTHR) * 8) =
+                    pb + (tid + l * NTHR) / (COUT / 8) < end ? gv[l] : u32x4{0u, 0u, 0u, 0u};
+        Place at = fp;
+#pragma unroll
+        for (int l = 0; l < B / NTHR; ++l) {
+            const int i = tid + l * NTHR;
+            flags[i] = (unsigned char)((at.x > 0 ? 1 : 0) | (at.x + 1 < w ? 2 : 0) | (at.y > 0 ? 4 : 0) |
+                                       (at.y + 1 < h ? 8 : 0) | (pb + i < end ? 16 : 0));
+            if (l + 1 < B / NTHR) at = at.plus(d_thr, w, h);
         }
+        fp = fp.plus(d_blk, w, h);
         __syncthreads();
-        if (pb + B < end) {
-#pragma unroll
-            for (int l = 0; l < XL; ++l) xv[l] = load_x(pb + B, tid + l * NTHR);
-#pragma unroll
-            for (int l = 0; l < GL; ++l) gv[l] = load_g(pb + B, tid + l * NTHR);
-        }
+        if (pb + B < end) load(pb + B);
         // U steps together, so that their reads are in flight at once; those past the end meet zeros
         constexpr int U = NCO <= 2 ? 4 : 2;
         const int steps = (min(B, end - pb) + 31) / 32;
@@ -420,17 +452,26 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
                         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga[u][t], bx[u], acc[t], 0, 0, 0);
             }
         } else if (do_bias) {
-            for (int st = 0; st < steps; ++st) {
-                const int i0 = st * 32 + grp * 8 + sub;
+            // a lane's sum is a chain of additions in pixel order: the reads of V steps in flight (one step at a time it
+            // added 10 us to the 9 us that staging 4800 pixels x 16 channels takes alone)
+            constexpr int V = 4;
+            for (int st = 0; st < steps; st += V) {
+                s16x4 g[V][2][NCO];
 #pragma unroll
-                for (int t = 0; t < NCO; ++t) {
-                    const s16x4 g0 = lds_read_tr(gs + i0 * COUT + t * 16 + c4);
-                    const s16x4 g1 = lds_read_tr(gs + (i0 + 4) * COUT + t * 16 + c4);
+                for (int u = 0; u < V; ++u) {
+                    const int i0 = (st + u) * 32 + grp * 8 + sub;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) bsum[t] += bf2f((bf16_t)g0[e]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) bsum[t] += bf2f((bf16_t)g1[e]);
+                    for (int t = 0; t < NCO; ++t) {
+                        g[u][0][t] = lds_read_tr(gs + i0 * COUT + t * 16 + c4);
+                        g[u][1][t] = lds_read_tr(gs + (i0 + 4) * COUT + t * 16 + c4);
+                    }
                 }
+#pragma unroll
+                for (int u = 0; u < V; ++u)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+#pragma unroll
+                        for (int t = 0; t < NCO; ++t) bsum[t] += bf2f((bf16_t)g[u][e >> 2][t][e & 3]);
             }
         }
     }
