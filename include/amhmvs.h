@@ -249,7 +249,8 @@ amh_status amh_get_job_times(amh_ctx *ctx, int n, float *job_ms);
 
 /* Autotuner: times the batch under each launch configuration -- tile order (XCD
  * bands or hardware order) x job order (as given or largest first) x tile shape
- * of the half-pass (4 or 2 image rows per workgroup) x the batch's half-passes
+ * of the half-pass (4 image rows per workgroup -- 3 from 13 sources on, 1 for
+ * small references run by themselves -- or 2) x the batch's half-passes
  * launched one per phase or all in one persistent launch; configuration =
  * tile_order + 2 * job_order + 4 * (two-row tiles) + 8 * persistent -- keeps the
  * fastest for the following launches of this context (single images included)

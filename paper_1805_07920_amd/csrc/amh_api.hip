@@ -103,7 +103,6 @@ static void make_stage(amh_ctx *c) {
     void *p = nullptr;
     if (hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocDefault) == hipSuccess) {
         c->stage = static_cast<unsigned char *>(p);
-        std::memset(c->stage, 0, 2 * kStageHalf);  // its pages, before the first call
         for (auto &e : c->stage_ev)
             if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
                 e = nullptr;
@@ -758,7 +757,6 @@ amh_status amh_create(amh_ctx **out, const amh_params *p, void *hip_stream) {
     // lookup is kept and reported by amh_run_checkerboard_static, the rest of the library does not need it
     unsigned char *sp = nullptr;
     (void)static_scratch(c->device, &sp);
-    make_stage(c);
     *out = c;
     return AMH_OK;
 }
@@ -1095,8 +1093,9 @@ amh_status amh_set_state(amh_ctx *c, const float *planes, const float *cost, con
 }
 
 // Fixed hypotheses in host memory: the kernel reads the queries from pinned memory and writes the costs there, in equal
-// parts that fit a half of it, the host copying one part in or out while the GPU scores the other.  (Three copies from
-// and to pageable memory took about 100 us of the call's 151 at 20 000 queries x 10 sources; 119; 100 queries: 36 -> 22 us, 400 000: 2502 -> 1621 us.)
+// parts that fit a half of it, the host copying one part in or out while the GPU scores the other.  20 000 queries x 10
+// sources: three copies from and to pageable memory, which the first call still makes, took about 100 us of the call's
+// 151; now 119 in all (100 queries: 36 -> 22 us, 400 000: 2502 -> 1621 us).
 static amh_status score_staged(amh_ctx *c, const ScoreArgs &all, const float *planes, const int *pix, float *costs) {
     const size_t n = (size_t)all.n_src, per_q = 24 + 4 * n;
     const int most = (int)(kStageHalf / per_q), parts = (all.Q + most - 1) / most;
@@ -1154,6 +1153,7 @@ amh_status amh_score_fixed(amh_ctx *c, const float *planes, const int *pix, int 
         HIPCHK(c, launch_score(a, c->half, c->stream));
         return AMH_OK;
     }
+    if (c->host_scores < kStageFrom && ++c->host_scores == kStageFrom) make_stage(c);
     if (c->stage) return score_staged(c, a, planes, pix, costs);
     const size_t bp = (size_t)Q * 16, bq = (size_t)Q * 8, bc = (size_t)Q * N * 4;
     unsigned char *buf = nullptr;

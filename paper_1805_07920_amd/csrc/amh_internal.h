@@ -80,7 +80,7 @@ struct PassArgs {
     int tiles_x, n_tiles;        // tile grid of this colour
     unsigned long long *counters;  // [kCounterKinds][kCounterSlots], kinds as listed at kCounterKinds
     int order;                   // tile order: 0 XCD bands, 1 hardware order
-    int rows = kDefaultTileRows;  // image rows of a tile (half-pass: 1, 2 or 4; ablation build: 2 or 4)
+    int rows = kDefaultTileRows;  // image rows of a tile (half-pass: 1 to 4; ablation build: 2 or 4)
     // initialisation from per-cell predictions (NULL: random initialisation)
     const float *prop = nullptr;  // [prop_h][prop_w][5]: depth, normal (3), confidence
     int prop_w = 0, prop_s = 0;   // cell grid width, cell size in reference pixels
@@ -119,7 +119,7 @@ struct BatchPhaseArgs {
     MethodDev m;
     int t, colour, kind;         // kind 0: init, 1: half-pass
     int order;
-    int rows;                    // image rows of a tile (2 or 4)
+    int rows;                    // image rows of a tile (2, 3 or 4)
     float conf_min;              // proposal initialisation threshold
     unsigned long long *counters;
     unsigned long long *tiles_done;  // [n_jobs] tiles finished in the job's last phase
