@@ -73,7 +73,7 @@ struct amh_ctx {
     hipEvent_t ev_init[2] = {nullptr, nullptr};
     bool init_timed = false;
     // launch configuration (autotuned): tile order of a launch, job order of a batch
-    int cfg_order = 0;
+    int cfg_order = -1;  // 0 XCD bands, 1 hardware order; -1 (not configured): bands in a batch, tile_order() alone
     int cfg_job_order = 1;
     int cfg_rows = kDefaultTileRows;  // tile rows of the half-pass: 2, or 4 for what views and size choose
     int cfg_persist = 0;               // batches: every half-pass in one persistent launch (1) or one launch each
