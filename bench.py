@@ -804,8 +804,8 @@ def main():
                      "peak_basis": "fp32 lane-operations: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz (157.3 TFLOP/s, "
                                    "FMA = 2 flops); unpacked v_add_f32 reaches 91 %, v_fma_f32 72 % "
                                    "(bench.py --calibrate-valu)",
-                     # counters taken per workload and tile shape; null for a shape not measured
-                     "traffic": pass_traffic_bytes(args.config, tile_rows),
+                     # counters taken per workload and tile shape, in XCD bands; null for a shape or order not measured
+                     "traffic": None if best_cfg & 1 else pass_traffic_bytes(args.config, tile_rows),
                      "traffic_unit": "bytes per launch (L2 <-> memory, calibrated rocprofv3 FETCH_SIZE + WRITE_SIZE)",
                      "kernel": f"pass_kernel<{1 if store == amh.AMH_F16 else 0}, {tile_rows}> "
                                f"(fused checkerboard half-pass, {tile_rows}-row tiles)",
