@@ -558,11 +558,6 @@ amh_status build_batch(amh_ctx *c, int n_jobs, const amh_job *jobs, bool proposa
     HIPCHK(c, hipMemcpyAsync(c->d_bviews, hv.data(), sizeof(ViewDev) * total_src, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->d_jobs, hj.data(), sizeof(BatchJobDev) * n_jobs, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->d_tables, tab.data(), sizeof(int) * tab.size(), hipMemcpyHostToDevice, c->stream));
-    if (proposal) {
-        size_t most = 0;
-        for (int j = 0; j < n_jobs; ++j) most = std::max(most, c->jobs[j].cells);
-        if ((st = nn_reserve(c, most)) != AMH_OK) return st;  // before capture: may allocate
-    }
     unsigned long long *tiles_done = c->d_bcount + kCounterKinds * kCounterSlots;
     unsigned long long *clocks = tiles_done + n_jobs;  // [n_jobs] completion, [n_jobs] start
     // persistent launch: its arguments and phase table in device memory, then the counters it clears
@@ -1197,12 +1192,27 @@ static amh_status run_batch_impl(amh_ctx *c, int n_jobs, const amh_job *jobs, bo
         key.push_back(jobs[j].iters);
         key.insert(key.end(), jobs[j].srcs, jobs[j].srcs + jobs[j].n_src);
     }
+    if (proposal) {
+        // the graph holds the addresses of the network's activations: one captured before they were last freed is not
+        // run again (reserved here, as nothing may be allocated during the capture)
+        size_t most = 0;
+        for (int j = 0; j < n_jobs; ++j) {
+            const View &r = c->views[jobs[j].ref];
+            most = std::max(most, (size_t)cell_rows(r.H) * cell_rows(r.W));
+        }
+        if ((st = nn_reserve(c, most)) != AMH_OK) return st;
+        key.push_back(nn_generation(c));
+    }
     if (!(c->graph_exec && key == c->batch_key)) {
         st = build_batch(c, n_jobs, jobs, proposal);
         if (st != AMH_OK) return st;
         c->batch_key = key;
     }
     HIPCHK(c, hipGraphLaunch(c->graph_exec, c->stream));
+    if (proposal) {  // the kept forward pass is the last job's, when the graph is run again too
+        const View &r = c->views[jobs[n_jobs - 1].ref];
+        nn_kept(c, 1, cell_rows(r.H), cell_rows(r.W));
+    }
     c->batch_ran = true;
     c->batch_stats = true;
     c->batch_jobs = n_jobs;

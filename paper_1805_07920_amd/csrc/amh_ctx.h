@@ -133,9 +133,12 @@ amh_status fail(amh_ctx *c, amh_status s, const char *fmt, ...) __attribute__((f
 // n-th allocation fails, 1-based)
 amh_status dalloc(amh_ctx *c, void **ptr, size_t bytes);
 
-// proposal network (amh_nn_api.hip): reserve activations for `cells` level-0 cells, and a forward pass
-// on an explicit stream that neither allocates nor synchronises (capturable)
+// proposal network (amh_nn_api.hip): reserve activations for `cells` level-0 cells (their generation counts how often
+// they were freed, and with them every address a graph holds), and a forward pass on an explicit stream that neither
+// allocates nor synchronises (capturable); nn_kept makes the pass that was launched the one kept for the backward pass
 amh_status nn_reserve(amh_ctx *c, size_t cells);
+int nn_generation(const amh_ctx *c);
+void nn_kept(amh_ctx *c, int n, int h, int w);
 amh_status nn_forward_stream(amh_ctx *c, const void *feats, const float *q_ref, int n, int h, int w, float *out,
                              hipStream_t s);
 

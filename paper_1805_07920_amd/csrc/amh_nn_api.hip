@@ -69,6 +69,7 @@ struct NetState {
     float *z;
     bf16_t *dz, *g_d0, *dc0, *g_d1, *dc1, *g_d2, *dc2, *g_e3, *g_e3a, *dp2, *g_e2, *g_e2a, *dp1, *g_e1, *g_e1a, *dp0,
         *g_e0, *g_e0a;
+    int acts_gen = 0;                    // ... how often they were freed
     int n = 0, h = 0, w = 0;
     bool have_fwd = false, have_grad = false;
 };
@@ -89,12 +90,14 @@ void free_net(amh_ctx *c) {
 
 namespace {
 
-amh_status free_acts(NetState *N) {
+// The kept forward pass goes with them, and so does every graph that was captured on them (acts_gen).
+void free_acts(NetState *N) {
     for (void *p : N->bufs)
         if (p) (void)hipFree(p);
     N->bufs.clear();
     N->cap_px = 0;
-    return AMH_OK;
+    N->have_fwd = false;
+    ++N->acts_gen;
 }
 
 // (re)allocates activations and gradients for P0 level-0 cells
@@ -343,6 +346,16 @@ namespace amh {
 
 amh_status nn_reserve(amh_ctx *c, size_t cells) { return ensure_acts(c, cells); }
 
+int nn_generation(const amh_ctx *c) { return c->net->acts_gen; }
+
+void nn_kept(amh_ctx *c, int n, int h, int w) {
+    NetState *N = c->net;
+    N->n = n;
+    N->h = h;
+    N->w = w;
+    N->have_fwd = true;
+}
+
 // forward pass on stream s; activations must be reserved (no allocation or synchronisation here,
 // so that it can be captured into a graph)
 amh_status nn_forward_stream(amh_ctx *c, const void *feats, const float *q_ref, int n, int h, int w, float *out,
@@ -380,10 +393,6 @@ amh_status nn_forward_stream(amh_ctx *c, const void *feats, const float *q_ref, 
     HIPCHK(c, layer(DEC2, N->e2, N->e3, N->d2, nullptr, h2, w2));
     HIPCHK(c, layer(DEC1, N->e1, N->d2, N->d1, nullptr, h1, w1));
     HIPCHK(c, layer(DEC0, N->e0, N->d1, N->d0, nullptr, h, w));
-    N->n = n;
-    N->h = h;
-    N->w = w;
-    N->have_fwd = true;
     return AMH_OK;
 }
 
@@ -460,7 +469,10 @@ amh_status amh_nn_forward(amh_ctx *c, const void *feats, const float *q_ref, int
     amh_status st = check_net(c);
     if (st != AMH_OK) return st;
     if ((st = nn_reserve(c, (size_t)n * h * w)) != AMH_OK) return st;
-    return nn_forward_stream(c, feats, q_ref, n, h, w, out, c->stream);
+    c->net->have_fwd = false;  // the launches write over the pass kept so far
+    if ((st = nn_forward_stream(c, feats, q_ref, n, h, w, out, c->stream)) != AMH_OK) return st;
+    nn_kept(c, n, h, w);
+    return AMH_OK;
 }
 
 amh_status amh_nn_backward(amh_ctx *c, const float *target, float *loss) {
