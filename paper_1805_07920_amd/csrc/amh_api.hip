@@ -89,30 +89,6 @@ amh_status dalloc(amh_ctx *c, void **ptr, size_t bytes) {
     return AMH_OK;
 }
 
-// The staging memory and its events, all or none (they are not needed for anything to work).
-static void free_stage(amh_ctx *c) {
-    for (auto &e : c->stage_ev) {
-        if (e) (void)hipEventDestroy(e);
-        e = nullptr;
-    }
-    if (c->stage) (void)hipHostFree(c->stage);
-    c->stage = nullptr;
-}
-
-static void make_stage(amh_ctx *c) {
-    void *p = nullptr;
-    if (hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocDefault) == hipSuccess) {
-        c->stage = static_cast<unsigned char *>(p);
-        for (auto &e : c->stage_ev)
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-                e = nullptr;
-                free_stage(c);
-                break;
-            }
-    }
-    (void)hipGetLastError();
-}
-
 }  // namespace amh
 
 namespace {
@@ -1099,42 +1075,6 @@ amh_status amh_set_state(amh_ctx *c, const float *planes, const float *cost, con
     return AMH_OK;
 }
 
-// Fixed hypotheses in host memory: the kernel reads the queries from pinned memory and writes the costs there, in equal
-// parts that fit a half of it, the host copying one part in or out while the GPU scores the other.  20 000 queries x 10
-// sources: three copies from and to pageable memory, which the first call still makes, took about 100 us of the call's
-// 151; now 119 in all (100 queries: 36 -> 22 us, 400 000: 2502 -> 1621 us).
-static amh_status score_staged(amh_ctx *c, const ScoreArgs &all, const float *planes, const int *pix, float *costs) {
-    const size_t n = (size_t)all.n_src, per_q = 24 + 4 * n;
-    const int most = (int)(kStageHalf / per_q), parts = (all.Q + most - 1) / most;
-    const int per = (all.Q + parts - 1) / parts;
-    const auto out_of = [&](int k) { return reinterpret_cast<float *>(c->stage + (k & 1) * kStageHalf + (size_t)per * 24); };
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < parts + 2 && e == hipSuccess; ++k) {
-        if (k >= 2) {  // part k - 2 is in the half that part k takes
-            const int first = (k - 2) * per, m = std::min(per, all.Q - first);
-            e = hipEventSynchronize(c->stage_ev[k & 1]);
-            if (e == hipSuccess && m > 0) std::memcpy(costs + first * n, out_of(k), m * n * 4);
-        }
-        const int first = k * per;
-        if (e != hipSuccess || k >= parts || first >= all.Q) continue;
-        unsigned char *st = c->stage + (k & 1) * kStageHalf;
-        ScoreArgs a = all;
-        a.Q = std::min(per, all.Q - first);
-        std::memcpy(st, planes + (size_t)first * 4, (size_t)a.Q * 16);
-        std::memcpy(st + (size_t)per * 16, pix + (size_t)first * 2, (size_t)a.Q * 8);
-        a.planes = reinterpret_cast<const float4 *>(st);
-        a.pix = reinterpret_cast<const int2 *>(st + (size_t)per * 16);
-        a.costs = out_of(k);
-        e = launch_score(a, c->half, c->stream);
-        if (e == hipSuccess) e = hipEventRecord(c->stage_ev[k & 1], c->stream);
-    }
-    if (e != hipSuccess) {
-        (void)hipStreamSynchronize(c->stream);  // nothing reads or writes the stage any more
-        return fail(c, AMH_E_HIP, "score_fixed: %s", hipGetErrorString(e));
-    }
-    return AMH_OK;
-}
-
 amh_status amh_score_fixed(amh_ctx *c, const float *planes, const int *pix, int Q, float *costs, int on_device) {
     if (!c) return AMH_E_INVALID_ARG;
     if (Q < 0 || Q > (1 << 24)) return fail(c, AMH_E_INVALID_ARG, "need 0 <= Q <= 2^24");
@@ -1160,10 +1100,8 @@ amh_status amh_score_fixed(amh_ctx *c, const float *planes, const int *pix, int 
         HIPCHK(c, launch_score(a, c->half, c->stream));
         return AMH_OK;
     }
-    if (c->host_scores < kStageFrom && ++c->host_scores == kStageFrom) make_stage(c);
-    if (c->stage) return score_staged(c, a, planes, pix, costs);
-    const size_t bp = (size_t)Q * 16, bq = (size_t)Q * 8, bc = (size_t)Q * N * 4;
     unsigned char *buf = nullptr;
+    const size_t bp = (size_t)Q * 16, bq = (size_t)Q * 8, bc = (size_t)Q * N * 4;
     amh_status s = dalloc(c, (void **)&buf, bp + bq + bc);
     if (s != AMH_OK) return s;
     hipError_t e = hipMemcpyAsync(buf, planes, bp, hipMemcpyHostToDevice, c->stream);
@@ -1504,7 +1442,6 @@ void amh_destroy(amh_ctx *c) {
     if (c->prop_pred) (void)hipFree(c->prop_pred);
     if (c->prop_qref) (void)hipFree(c->prop_qref);
     if (c->hyp) (void)hipFree(c->hyp);
-    free_stage(c);
     for (auto e : c->ev) (void)hipEventDestroy(e);
     for (auto e : c->ev_init)
         if (e) (void)hipEventDestroy(e);

@@ -39,11 +39,6 @@ struct JobResult {
 
 using namespace amh;  // private header: the library's own translation units only
 
-constexpr size_t kStageHalf = (size_t)1024 << 10;
-// The staging memory is made at this call with host buffers: making it takes about 90 us, what three calls gain, which
-// a context that scores once would not earn back.
-constexpr int kStageFrom = 2;
-
 struct amh_ctx {
     amh_params p;
     int alloc_count = 0;      // device allocations made by this context
@@ -109,11 +104,6 @@ struct amh_ctx {
     std::vector<hipEvent_t> fuse_ev;  // timing = 1: a start/stop pair per fusion kernel launch
     float fuse_ms = 0.f;               // their total device time in the last amh_fuse
     int fuse_n = 0;
-    // fixed hypotheses in host memory: pinned memory of 2 kStageHalf bytes (NULL: none yet, or none to be had; such
-    // calls copy to and from pageable memory), and an event for each half
-    int host_scores = 0;  // such calls so far, up to kStageFrom
-    unsigned char *stage = nullptr;
-    hipEvent_t stage_ev[2] = {nullptr, nullptr};
 };
 
 namespace amh {
