@@ -2173,6 +2173,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             // (6) the own plane's unified cost, (7) best hypothesis: own plane first, then region order; strictly
             //     lower wins
             const uint32_t act = S.act[pi];
+            float4 best = make_float4(0.f, 0.f, -1.f, 1.f);
             if (pix_ok) {
                 float own = __builtin_inff();
                 if (m.include_self) {
@@ -2205,7 +2206,10 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                 }
                 bcost = bc;
                 // no valid row at all (1-pixel image, no self): the own plane
-                const float4 best = to_float4(br < 0 || br == 8 ? S.cand[pi * 7 + 6] : S.pl[pi * 8 + br]);
+                best = to_float4(br < 0 || br == 8 ? S.cand[pi * 7 + 6] : S.pl[pi * 8 + br]);
+            }
+            wave_sync();  // every lane holds best: the pixel's lanes write over the planes it was read from
+            if (pix_ok) {
                 if (!m.refine) {
                     if (row == 0) S.cand[pi * 7 + 6] = to_gf4(best);
                 } else if (row < ncand) {
