@@ -271,9 +271,16 @@ amh_status amh_get_job_times(amh_ctx *ctx, int n, float *job_ms);
 amh_status amh_tune(amh_ctx *ctx, int n_jobs, const amh_job *jobs, int *best_config, float *ms_per_config);
 
 /* Sets the launch configuration (0..15, numbered as for amh_tune) for the
- * following launches of this context; results do not depend on it.
+ * following launches of this context; results do not depend on it.  Two-row
+ * tiles are taken at every size; without them the shape follows from size and
+ * view count.
  * INVALID_ARG outside 0..15. */
 amh_status amh_set_launch_config(amh_ctx *ctx, int config);
+
+/* The launches of the current reference's half-passes under the launch
+ * configuration: image rows of a workgroup's tile (1, 2, 3 or 4) and tile order
+ * (0 XCD bands, 1 hardware order).  STATE without a reference. */
+amh_status amh_get_pass_shape(const amh_ctx *ctx, int *rows, int *order);
 
 /* Work counters and timings of the current reference (or of the last batch). */
 amh_status amh_get_stats(const amh_ctx *ctx, amh_stats *out);

@@ -30,6 +30,7 @@ EXPORTS = [
     "amh_init_from_proposal", "amh_run_proposal", "amh_set_launch_config", "amh_run_batch_proposal",
     "amh_fusion_params_default", "amh_median_filter4", "amh_fuse", "amh_run_checkerboard_static",
     "amh_set_initial_hypotheses", "amh_nn_targets", "amh_probe_valu",
+    "amh_get_pass_shape",
 ]
 NET_CELL = 4  # reference pixels per proposal cell side
 NET_IN, NET_OUT = 16, 5
@@ -129,6 +130,7 @@ def lib():
         L.amh_nn_targets.argtypes = [vp, vp, vp, vp, ip, ip, vp]
         L.amh_run_proposal.argtypes = [vp, ip, C.POINTER(C.c_int), ip, ip]
         L.amh_set_launch_config.argtypes = [vp, ip]
+        L.amh_get_pass_shape.argtypes = [vp, C.POINTER(C.c_int), C.POINTER(C.c_int)]
         L.amh_run_batch_proposal.argtypes = [vp, ip, C.POINTER(amh_job)]
         L.amh_fusion_params_default.argtypes = [C.POINTER(amh_fusion_params)]
         L.amh_median_filter4.argtypes = [vp, vp, vp, ip, ip]
@@ -390,6 +392,12 @@ class Context:
         self._check(self.L.amh_get_job_result(self.h, job, ptrs[0][0], ptrs[1][0], ptrs[2][0], dev),
                     "amh_get_job_result")
         return depth, normal, cost
+
+    def get_pass_shape(self) -> dict:
+        """Tile rows and tile order of the current reference's half-passes (amh_get_pass_shape)."""
+        rows, order = C.c_int(), C.c_int()
+        self._check(self.L.amh_get_pass_shape(self.h, C.byref(rows), C.byref(order)), "amh_get_pass_shape")
+        return dict(rows=rows.value, order=order.value)
 
     def get_stats(self) -> dict:
         s = amh_stats()

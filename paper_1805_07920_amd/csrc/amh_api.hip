@@ -237,7 +237,8 @@ PassArgs pass_args(amh_ctx *c, int t, int colour) {
     const int tile_pix = ablation_build(a.m) ? kTilePix : kPix;
     a.tiles_x = (per_row + tile_pix - 1) / tile_pix;
     a.rows = ablation_build(a.m) ? c->cfg_rows : half_rows(c, a.n_src);
-    if (!ablation_build(a.m) && a.tiles_x * ((H + 3) / 4) <= kSmallTiles) a.rows = 1;
+    // one-row tiles for a small reference, unless two rows are configured
+    if (!ablation_build(a.m) && a.rows != 2 && a.tiles_x * ((H + 3) / 4) <= kSmallTiles) a.rows = 1;
     a.n_tiles = a.tiles_x * ((H + a.rows - 1) / a.rows);
     a.counters = c->counters;
     a.order = tile_order(c);
@@ -1218,6 +1219,17 @@ amh_status amh_set_launch_config(amh_ctx *c, int config) {
     if (config < 0 || config >= kTuneConfigs)
         return fail(c, AMH_E_INVALID_ARG, "launch configuration %d outside 0..%d", config, kTuneConfigs - 1);
     apply_config(c, config);
+    return AMH_OK;
+}
+
+amh_status amh_get_pass_shape(const amh_ctx *cc, int *rows, int *order) {
+    amh_ctx *c = const_cast<amh_ctx *>(cc);
+    if (!c) return AMH_E_INVALID_ARG;
+    if (!rows || !order) return fail(c, AMH_E_INVALID_ARG, "rows and order are required");
+    if (c->ref < 0) return fail(c, AMH_E_STATE, "no reference selected (amh_begin)");
+    const PassArgs a = pass_args(c, 0, 0);
+    *rows = a.rows;
+    *order = a.order;
     return AMH_OK;
 }
 
