@@ -19,10 +19,11 @@
 
 // Minimum waves per SIMD the kernels are compiled for (a register budget of
 // 512 / waves VGPRs).  The single-image and batched half-passes are held to 4
-// waves per SIMD (128 VGPRs), which they fit without spilling; the ablation
-// build gets the budget of 2 waves and settles near 125 VGPRs by itself; the
-// initialisation kernels, which hold half a window block per lane, fit 3
-// waves (at 4 they spill inside the source loop).
+// waves per SIMD (128 VGPRs), which they fit without spilling (112 with float16
+// sources); the ablation build gets the budget of 2 waves and settles at 120
+// VGPRs (float16 sources) and 129 by itself; the initialisation kernels, which
+// hold half a window block per lane, fit 3 waves (at 4 they spill inside the
+// source loop).
 #ifndef AMH_PASS_WAVES_PER_EU
 #define AMH_PASS_WAVES_PER_EU 4
 #endif
@@ -1037,8 +1038,7 @@ constexpr int kStdRows = 20;  // propagated rows of the standard symmetric patte
 // own plane at R = 20, and the view selection's counts n1, n2 compared as the
 // same fractions of 20 rows as of 8) and m.heuristic (each hypothesis, and each refinement
 // candidate, costs the mean of its own k lowest per-view costs; no selection memory).
-// tid: threadIdx.x (the persistent launch passes it through an opaque copy, so that nothing derived from
-// it is kept live across its tiles)
+// tid: threadIdx.x
 template <int HALF, int WAVES>
 __device__ __forceinline__ void ablation_body(const PassArgs &a, int L, unsigned char *smem, int tid) {
     // row blocks: 3 in the standard symmetric pattern (ablation build only), else 1
@@ -1516,7 +1516,8 @@ struct QLds {
 };
 
 struct HalfLds {
-    float *tile;          // [ROWS + 10][kPassTileW] reference intensities; then the rows' aggregated costs
+    float *tile;          // [ROWS + 10][kPassTileW] reference intensities; then the rows' aggregated costs, and in
+                          // row 0's place the kept hypothesis's
     float2 *rw;           // [pixel][kWinStride] window blocks
     gf4 *pl;              // [pixel][8] the rows' planes; then [pixel][7] of QLds, cand's inverse-depth terms
     QLds *q;              // [pixel][8] their inverse-depth terms; then cand
@@ -1534,7 +1535,7 @@ struct HalfLds {
     float *wsum;          // [pixel] their sum
     int *count;           // [ROWS] distinct hypotheses of each row; [2][ROWS] its pairs in the stage, scored and counted
     unsigned *nshort;     // [ROWS] evaluations that took no samples
-    unsigned char *own;   // [pixel] the row that holds the pixel's own plane, or kNoRow
+    unsigned char *own;   // [pixel] the row that holds the pixel's own plane, or kNoRow; then the kept slot of cand
     gf4 *u;               // [2][pixel] the refinement's draws: perturbation, random (t >= 3)
 };
 
@@ -1636,6 +1637,14 @@ __device__ __forceinline__ void same_below(const int (&p)[4], int ok, int r, int
 
 // A cost as stored: negative (kShort, weighted or not) where no sample was taken and the cost is 2.
 __device__ __forceinline__ float stored_cost(float c) { return c < 0.f ? 2.f : c; }
+
+// threadIdx.x anew, from the wave's number and the lane's: nothing of it is kept in a register meanwhile, nor what follows
+// from it (the compiler cannot see that it is the same again)
+__device__ __forceinline__ int thread_again(int wave) {
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    return wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (unsigned)zero));
+}
 
 // distance of window sample s from the centre, the square roots correctly rounded
 constexpr float kR2 = 1.4142135623730951f, kR10 = 3.1622776601683795f, kR18 = 4.242640687119285f,
@@ -1744,8 +1753,9 @@ __device__ __forceinline__ WinStats build_window8(const Reader &rd, const Method
 
 __device__ __forceinline__ QLds q_lds(const PlaneQ &q) { return QLds{q.ok ? q.q0 : -1.0, q.qu, q.qv}; }
 
-// tid: threadIdx.x (the persistent launch passes it through an opaque copy, so that nothing derived from
-// it is kept live across its tiles)
+// tid: threadIdx.x.  Registers: the float32 build has 128 for 4 waves on a SIMD and needs all of them in the evaluation;
+// nothing that the pixel's own lanes hold between the stages stays in one meanwhile (thread_again, the row, the kept cost
+// and slot in LDS), and nothing is spilled.
 template <int HALF, int ROWS>
 __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned char *smem, int tid) {
     constexpr int WAVES = tile_waves(ROWS);
@@ -1867,7 +1877,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
         return q_lds(plane_q(a.ref, m, load_plane(a.st.planes, (size_t)hy * W + hx), hx, hy));
     };
     {
-        int lane = tid & 63, slot = 0, hp = 0;
+        int lane = thread_again(wave) & 63, slot = 0, hp = 0;
         bool live = false;
         QLds q = {-1.0, 0.f, 0.f};
         WinStats ws = {1.f, 0.f};
@@ -1908,16 +1918,15 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
     const int rest0 = n_chunks * 64, n_rest = max(n_hyp - rest0, 0);
     const uint32_t div_rest = n_rest ? ((1u << 18) + n_rest - 1) / n_rest : 0u;  // exact: i n_rest < 2^18
     const int ncand = a.t >= 3 ? 6 : 3;
-    float bcost = 0.f;  // cost of the kept hypothesis
-    int bcand = 6;      // its slot in cand
     int n_ref = 0;      // refinement pairs
     for (int stage = 0; stage < 4; ++stage) {
-        // the lane's place, derived anew in every stage from a copy the compiler cannot see through: what follows
-        // from it (the random draws among it) is not computed ahead of the loop and held in scratch
-        int tid_s = tid;
-        asm volatile("" : "+v"(tid_s));
+        // the lane's place, derived anew in every stage: what follows from it (the random draws among it) is not computed
+        // ahead of the loop and held in scratch
+        const int tid_s = thread_again(wave);
         const int lane = tid_s & 63, g = lane >> 3, row = lane & 7, pi = tid_s >> 3;
-        const int y = y0 + wave, x = col_of(pi);
+        int wave_s = wave;
+        asm volatile("" : "+s"(wave_s));
+        const int y = y0 + wave_s, x = col_of(pi);
         const bool pix_ok = y < Hh && x < W;
         const size_t p = pix_ok ? (size_t)y * W + x : 0;
         // pairs of the stage, and where they lie
@@ -2174,6 +2183,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             //     lower wins
             const uint32_t act = S.act[pi];
             float4 best = make_float4(0.f, 0.f, -1.f, 1.f);
+            float bc = 0.f;  // its cost
             if (pix_ok) {
                 float own = __builtin_inff();
                 if (m.include_self) {
@@ -2195,7 +2205,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                     }
                 }
                 int br = m.include_self ? 8 : -1;
-                float bc = own;
+                bc = own;
                 for (int r = 0; r < 8; ++r) {
                     if (S.rep[pi * 8 + r] == kNoRow) continue;
                     const float c = S.tile[pi * 8 + r];
@@ -2204,12 +2214,12 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                         bc = c;
                     }
                 }
-                bcost = bc;
                 // no valid row at all (1-pixel image, no self): the own plane
                 best = to_float4(br < 0 || br == 8 ? S.cand[pi * 7 + 6] : S.pl[pi * 8 + br]);
             }
-            wave_sync();  // every lane holds best: the pixel's lanes write over the planes it was read from
+            wave_sync();  // every lane holds best: the pixel's lanes write over the planes and costs it was found by
             if (pix_ok) {
+                if (row == 0) S.tile[pi * 8] = bc;
                 if (!m.refine) {
                     if (row == 0) S.cand[pi * 7 + 6] = to_gf4(best);
                 } else if (row < ncand) {
@@ -2261,7 +2271,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                 const int vt = S.vt[pi];
                 j0 = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
                 const float r0 = S.ms[(pi * 6 + row) * N + __popc(act & ((1u << j0) - 1u))];
-                if (weighted_cost(r0) / S.wsum[pi] < bcost) {
+                if (weighted_cost(r0) / S.wsum[pi] < S.tile[pi * 8]) {
                     n_mine = __popc(act) - 1;
                 } else {
                     if (r0 < 0.f) atomicAdd(&S.nshort[wave], 1u);
@@ -2281,7 +2291,9 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             if (n_mine > 0)
                 for (uint32_t rest = act & ~(1u << j0); rest; rest &= rest - 1u)
                     list3[pre++] = (unsigned short)(pi | (__builtin_ctz(rest) << kPairView) | (row << kPairCand));
-        } else if (stage == 3 && pix_ok) {
+        } else if (stage == 3 && pix_ok && row == 0) {
+            float bcost = S.tile[pi * 8];
+            int bcand = 6;  // the kept hypothesis's slot in cand
             const uint32_t act = S.act[pi];
             const int nw = __popc(act);
             const float wsum = S.wsum[pi];
@@ -2301,22 +2313,23 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                     bcand = c;
                 }
             }
-            if (ns && row == 0) atomicAdd(&S.nshort[wave], ns);
+            if (ns) atomicAdd(&S.nshort[wave], ns);
+            S.tile[pi * 8] = bcost;
+            S.own[pi] = (unsigned char)bcand;
         }
         __syncthreads();
     }
 
     // (9) write the pixel
     if (wave >= ROWS) return;
-    int tid_e = tid;
-    asm volatile("" : "+v"(tid_e));
     {
+        const int tid_e = thread_again(wave);
         const int pi = tid_e >> 3, x = col_of(pi), y = y0 + wave, lane = tid_e & 63;
         const bool first = (tid_e & 7) == 0 && y < Hh && x < W;  // the pixel's first lane
         if (first) {
             const size_t p = (size_t)y * W + x;
-            store_plane(a.st.planes, p, to_float4(S.cand[pi * 7 + bcand]));
-            glob(a.st.cost)[p] = bcost;
+            store_plane(a.st.planes, p, to_float4(S.cand[pi * 7 + (m.refine ? S.own[pi] : 6)]));
+            glob(a.st.cost)[p] = S.tile[pi * 8];
             glob(a.st.S)[p] = S.sel[pi];
             glob(a.st.v)[p] = S.vt[pi];
         }
@@ -2434,10 +2447,10 @@ __device__ __forceinline__ PassArgs batch_pass_args(const BatchPhaseArgs &b, con
 }
 
 // the job's completion time: stamped by the last work item of its last phase
-__device__ __forceinline__ void batch_stamp(const BatchPhaseArgs &b, int lo, int j, long long items) {
+__device__ __forceinline__ void batch_stamp(const BatchPhaseArgs &b, int lo, int j, long long items, int wave) {
     if (b.is_last[lo]) {
         __syncthreads();
-        if (threadIdx.x == 0) {
+        if (thread_again(wave) == 0) {
             __threadfence();
             if (atomicAdd(&b.tiles_done[j], 1ull) == (unsigned long long)(items - 1)) b.job_end[j] = wall_clock64();
         }
@@ -2455,7 +2468,7 @@ void batch_kernel(BatchPhaseArgs b) {
     const BatchJobDev &J = b.jobs[j];
     const PassArgs a = batch_pass_args(b, J, ROWS);
     pass_body<HALF, ROWS>(a, __builtin_amdgcn_readfirstlane(L), smem, (int)threadIdx.x);
-    batch_stamp(b, lo, j, J.n_tiles);
+    batch_stamp(b, lo, j, J.n_tiles, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // Batched initialisation: one initialisation block (kInitBlock pixels of the colour) per workgroup, the body
@@ -2471,7 +2484,7 @@ batch_init_kernel(BatchPhaseArgs b) {
     const BatchJobDev &J = b.jobs[j];
     const PassArgs a = batch_pass_args(b, J, 4);
     init_pair_body<HALF>(a, __builtin_amdgcn_readfirstlane(L), cst, &nshort);
-    batch_stamp(b, lo, j, J.n_iblocks);
+    batch_stamp(b, lo, j, J.n_iblocks, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // ---------------------------------------------------------------------------
@@ -2481,10 +2494,10 @@ batch_init_kernel(BatchPhaseArgs b) {
 // ---------------------------------------------------------------------------
 // Grid barrier between phases: every thread releases its writes at device scope, the workgroup counts its
 // arrival, waits (bounded) until `target` workgroups arrived, and acquires.  False when a wait ran out.
-__device__ __forceinline__ bool grid_barrier(const PersistArgs *P, unsigned target, int *s_ok) {
+__device__ __forceinline__ bool grid_barrier(const PersistArgs *P, unsigned target, int *s_ok, int wave) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (thread_again(wave) == 0) {
         __hip_atomic_fetch_add(P->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned long long t0 = wall_clock64();
         int ok = 1;
@@ -2536,10 +2549,11 @@ void persist_kernel(const PersistArgs *__restrict__ Pg) {
         return;
     }
     const int n_phases = __builtin_amdgcn_readfirstlane(Pg->n_phases);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int ph = 0; ph < n_phases; ++ph) {
         for (;;) {
             const PersistArgs *P = opaque(Pg);
-            if (threadIdx.x == 0) s_item = (int)atomicAdd(&P->next[ph * 8 + x], 1u);
+            if (thread_again(wave) == 0) s_item = (int)atomicAdd(&P->next[ph * 8 + x], 1u);
             __syncthreads();
             const int g = __builtin_amdgcn_readfirstlane(s_item);
             __syncthreads();
@@ -2576,21 +2590,20 @@ void persist_kernel(const PersistArgs *__restrict__ Pg) {
             a.conf_min = P->conf_min;
             a = make_uniform(a);
             a.views = P->views + __builtin_amdgcn_readfirstlane(J.view_off);
-            int tid = (int)threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            pass_body<HALF, ROWS>(a, L, smem, tid);
+            pass_body<HALF, ROWS>(a, L, smem, thread_again(wave));
             // per-job completion stamp of the job's last half-pass
             const PersistArgs *P2 = opaque(Pg);
             if (P2->phases[ph].is_last[lo]) {
                 __syncthreads();
-                if (threadIdx.x == 0) {
+                if (thread_again(wave) == 0) {
                     __threadfence();
                     if (atomicAdd(&P2->tiles_done[j], 1ull) == (unsigned long long)(P2->jobs[j].n_tiles - 1))
                         P2->job_end[j] = wall_clock64();
                 }
             }
         }
-        if (ph + 1 < n_phases && !grid_barrier(opaque(Pg), (unsigned)(ph + 1) * gridDim.x, &s_ok)) return;
+        if (ph + 1 < n_phases && !grid_barrier(opaque(Pg), (unsigned)(ph + 1) * gridDim.x, &s_ok, wave))
+            return;
     }
 }
 
