@@ -110,15 +110,13 @@ typedef struct {
                           * sources (list the nearest first); 0 (default) = 4; at most 32 */
 } amh_params;
 
-/* Counters of the work performed since the last amh_begin / amh_run_checkerboard. */
+/* Counters of the work performed since the last amh_begin / amh_run_checkerboard: the evaluations of the method,
+ * whether each was computed by itself or not (amh_get_scored_evals). */
 typedef struct {
     uint64_t evals_total;       /* hypothesis x view NCC evaluations (36 samples each) */
     uint64_t evals_init;        /* ... in the random initialisation */
-    uint64_t evals_propagation; /* ... of the 8 propagated planes and the pixel's own, on every view (a plane that
-                                 * several regions hold counts for each, the pixel's own also on views without
-                                 * weight, though such evaluations are shared or left out) */
-    uint64_t evals_refine;      /* ... of refinement candidates, as far as they were scored (a candidate out of the
-                                 * running after its first view is not scored on the others) */
+    uint64_t evals_propagation; /* ... of the 8 propagated planes and the pixel's own, on every view */
+    uint64_t evals_refine;      /* ... of refinement candidates, on every view that carries weight */
     int n_passes;
     float ms_per_pass[64];      /* device time of each half-pass (timing = 1), else 0 */
     float ms_init;
@@ -129,7 +127,9 @@ typedef struct {
     uint64_t evals_short;       /* of evals_propagation + evals_refine: evaluations whose cost 2 was decided
                                  * before any sample was taken (plane depth outside [depth_min, depth_max] at the
                                  * pixel, window centre behind the source camera or outside its image, a window
-                                 * corner not in front of it) */
+                                 * corner not in front of it).  Of a refinement candidate that is out of the
+                                 * running after the pixel's most important view, the other views count here only
+                                 * where its plane is out of range on all of them */
     uint64_t evals_init_short;  /* the same among evals_init */
 } amh_stats;
 
@@ -284,6 +284,12 @@ amh_status amh_get_pass_shape(const amh_ctx *ctx, int *rows, int *order);
 
 /* Work counters and timings of the current reference (or of the last batch). */
 amh_status amh_get_stats(const amh_ctx *ctx, amh_stats *out);
+
+/* Of evals_propagation + evals_refine as amh_get_stats has them: the evaluations
+ * that were computed.  A plane that several regions of a pixel hold is scored
+ * once for them, the pixel's own on the views that carry weight, and a candidate
+ * that is out of the running after the pixel's most important view on that view. */
+amh_status amh_get_scored_evals(const amh_ctx *ctx, uint64_t *n);
 
 /* ------------------------------------------------------------------------
  * Learned proposal.  Not part of the paper: a small convolutional network

@@ -30,7 +30,7 @@ EXPORTS = [
     "amh_init_from_proposal", "amh_run_proposal", "amh_set_launch_config", "amh_run_batch_proposal",
     "amh_fusion_params_default", "amh_median_filter4", "amh_fuse", "amh_run_checkerboard_static",
     "amh_set_initial_hypotheses", "amh_nn_targets", "amh_probe_valu",
-    "amh_get_pass_shape",
+    "amh_get_pass_shape", "amh_get_scored_evals",
 ]
 NET_CELL = 4  # reference pixels per proposal cell side
 NET_IN, NET_OUT = 16, 5
@@ -131,6 +131,7 @@ def lib():
         L.amh_run_proposal.argtypes = [vp, ip, C.POINTER(C.c_int), ip, ip]
         L.amh_set_launch_config.argtypes = [vp, ip]
         L.amh_get_pass_shape.argtypes = [vp, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        L.amh_get_scored_evals.argtypes = [vp, C.POINTER(C.c_uint64)]
         L.amh_run_batch_proposal.argtypes = [vp, ip, C.POINTER(amh_job)]
         L.amh_fusion_params_default.argtypes = [C.POINTER(amh_fusion_params)]
         L.amh_median_filter4.argtypes = [vp, vp, vp, ip, ip]
@@ -408,6 +409,12 @@ class Context:
                     ms_fuse_kernels=s.ms_fuse_kernels, n_fuse_kernels=s.n_fuse_kernels,
                     fallback_pixels=s.fallback_pixels, evals_short=s.evals_short,
                     evals_init_short=s.evals_init_short)
+
+    def get_scored_evals(self) -> int:
+        """Evaluations of the half-passes that were computed (amh_get_scored_evals)."""
+        n = C.c_uint64()
+        self._check(self.L.amh_get_scored_evals(self.h, C.byref(n)), "amh_get_scored_evals")
+        return n.value
 
     # --- learned proposal ----------------------------------------------------------------
     @staticmethod

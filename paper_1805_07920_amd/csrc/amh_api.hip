@@ -1384,40 +1384,46 @@ amh_status amh_run_proposal(amh_ctx *c, int ref, const int *srcs, int n_src, int
     return AMH_OK;
 }
 
+// the evaluation counters of the current reference, or of the last batch (zeros once its buffers are gone)
+static amh_status read_counts(amh_ctx *c, unsigned long long k[kCounterKinds]) {
+    std::fill(k, k + kCounterKinds, 0ull);
+    const unsigned long long *src = c->batch_stats ? c->d_bcount : c->counters;
+    if (!src) return AMH_OK;
+    std::vector<unsigned long long> h(kCounterKinds * kCounterSlots);
+    HIPCHK(c, hipMemcpyAsync(h.data(), src, h.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (c->batch_stats) {
+        amh_status fs = check_persist_fault(c);
+        if (fs != AMH_OK) return fs;
+    }
+    for (int i = 0; i < kCounterKinds * kCounterSlots; ++i) k[i / kCounterSlots] += h[i];
+    return AMH_OK;
+}
+
+amh_status amh_get_scored_evals(const amh_ctx *cc, uint64_t *n) {
+    amh_ctx *c = const_cast<amh_ctx *>(cc);
+    if (!c) return AMH_E_INVALID_ARG;
+    if (!n) return fail(c, AMH_E_INVALID_ARG, "n is NULL");
+    unsigned long long k[kCounterKinds];
+    amh_status st = read_counts(c, k);
+    if (st != AMH_OK) return st;
+    *n = k[6];
+    return AMH_OK;
+}
+
 amh_status amh_get_stats(const amh_ctx *cc, amh_stats *out) {
     amh_ctx *c = const_cast<amh_ctx *>(cc);
     if (!c || !out) return AMH_E_INVALID_ARG;
     memset(out, 0, sizeof *out);
-    if (c->batch_stats && c->d_bcount) {
-        std::vector<unsigned long long> h(kCounterKinds * kCounterSlots);
-        HIPCHK(c, hipMemcpyAsync(h.data(), c->d_bcount, h.size() * 8, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        amh_status fs = check_persist_fault(c);
-        if (fs != AMH_OK) return fs;
-        for (int k = 0; k < kCounterKinds; ++k) {
-            c->batch_counts[k] = 0;
-            for (int i = 0; i < kCounterSlots; ++i) c->batch_counts[k] += h[k * kCounterSlots + i];
-        }
-        out->evals_init = c->batch_counts[0];
-        out->evals_propagation = c->batch_counts[1];
-        out->evals_refine = c->batch_counts[2];
-        out->fallback_pixels = c->batch_counts[3];
-        out->evals_short = c->batch_counts[4];
-        out->evals_init_short = c->batch_counts[5];
-    } else if (!c->batch_stats && c->counters) {
-        std::vector<unsigned long long> h(kCounterKinds * kCounterSlots);
-        HIPCHK(c, hipMemcpyAsync(h.data(), c->counters, h.size() * 8, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        unsigned long long s[kCounterKinds] = {};
-        for (int k = 0; k < kCounterKinds; ++k)
-            for (int i = 0; i < kCounterSlots; ++i) s[k] += h[k * kCounterSlots + i];
-        out->evals_init = s[0];
-        out->evals_propagation = s[1];
-        out->evals_refine = s[2];
-        out->fallback_pixels = s[3];
-        out->evals_short = s[4];
-        out->evals_init_short = s[5];
-    }
+    unsigned long long k[kCounterKinds];
+    amh_status st = read_counts(c, k);
+    if (st != AMH_OK) return st;
+    out->evals_init = k[0];
+    out->evals_propagation = k[1];
+    out->evals_refine = k[2];
+    out->fallback_pixels = k[3];
+    out->evals_short = k[4];
+    out->evals_init_short = k[5];
     out->evals_total = out->evals_init + out->evals_propagation + out->evals_refine;
     out->n_passes = c->n_timed;
     for (int i = 0; i < c->n_timed && i < 64; ++i) {

@@ -13,8 +13,9 @@ constexpr int kMaxSrc = 32;
 constexpr int kQuadPad = 16;
 constexpr int kMaxImageSide = 16383 - 2 * kQuadPad;
 constexpr int kCounterSlots = 256;    // eval counters are spread over slots to avoid one hot atomic
-constexpr int kCounterKinds = 6;      // init, propagation, refinement evaluations; proposal fallbacks;
-                                       // short evaluations (no samples taken) of the half-pass and of init
+constexpr int kCounterKinds = 7;      // init, propagation, refinement evaluations; proposal fallbacks;
+                                       // short evaluations (no samples taken) of the half-pass and of init;
+                                       // evaluations the half-pass computed
 constexpr int kPix = 8;               // half-pass: same-colour pixels per tile row (a wave: 8 pixels x 8 regions)
 constexpr int kGroups = 7;            // ablation build: pixels per wave (7 groups x 9 lanes = 63 lanes)
 constexpr int kRows = 9;              // ... 8 propagated hypotheses + the pixel's own

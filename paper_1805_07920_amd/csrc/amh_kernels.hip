@@ -1457,6 +1457,7 @@ __device__ __forceinline__ void ablation_body(const PassArgs &a, int L, unsigned
     }
     count_evals(a.counters, 1, (unsigned long long)n_prop);
     if (m.refine) count_evals(a.counters, 2, (unsigned long long)n_ref);
+    count_evals(a.counters, 6, (unsigned long long)(n_prop + n_ref));  // each scored by itself
     // the wave's own LDS atomics are complete before this read (LDS operations of a wave are in order)
     count_evals(a.counters, 4, lane == 0 ? (unsigned long long)S.nshort[wave] : 0ull);
 }
@@ -1495,9 +1496,12 @@ __device__ __forceinline__ void ablation_body(const PassArgs &a, int L, unsigned
 // beats.  One piece of code scores every kind of pair (stages 0..3), so that
 // the evaluation is in the instruction cache twice, not five times.
 //
-// The counters report every region's plane and the pixel's own on every view,
-// shared or left out evaluations included, and of the refinement what was
-// scored.
+// The counters report the method's evaluations: every region's plane and the
+// pixel's own on every view and every refinement candidate on the views that
+// carry weight, shared or left out ones included.  Those left out count as
+// short where it is known: own planes are tested on every view, of a dropped
+// candidate only its plane (its views too cost 1.2 to 2.3 % of the time, for
+// 0.4 % of the short ones).  What was scored is counted by itself.
 // ---------------------------------------------------------------------------
 constexpr int kFullChunk = 53;
 // Up to this many views the own planes are listed with the propagated ones: at most k = 4 views carry weight, so with
@@ -1918,7 +1922,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
     const int rest0 = n_chunks * 64, n_rest = max(n_hyp - rest0, 0);
     const uint32_t div_rest = n_rest ? ((1u << 18) + n_rest - 1) / n_rest : 0u;  // exact: i n_rest < 2^18
     const int ncand = a.t >= 3 ? 6 : 3;
-    int n_ref = 0;      // refinement pairs
+    int n_scored = n_hyp * N;  // evaluations computed by the workgroup
     for (int stage = 0; stage < 4; ++stage) {
         // the lane's place, derived anew in every stage: what follows from it (the random draws among it) is not computed
         // ahead of the loop and held in scratch
@@ -1982,6 +1986,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                                            : kShort;
             S.ms[dst] = stage >= 2 ? S.wgt[hp * N + j] * cost : cost;
         }
+        if (stage > 0) n_scored += total;
         if (stage == 1) {
             // the own planes' evaluations on the views without weight, which nothing reads: short or not
             unsigned ns = 0;
@@ -2006,9 +2011,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                 if (!q.ok || !src_warp<HALF>(a.views[d >> kPairView], hx, hy, q.q0, q.qu, q.qv, sw)) ++ns;
             }
             if (ns) atomicAdd(&S.nshort[0], ns);
-        } else if (stage >= 2) {
-            n_ref += total;
-        } else if (m.refine && wave == (n_chunks * N + ((n_rest * N + 63) >> 6)) % WAVES) {
+        } else if (stage == 0 && m.refine && wave == (n_chunks * N + ((n_rest * N + 63) >> 6)) % WAVES) {
             // the refinement's draws, one per pixel and stream, by the wave whose turn it is (Philox is ~700 issue
             // slots: too many for every lane of every wave)
             const int pix = lane % P, str = lane / P;
@@ -2266,31 +2269,32 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             // candidates still in the running: their pairs with the pixel's other views
             const uint32_t act = S.act[pi];
             unsigned short *list3 = reinterpret_cast<unsigned short *>(S.ms + 6 * N * P) + wave * 6 * kPix * N;
-            int n_mine = 0, j0 = 0;
+            uint32_t others = 0;
             if (pix_ok && row < ncand) {
                 const int vt = S.vt[pi];
-                j0 = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
+                const int j0 = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
                 const float r0 = S.ms[(pi * 6 + row) * N + __popc(act & ((1u << j0) - 1u))];
-                if (weighted_cost(r0) / S.wsum[pi] < S.tile[pi * 8]) {
-                    n_mine = __popc(act) - 1;
-                } else {
-                    if (r0 < 0.f) atomicAdd(&S.nshort[wave], 1u);
-                    n_mine = -1;
+                others = act & ~(1u << j0);
+                if (!(weighted_cost(r0) / S.wsum[pi] < S.tile[pi * 8])) {
+                    // out; its other evaluations are short too where its plane is out of range
+                    if (r0 < 0.f)
+                        atomicAdd(&S.nshort[wave],
+                                  reinterpret_cast<const QLds *>(S.pl + pi * 8)[row].q0 < 0.0 ? 1u + __popc(others) : 1u);
+                    S.ms[(pi * 6 + row) * N] = __builtin_nanf("");
+                    others = 0;
                 }
             }
-            if (row < ncand && n_mine < 0) S.ms[(pi * 6 + row) * N] = __builtin_nanf("");  // out
             // exclusive prefix of the wave's pair counts
-            int pre = max(n_mine, 0);
+            int pre = __popc(others);
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 const int u = __shfl_up(pre, o, 64);
                 if (lane >= o) pre += u;
             }
             if (lane == 63) S.count[ROWS + wave] = pre;
-            pre -= max(n_mine, 0);
-            if (n_mine > 0)
-                for (uint32_t rest = act & ~(1u << j0); rest; rest &= rest - 1u)
-                    list3[pre++] = (unsigned short)(pi | (__builtin_ctz(rest) << kPairView) | (row << kPairCand));
+            pre -= __popc(others);
+            for (uint32_t rest = others; rest; rest &= rest - 1u)
+                list3[pre++] = (unsigned short)(pi | (__builtin_ctz(rest) << kPairView) | (row << kPairCand));
         } else if (stage == 3 && pix_ok && row == 0) {
             float bcost = S.tile[pi * 8];
             int bcand = 6;  // the kept hypothesis's slot in cand
@@ -2321,26 +2325,39 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
     }
 
     // (9) write the pixel
-    if (wave >= ROWS) return;
-    {
-        const int tid_e = thread_again(wave);
-        const int pi = tid_e >> 3, x = col_of(pi), y = y0 + wave, lane = tid_e & 63;
-        const bool first = (tid_e & 7) == 0 && y < Hh && x < W;  // the pixel's first lane
-        if (first) {
+    const int tid_e = thread_again(wave);
+    if (wave < ROWS && (tid_e & 7) == 0) {  // the pixel's first lane
+        const int pi = tid_e >> 3, x = col_of(pi), y = y0 + wave;
+        if (y < Hh && x < W) {
             const size_t p = (size_t)y * W + x;
             store_plane(a.st.planes, p, to_float4(S.cand[pi * 7 + (m.refine ? S.own[pi] : 6)]));
             glob(a.st.cost)[p] = S.tile[pi * 8];
             glob(a.st.S)[p] = S.sel[pi];
             glob(a.st.v)[p] = S.vt[pi];
         }
-        const int rows = __popcll(__ballot(S.rep[tid_e] != kNoRow)) + (m.include_self ? __popcll(__ballot(first)) : 0);
-        // the wave's own LDS atomics are complete before this read (LDS operations of a wave are in order)
-        const unsigned ns = S.nshort[wave];
+    }
+    // (10) the workgroup's counters, by one wave (an atomic on each per row is a few tenths of a percent of the launch)
+    if (!m.refine) __syncthreads();  // the rows' last short counts
+    if (wave == 0) {
+        const int lane = tid_e & 63, y = y0 + (lane >> 3);
+        const bool in = lane < P && y < Hh && col_of(lane) < W;  // lane: a pixel
+        int rows = m.include_self ? __popcll(__ballot(in)) : 0, n_ref = 0, n_short = 0;
+#pragma unroll
+        for (int k = 0; k < ROWS; ++k) {
+            rows += __popcll(__ballot(S.rep[64 * k + lane] != kNoRow));
+            n_short += __builtin_amdgcn_readfirstlane((int)S.nshort[k]);
+        }
+        if (m.refine) {
+            const int views = in ? __popc(S.act[lane]) : 0;
+#pragma unroll
+            for (int b = 0; b < 6; ++b) n_ref += __popcll(__ballot((views >> b) & 1)) << b;
+        }
         if (lane == 0) {
-            const int at = (blockIdx.x * ROWS + wave) % kCounterSlots;
+            const int at = blockIdx.x % kCounterSlots;
             atomicAdd(&a.counters[1 * kCounterSlots + at], (unsigned long long)(rows * N));
-            if (wave == 0 && n_ref) atomicAdd(&a.counters[2 * kCounterSlots + at], (unsigned long long)n_ref);
-            if (ns) atomicAdd(&a.counters[4 * kCounterSlots + at], (unsigned long long)ns);
+            if (n_ref) atomicAdd(&a.counters[2 * kCounterSlots + at], (unsigned long long)(n_ref * ncand));
+            if (n_short) atomicAdd(&a.counters[4 * kCounterSlots + at], (unsigned long long)n_short);
+            atomicAdd(&a.counters[6 * kCounterSlots + at], (unsigned long long)n_scored);
         }
     }
 }
