@@ -927,6 +927,7 @@ amh_status amh_begin(amh_ctx *c, int ref, const int *srcs, int n_src) {
     c->init_timed = false;
     c->batch_stats = false;
     HIPCHK(c, launch_zero_u64(c->counters, kCounterKinds * kCounterSlots, c->stream));
+    c->counted = true;
     return AMH_OK;
 }
 
@@ -1004,6 +1005,7 @@ amh_status amh_run_checkerboard_static(amh_ctx *c, int ref, const int *srcs, int
     c->init_timed = false;
     c->batch_stats = false;
     HIPCHK(c, launch_zero_u64(c->counters, kCounterKinds * kCounterSlots, c->stream));
+    c->counted = true;
     for (int colour = 0; colour < 2; ++colour) {  // random initialisation writes every pixel of the state
         PassArgs a = pass_args(c, 0, colour);
         a.views = viewc;
@@ -1384,10 +1386,11 @@ amh_status amh_run_proposal(amh_ctx *c, int ref, const int *srcs, int n_src, int
     return AMH_OK;
 }
 
-// the evaluation counters of the current reference, or of the last batch (zeros once its buffers are gone)
+// the evaluation counters of the current reference, or of the last batch (zeros once its buffers are gone, or before there
+// was either)
 static amh_status read_counts(amh_ctx *c, unsigned long long k[kCounterKinds]) {
     std::fill(k, k + kCounterKinds, 0ull);
-    const unsigned long long *src = c->batch_stats ? c->d_bcount : c->counters;
+    const unsigned long long *src = c->batch_stats ? c->d_bcount : c->counted ? c->counters : nullptr;
     if (!src) return AMH_OK;
     std::vector<unsigned long long> h(kCounterKinds * kCounterSlots);
     HIPCHK(c, hipMemcpyAsync(h.data(), src, h.size() * 8, hipMemcpyDeviceToHost, c->stream));

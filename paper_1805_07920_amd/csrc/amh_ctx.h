@@ -62,6 +62,7 @@ struct amh_ctx {
     size_t state_cap = 0;
     bool have_state = false;
     unsigned long long *counters = nullptr;
+    bool counted = false;  // they were cleared: a reference was selected
     // timing
     std::vector<hipEvent_t> ev;  // pairs: [2i] start, [2i+1] stop
     int n_timed = 0;

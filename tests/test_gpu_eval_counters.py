@@ -85,3 +85,13 @@ def test_ablation_build_scores_what_it_counts(amh):  # noqa: F811
         ctx.run_checkerboard(0, [1, 2, 3], 1)
         st = ctx.get_stats()
         assert ctx.get_scored_evals() == st["evals_propagation"] + st["evals_refine"] > 0
+
+
+def test_zero_before_the_first_reference(amh):  # noqa: F811
+    say("case counters of a new context")
+    with make_ctx(amh, scene(131, 77, 3), refine=1, seed=4) as ctx:
+        ctx.run_checkerboard(0, [1, 2, 3], 1)  # leaves counts in memory that a new context may get
+    with make_ctx(amh, scene(131, 77, 3)) as ctx:
+        st = ctx.get_stats()
+        assert all(st[k] == 0 for k in st if k.startswith("evals") or k == "fallback_pixels")
+        assert ctx.get_scored_evals() == 0
