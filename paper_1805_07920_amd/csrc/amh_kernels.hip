@@ -34,6 +34,11 @@
 #define AMH_INIT_WAVES_PER_EU 3
 #endif
 
+// Every operation of this file is rounded as written, a product fused with a sum only where fma says so: the kernels that
+// score the same hypothesis (tile shapes, batched and persistent launches, initialisations, fixed costs) must agree bit for
+// bit, and a contraction the compiler may or may not make, or make of either product, would leave that to chance.
+#pragma clang fp contract(off)
+
 namespace amh {
 
 // ---------------------------------------------------------------------------
@@ -252,9 +257,6 @@ constexpr int kWinStride = 50;  // float2 units: 36 + 6 float4 + 2 of padding
 // 36 samples, sink.row(r, constants) for the 6 rows.
 template <typename Reader, typename Sink>
 __device__ __forceinline__ WinStats build_window_to(const Reader &rd, const MethodDev &m, Sink &sink) {
-    // every operation rounded as written: the kernels that build a pixel's block must agree bit for bit, and
-    // a contraction the compiler may or may not make in each of them would break that
-#pragma clang fp contract(off)
     float a[36];
     const float ac = rd(0, 0);
     float sw = 0.f, swa = 0.f;
@@ -369,9 +371,6 @@ __device__ __forceinline__ void window_moments(const void *__restrict__ quads, c
                                                float N0x, float N0y, float Z0, float pux, float puy, float puz,
                                                float pvx, float pvy, float pvz, int xlo, int xhi, int ylo, int yhi,
                                                int row_bytes, int base, float &m2, float &cab) {
-    // every operation rounded as written (see build_window_to); the products with the unrounded row mean
-    // are explicit fused multiply-adds
-#pragma clang fp contract(off)
     // Source moments row by row: the 6 samples of a window row are held, their weighted mean,
     // centred square sum and cross sum with the reference formed exactly (two passes over the
     // row), and the rows merged with the parallel-variance update (Chan, Golub, LeVeque):
@@ -445,9 +444,9 @@ struct SrcWarp {
 template <int HALF>
 __device__ __forceinline__ bool src_warp(const ViewDev &vw, int x, int y, double q0, float qu, float qv,
                                          SrcWarp &w) {
-    const double P0x = fma(vw.A[1], (double)y, fma(vw.A[0], (double)x, vw.A[2])) + vw.b[0] * q0;
-    const double P0y = fma(vw.A[4], (double)y, fma(vw.A[3], (double)x, vw.A[5])) + vw.b[1] * q0;
-    const double P0z = fma(vw.A[7], (double)y, fma(vw.A[6], (double)x, vw.A[8])) + vw.b[2] * q0;
+    const double P0x = fma(vw.b[0], q0, fma(vw.A[1], (double)y, fma(vw.A[0], (double)x, vw.A[2])));
+    const double P0y = fma(vw.b[1], q0, fma(vw.A[4], (double)y, fma(vw.A[3], (double)x, vw.A[5])));
+    const double P0z = fma(vw.b[2], q0, fma(vw.A[7], (double)y, fma(vw.A[6], (double)x, vw.A[8])));
     if (!(P0z > 0.0)) return false;
     const int W = vw.W, H = vw.H;
     // centre inside the source: 0 <= P0x / P0z <= W - 1 with P0z > 0, tested without a division
@@ -458,19 +457,20 @@ __device__ __forceinline__ bool src_warp(const ViewDev &vw, int x, int y, double
     // float estimate serves; it lies in [-1, W - 1] x [-1, H - 1] (the estimate is a few 1e-3 px off at most)
     const float rzf = __builtin_amdgcn_rcpf((float)P0z);
     const int ix = (int)floorf((float)P0x * rzf), iy = (int)floorf((float)P0y * rzf);
-    w.N0x = (float)(P0x - (double)ix * P0z);
-    w.N0y = (float)(P0y - (double)iy * P0z);
+    w.N0x = (float)fma(-(double)ix, P0z, P0x);
+    w.N0y = (float)fma(-(double)iy, P0z, P0y);
     w.Z0 = (float)P0z;
-    w.puz = (float)vw.A[6] + (float)vw.b[2] * qu;
-    w.pvz = (float)vw.A[7] + (float)vw.b[2] * qv;
-    w.pux = (float)vw.A[0] + (float)vw.b[0] * qu - (float)ix * w.puz;
-    w.puy = (float)vw.A[3] + (float)vw.b[1] * qu - (float)iy * w.puz;
-    w.pvx = (float)vw.A[1] + (float)vw.b[0] * qv - (float)ix * w.pvz;
-    w.pvy = (float)vw.A[4] + (float)vw.b[1] * qv - (float)iy * w.pvz;
+    w.puz = fmaf((float)vw.b[2], qu, (float)vw.A[6]);
+    w.pvz = fmaf((float)vw.b[2], qv, (float)vw.A[7]);
+    w.pux = fmaf(-(float)ix, w.puz, fmaf((float)vw.b[0], qu, (float)vw.A[0]));
+    w.puy = fmaf(-(float)iy, w.puz, fmaf((float)vw.b[1], qu, (float)vw.A[3]));
+    w.pvx = fmaf(-(float)ix, w.pvz, fmaf((float)vw.b[0], qv, (float)vw.A[1]));
+    w.pvy = fmaf(-(float)iy, w.pvz, fmaf((float)vw.b[1], qv, (float)vw.A[4]));
     // every sample must see the plane in front of the source camera: the depth is affine in the
     // window offsets, so the four corners decide
-    const float zc0 = w.Z0 - 5.f * w.puz - 5.f * w.pvz, zc1 = w.Z0 + 5.f * w.puz - 5.f * w.pvz;
-    const float zc2 = w.Z0 - 5.f * w.puz + 5.f * w.pvz, zc3 = w.Z0 + 5.f * w.puz + 5.f * w.pvz;
+    const float zm = fmaf(-5.f, w.puz, w.Z0), zp = fmaf(5.f, w.puz, w.Z0);
+    const float zc0 = fmaf(-5.f, w.pvz, zm), zc1 = fmaf(-5.f, w.pvz, zp);
+    const float zc2 = fmaf(5.f, w.pvz, zm), zc3 = fmaf(5.f, w.pvz, zp);
     if (!(fminf(fminf(zc0, zc1), fminf(zc2, zc3)) > 1e-20f)) return false;
 
     // texel indices relative to (ix, iy), clamped to [-1, W-1] x [-1, H-1] in absolute terms;
@@ -503,7 +503,7 @@ __device__ __forceinline__ float cost_from_moments(const WinStats &ws, float m2,
     const float var_b = m2 * ws.invW;
     const float cov = cab * ws.invW;
     if (ws.var_a < 1e-5f || var_b < 1e-5f) return 2.f;
-    const float mm = 1.f - cov * rsqrtf(ws.var_a * var_b);
+    const float mm = fmaf(-cov, rsqrtf(ws.var_a * var_b), 1.f);
     return fminf(fmaxf(mm, 0.f), 2.f);
 }
 
@@ -614,7 +614,6 @@ __device__ __forceinline__ void issue_cols(const void *quads, float vf, const fl
 template <int HALF>
 __device__ __forceinline__ void pair_moments(const void *__restrict__ quads, const PairWin &win,
                                              const float (&uf)[3], const SrcWarp &w, float &m2, float &cab) {
-#pragma clang fp contract(off)
     float mu = 0.f, acum = 0.f;
     m2 = 0.f;
     cab = 0.f;
@@ -673,7 +672,7 @@ struct PlaneQ {
 __device__ __forceinline__ PlaneQ plane_q(const RefDev &ref, const MethodDev &m, float4 pl, int x, int y) {
     const double rx = fma(ref.kinv_a, (double)x, fma(ref.kinv_b, (double)y, ref.kinv_c));
     const double ry = fma(ref.kinv_e, (double)y, ref.kinv_f);
-    const double nr = (double)pl.x * rx + (double)pl.y * ry + (double)pl.z;
+    const double nr = fma((double)pl.x, rx, (double)pl.y * ry) + (double)pl.z;
     const double d = (double)pl.w;
     PlaneQ q;
     const double inv_d = -1.0 / d;  // the one division: q0 = -nr / d is the inverse depth at the pixel
@@ -684,11 +683,12 @@ __device__ __forceinline__ PlaneQ plane_q(const RefDev &ref, const MethodDev &m,
     q.ok = q.q0 >= m.q_lo && q.q0 <= m.q_hi;
     const float invd = (float)inv_d;
     q.qu = (float)(pl.x * ref.kinv_a) * invd;
-    q.qv = (float)(pl.x * ref.kinv_b + pl.y * ref.kinv_e) * invd;
+    q.qv = (float)fma((double)pl.x, ref.kinv_b, pl.y * ref.kinv_e) * invd;
     // every window sample's ray must meet the plane in front of the camera: the inverse depth is
     // affine in the window offsets, so the four corners decide
-    const float qc = (float)q.q0, hu = 5.f * q.qu, hv = 5.f * q.qv;
-    q.ok = q.ok && fminf(fminf(qc - hu - hv, qc + hu - hv), fminf(qc - hu + hv, qc + hu + hv)) > 0.f;
+    const float qc = (float)q.q0, qm = fmaf(-5.f, q.qu, qc), qp = fmaf(5.f, q.qu, qc);
+    q.ok = q.ok && fminf(fminf(fmaf(-5.f, q.qv, qm), fmaf(-5.f, q.qv, qp)),
+                         fminf(fmaf(5.f, q.qv, qm), fmaf(5.f, q.qv, qp))) > 0.f;
     return q;
 }
 
@@ -698,26 +698,28 @@ __device__ __forceinline__ float2 ref_ray(const RefDev &ref, int x, int y) {
                        (float)fma(ref.kinv_e, (double)y, ref.kinv_f));
 }
 
-// plane through the point at `depth` on the ray r with normal n turned to face the camera
-__device__ __forceinline__ float4 plane_from(float2 r, float depth, float nx, float ny, float nz) {
-    float nr = nx * r.x + ny * r.y + nz;
+// plane through the point at `depth` on a ray with normal n turned to face the camera; nr is n's product with the ray
+__device__ __forceinline__ float4 plane_from(float nr, float depth, float nx, float ny, float nz) {
     if (nr > 0.f) {
         nx = -nx; ny = -ny; nz = -nz; nr = -nr;
     }
     return make_float4(nx, ny, nz, -depth * nr);
 }
+__device__ __forceinline__ float4 plane_from(float2 r, float depth, float nx, float ny, float nz) {
+    return plane_from(fmaf(nx, r.x, ny * r.y) + nz, depth, nx, ny, nz);
+}
 
 // uniform direction on the sphere: z = 1 - 2 u1, azimuth 2 pi u2
 __device__ __forceinline__ void normal_from_uniforms(float u1, float u2, float &nx, float &ny, float &nz) {
     const float z = 1.f - 2.f * u1;
-    const float s = sqrtf(fmaxf(0.f, 1.f - z * z));
+    const float s = sqrtf(fmaxf(0.f, fmaf(-z, z, 1.f)));
     float sn, cs;
     sincospif(2.f * u2, &sn, &cs);
     nx = s * cs; ny = s * sn; nz = z;
 }
 
 __device__ __forceinline__ float plane_depth(float2 r, float4 pl) {
-    return -pl.w / (pl.x * r.x + pl.y * r.y + pl.z);
+    return -pl.w / (fmaf(pl.x, r.x, pl.y * r.y) + pl.z);
 }
 
 // ---------------------------------------------------------------------------
@@ -923,7 +925,7 @@ __device__ __forceinline__ void init_pair_body(const PassArgs &a, long long blk,
             fell_back = a.prop != nullptr;
             float u[4], nx, ny, nz;
             philox((uint64_t)y * a.ref.W + x, 0, 0, a.m.seed, u);
-            const float depth = a.m.d_min + u[0] * (a.m.d_max - a.m.d_min);
+            const float depth = fmaf(u[0], a.m.d_max - a.m.d_min, a.m.d_min);
             normal_from_uniforms(u[1], u[2], nx, ny, nz);
             pl = plane_from(r, depth, nx, ny, nz);
         }
@@ -1366,15 +1368,15 @@ __device__ __forceinline__ void ablation_body(const PassArgs &a, int L, unsigned
             float dnew, qx, qy, qz;
             if (!rnd) {
                 const float rho = ldexpf(1.f, -(a.t + 2));
-                dnew = dcur + (2.f * u[0] - 1.f) * rho * (m.d_max - m.d_min);
+                dnew = fmaf((2.f * u[0] - 1.f) * rho, m.d_max - m.d_min, dcur);
                 dnew = fminf(fmaxf(dnew, m.d_min), m.d_max);
-                qx = best.x + 2.f * rho * (2.f * u[1] - 1.f);
-                qy = best.y + 2.f * rho * (2.f * u[2] - 1.f);
-                qz = best.z + 2.f * rho * (2.f * u[3] - 1.f);
-                const float inv = 1.f / sqrtf(qx * qx + qy * qy + qz * qz);
+                qx = fmaf(2.f * rho, 2.f * u[1] - 1.f, best.x);
+                qy = fmaf(2.f * rho, 2.f * u[2] - 1.f, best.y);
+                qz = fmaf(2.f * rho, 2.f * u[3] - 1.f, best.z);
+                const float inv = 1.f / sqrtf(fmaf(qz, qz, fmaf(qx, qx, qy * qy)));
                 qx *= inv; qy *= inv; qz *= inv;
             } else {
-                dnew = m.d_min + u[0] * (m.d_max - m.d_min);
+                dnew = fmaf(u[0], m.d_max - m.d_min, m.d_min);
                 normal_from_uniforms(u[1], u[2], qx, qy, qz);
             }
             S.cand[(wave * kGroups + g) * 6 + row] =
@@ -1520,8 +1522,7 @@ struct QLds {
 };
 
 struct HalfLds {
-    float *tile;          // [ROWS + 10][kPassTileW] reference intensities; then the rows' aggregated costs, and in
-                          // row 0's place the kept hypothesis's
+    float *tile;          // [ROWS + 10][kPassTileW] reference intensities; then the rows' aggregated costs
     float2 *rw;           // [pixel][kWinStride] window blocks
     gf4 *pl;              // [pixel][8] the rows' planes; then [pixel][7] of QLds, cand's inverse-depth terms
     QLds *q;              // [pixel][8] their inverse-depth terms; then cand
@@ -1539,7 +1540,7 @@ struct HalfLds {
     float *wsum;          // [pixel] their sum
     int *count;           // [ROWS] distinct hypotheses of each row; [2][ROWS] its pairs in the stage, scored and counted
     unsigned *nshort;     // [ROWS] evaluations that took no samples
-    unsigned char *own;   // [pixel] the row that holds the pixel's own plane, or kNoRow; then the kept slot of cand
+    unsigned char *own;   // [pixel] the row that holds the pixel's own plane, or kNoRow
     gf4 *u;               // [2][pixel] the refinement's draws: perturbation, random (t >= 3)
 };
 
@@ -1674,7 +1675,6 @@ __device__ __forceinline__ float pixel_min(float v) {
 // work on every lane, as build_window does it, is 830 vector instructions; this is ~400.)
 template <typename Reader>
 __device__ __forceinline__ WinStats build_window8(const Reader &rd, const MethodDev &m, float2 *rw, int r) {
-#pragma clang fp contract(off)
     gf4 *rw4 = reinterpret_cast<gf4 *>(rw);
     const float ac = rd(0, 0);
     float e[5], as[5];
@@ -1758,8 +1758,7 @@ __device__ __forceinline__ WinStats build_window8(const Reader &rd, const Method
 __device__ __forceinline__ QLds q_lds(const PlaneQ &q) { return QLds{q.ok ? q.q0 : -1.0, q.qu, q.qv}; }
 
 // tid: threadIdx.x.  Registers: the float32 build has 128 for 4 waves on a SIMD and needs all of them in the evaluation;
-// nothing that the pixel's own lanes hold between the stages stays in one meanwhile (thread_again, the row, the kept cost
-// and slot in LDS), and nothing is spilled.
+// what the pixel's own lanes need in a stage of its row and lane is derived anew there, and nothing is spilled.
 template <int HALF, int ROWS>
 __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned char *smem, int tid) {
     constexpr int WAVES = tile_waves(ROWS);
@@ -1881,7 +1880,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
         return q_lds(plane_q(a.ref, m, load_plane(a.st.planes, (size_t)hy * W + hx), hx, hy));
     };
     {
-        int lane = thread_again(wave) & 63, slot = 0, hp = 0;
+        int lane = tid & 63, slot = 0, hp = 0;
         bool live = false;
         QLds q = {-1.0, 0.f, 0.f};
         WinStats ws = {1.f, 0.f};
@@ -1923,6 +1922,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
     const uint32_t div_rest = n_rest ? ((1u << 18) + n_rest - 1) / n_rest : 0u;  // exact: i n_rest < 2^18
     const int ncand = a.t >= 3 ? 6 : 3;
     int n_scored = n_hyp * N;  // evaluations computed by the workgroup
+    float bcost = 0.f;  // cost of the kept hypothesis
+    int bcand = 6;      // its slot in cand
     for (int stage = 0; stage < 4; ++stage) {
         // the lane's place, derived anew in every stage: what follows from it (the random draws among it) is not computed
         // ahead of the loop and held in scratch
@@ -2186,7 +2187,6 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             //     lower wins
             const uint32_t act = S.act[pi];
             float4 best = make_float4(0.f, 0.f, -1.f, 1.f);
-            float bc = 0.f;  // its cost
             if (pix_ok) {
                 float own = __builtin_inff();
                 if (m.include_self) {
@@ -2208,7 +2208,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                     }
                 }
                 int br = m.include_self ? 8 : -1;
-                bc = own;
+                float bc = own;
                 for (int r = 0; r < 8; ++r) {
                     if (S.rep[pi * 8 + r] == kNoRow) continue;
                     const float c = S.tile[pi * 8 + r];
@@ -2217,12 +2217,12 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                         bc = c;
                     }
                 }
+                bcost = bc;
                 // no valid row at all (1-pixel image, no self): the own plane
                 best = to_float4(br < 0 || br == 8 ? S.cand[pi * 7 + 6] : S.pl[pi * 8 + br]);
             }
-            wave_sync();  // every lane holds best: the pixel's lanes write over the planes and costs it was found by
+            wave_sync();  // every lane holds best: the pixel's lanes write over the planes it was read from
             if (pix_ok) {
-                if (row == 0) S.tile[pi * 8] = bc;
                 if (!m.refine) {
                     if (row == 0) S.cand[pi * 7 + 6] = to_gf4(best);
                 } else if (row < ncand) {
@@ -2238,19 +2238,21 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                     float dnew, qx, qy, qz;
                     if (!rnd) {
                         const float rho = ldexpf(1.f, -(a.t + 2));
-                        dnew = dcur + (2.f * u.x - 1.f) * rho * (m.d_max - m.d_min);
+                        dnew = fmaf((2.f * u.x - 1.f) * rho, m.d_max - m.d_min, dcur);
                         dnew = fminf(fmaxf(dnew, m.d_min), m.d_max);
-                        qx = best.x + 2.f * rho * (2.f * u.y - 1.f);
-                        qy = best.y + 2.f * rho * (2.f * u.z - 1.f);
-                        qz = best.z + 2.f * rho * (2.f * u.w - 1.f);
-                        const float inv = 1.f / sqrtf(qx * qx + qy * qy + qz * qz);
+                        qx = fmaf(2.f * rho, 2.f * u.y - 1.f, best.x);
+                        qy = fmaf(2.f * rho, 2.f * u.z - 1.f, best.y);
+                        qz = fmaf(2.f * rho, 2.f * u.w - 1.f, best.z);
+                        const float inv = 1.f / sqrtf(fmaf(qz, qz, fmaf(qx, qx, qy * qy)));
                         qx *= inv; qy *= inv; qz *= inv;
                     } else {
-                        dnew = m.d_min + u.x * (m.d_max - m.d_min);
+                        dnew = fmaf(u.x, m.d_max - m.d_min, m.d_min);
                         normal_from_uniforms(u.y, u.z, qx, qy, qz);
                     }
+                    // (a new normal's product with the ray is fused in y: the bits that the results have always had)
                     const float4 cp = kind == 0 ? plane_from(rr, dnew, best.x, best.y, best.z)
-                                                : plane_from(rr, kind == 1 ? dcur : dnew, qx, qy, qz);
+                                                : plane_from(fmaf(qy, rr.y, qx * rr.x) + qz, kind == 1 ? dcur : dnew, qx,
+                                                             qy, qz);
                     S.cand[pi * 7 + row] = to_gf4(cp);
                     // the pixel's rows are read no more (best is in registers): their place takes the terms
                     reinterpret_cast<QLds *>(S.pl + pi * 8)[row] = q_lds(plane_q(a.ref, m, cp, x, y));
@@ -2275,7 +2277,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                 const int j0 = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
                 const float r0 = S.ms[(pi * 6 + row) * N + __popc(act & ((1u << j0) - 1u))];
                 others = act & ~(1u << j0);
-                if (!(weighted_cost(r0) / S.wsum[pi] < S.tile[pi * 8])) {
+                if (!(weighted_cost(r0) / S.wsum[pi] < bcost)) {
                     // out; its other evaluations are short too where its plane is out of range
                     if (r0 < 0.f)
                         atomicAdd(&S.nshort[wave],
@@ -2295,9 +2297,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             pre -= __popc(others);
             for (uint32_t rest = others; rest; rest &= rest - 1u)
                 list3[pre++] = (unsigned short)(pi | (__builtin_ctz(rest) << kPairView) | (row << kPairCand));
-        } else if (stage == 3 && pix_ok && row == 0) {
-            float bcost = S.tile[pi * 8];
-            int bcand = 6;  // the kept hypothesis's slot in cand
+        } else if (stage == 3 && pix_ok) {
             const uint32_t act = S.act[pi];
             const int nw = __popc(act);
             const float wsum = S.wsum[pi];
@@ -2317,9 +2317,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                     bcand = c;
                 }
             }
-            if (ns) atomicAdd(&S.nshort[wave], ns);
-            S.tile[pi * 8] = bcost;
-            S.own[pi] = (unsigned char)bcand;
+            if (ns && row == 0) atomicAdd(&S.nshort[wave], ns);
         }
         __syncthreads();
     }
@@ -2330,8 +2328,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
         const int pi = tid_e >> 3, x = col_of(pi), y = y0 + wave;
         if (y < Hh && x < W) {
             const size_t p = (size_t)y * W + x;
-            store_plane(a.st.planes, p, to_float4(S.cand[pi * 7 + (m.refine ? S.own[pi] : 6)]));
-            glob(a.st.cost)[p] = S.tile[pi * 8];
+            store_plane(a.st.planes, p, to_float4(S.cand[pi * 7 + bcand]));
+            glob(a.st.cost)[p] = bcost;
             glob(a.st.S)[p] = S.sel[pi];
             glob(a.st.v)[p] = S.vt[pi];
         }
@@ -2691,7 +2689,7 @@ __global__ __launch_bounds__(64) void sweep_kernel(SweepArgs a) {
     const int D = kSweepCoarse * a.sub;  // a multiple of 4
     if (cell_ok) {
         for (int i = k; i < D; i += 4) {
-            const float qi = a.q_far + ((float)i + 0.5f) * a.q_step;
+            const float qi = fmaf((float)i + 0.5f, a.q_step, a.q_far);
             const PlaneQ q = plane_q(a.ref, a.m, make_float4(0.f, 0.f, -1.f, 1.f / qi), x, y);
             float m1 = inf, m2 = inf;  // two lowest costs over the sources
             for (int j = 0; j < n; ++j) {
@@ -2744,7 +2742,7 @@ __global__ __launch_bounds__(64) void sweep_kernel(SweepArgs a) {
         out[1] = f2bf(__builtin_sqrtf(var * (1.f / (kCell * kCell))) * (1.f / 32.f));
         out[2] = f2bf(2.f * ((float)best_i + 0.5f) / (float)D - 1.f);
         out[3] = f2bf(1.f - best);
-        if (a.q_ref) a.q_ref[cell] = a.q_far + ((float)best_i + 0.5f) * a.q_step;
+        if (a.q_ref) a.q_ref[cell] = fmaf((float)best_i + 0.5f, a.q_step, a.q_far);
     } else {
         // lanes 1..3 write 4 coarse channels each
 #pragma unroll
@@ -2806,7 +2804,7 @@ __global__ void outputs_kernel(RefDev ref, StateDev st, float *depth, float *nor
     if (depth) {
         const double rx = fma(ref.kinv_a, (double)x, fma(ref.kinv_b, (double)y, ref.kinv_c));
         const double ry = fma(ref.kinv_e, (double)y, ref.kinv_f);
-        depth[p] = (float)(-(double)pl.w / ((double)pl.x * rx + (double)pl.y * ry + (double)pl.z));
+        depth[p] = (float)(-(double)pl.w / (fma((double)pl.x, rx, (double)pl.y * ry) + (double)pl.z));
     }
     if (normal) {
         normal[3 * p] = pl.x;
