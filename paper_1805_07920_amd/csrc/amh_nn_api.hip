@@ -370,7 +370,7 @@ amh_status nn_forward_stream(amh_ctx *c, const void *feats, const float *q_ref, 
     const auto layer = [&](int li, const bf16_t *x, const bf16_t *low, bf16_t *y, bf16_t *pool, int hh, int ww) {
         Conv3Args a = fwd_args(N, li, x, low, y, n, hh, ww);
         a.pool = pool;
-        if (li == ENC0A) a.xcopy = N->x;
+        if (li == ENC0A && x != N->x) a.xcopy = N->x;
         if (li == DEC0) {
             a.head_w = N->pb + N->L[HEAD].w_off;
             a.head_b = N->p32 + N->L[HEAD].b_off;
@@ -469,7 +469,20 @@ amh_status amh_nn_forward(amh_ctx *c, const void *feats, const float *q_ref, int
     amh_status st = check_net(c);
     if (st != AMH_OK) return st;
     if ((st = nn_reserve(c, (size_t)n * h * w)) != AMH_OK) return st;
-    c->net->have_fwd = false;  // the launches write over the pass kept so far
+    NetState *N = c->net;
+    N->have_fwd = false;  // the launches write over the pass kept so far
+    // The last layer reads q_ref while it writes out, cell by cell in no order: an out over q_ref takes the kept copy.  The
+    // first layer reads feats 16 bytes at a time: the kept copy again where they don't lie so.
+    const size_t cells = (size_t)n * h * w;
+    const uintptr_t q0 = (uintptr_t)q_ref, o0 = (uintptr_t)out;
+    if (out && q0 < o0 + cells * 5 * sizeof(float) && o0 < q0 + cells * sizeof(float)) {
+        HIPCHK(c, hipMemcpyAsync(N->qref, q_ref, cells * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+        q_ref = N->qref;
+    }
+    if ((uintptr_t)feats & 15) {
+        HIPCHK(c, hipMemcpyAsync(N->x, feats, cells * kIn * sizeof(bf16_t), hipMemcpyDeviceToDevice, c->stream));
+        feats = N->x;
+    }
     if ((st = nn_forward_stream(c, feats, q_ref, n, h, w, out, c->stream)) != AMH_OK) return st;
     nn_kept(c, n, h, w);
     return AMH_OK;
