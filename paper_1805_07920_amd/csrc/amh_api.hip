@@ -211,11 +211,15 @@ void free_job(JobResult &j) {
 // tile rows of the half-pass under the launch configuration: its alternative shape, or the default by view count
 int half_rows(const amh_ctx *c, int n_src) { return c->cfg_rows == 2 ? 2 : pass_tile_rows(n_src); }
 
-// Tile order of a reference by itself, unless configured: XCD bands keep an XCD's tiles together in its L2, but work in 8
-// places of every source at once, which the 256 MB last-level cache holds only while it holds the sources; in hardware
-// order the card moves through them together.  Bands / hardware order, ms: 197 MB (10 x 1920x1280) 20.91 / 20.83, 154 MB
-// (20 x 1600x1200 float16) 32.74 / 32.84; 275 MB (14 x 1920x1280) 28.73 / 28.18, 393 MB 37.71 / 36.72, 545 MB (20 x
-// 3200x2130 float16) 93.53 / 89.97, 1091 MB 84.20 / 83.98.
+// Tile order of a reference by itself, unless configured.  XCD bands keep an XCD's tiles together in its L2, but work in 8
+// places of every source at once; in hardware order the card moves through the sources together, and the L2s fetch more
+// (1920x1280 x 10: 0.78 GB a half-pass in bands, 4.3 GB in hardware order; 3200x2130 x 20 float16: 13.1 and 50.2 GB).
+// Hardware order is faster all the same where the sources exceed the 256 MB last-level cache, presumably because it serves
+// those fetches (the counters don't tell it from memory).  Bands / hardware order, ms: 20 MB (640x480 x 8) 2.30 / 2.31,
+// 154 MB (1600x1200 x 20 float16) 32.76 / 32.99, 197 MB (1920x1280 x 10) 20.85 / 20.76; 273 MB (3200x2130 x 10 float16)
+// 52.93 / 51.67, 275 MB (1920x1280 x 14) 28.71 / 28.19, 348 MB (2560x1700 x 10) 29.69 / 29.44, 393 MB (1920x1280 x 20)
+// 37.75 / 36.78, 436 MB (3200x2130 x 8) 41.91 / 41.00, 545 MB (3200x2130 x 20 float16) 93.62 / 90.28, 1091 MB (the same in
+// float32) 84.64 / 83.87: 0.8 to 3.7 % above the line, within 0.7 % either way below it.
 int tile_order(const amh_ctx *c) {
     if (c->cfg_order >= 0) return c->cfg_order;
     size_t bytes = 0;

@@ -28,8 +28,9 @@ constexpr int kDefaultTileRows = 4;
 constexpr int tile_waves(int rows) { return rows == 2 ? 2 : 4; }
 // A reference with at most this many 4-row tiles of a colour takes one-row tiles: fewer workgroups than the card's 256
 // CUs leave most of them idle, and a pass lasts as long as one workgroup's chain of evaluations, which four waves on
-// one row shorten (128x96, 4 sources, 192 tiles: 219 -> 174 us for 3 iterations; 200x150, 6 sources, 494 tiles: 404
-// us, one-row tiles 509).
+// one row shorten.  3 iterations with refinement, 4-row (14 sources: 3-row) and one-row tiles, us, for 4, 8 and 14
+// sources: 192 tiles (128x96) 313 / 256, 405 / 321, 489 / 413; 256 tiles (128x128) 324 / 274, 409 / 338, 566 / 453; 300
+// tiles (160x120) 348 / 376, 463 / 455, 557 / 587; 494 tiles (200x150) 350 / 432, 465 / 549, 646 / 715.
 constexpr int kSmallTiles = 256;
 
 // One source view relative to the current reference (Sec. 3.3: plane-induced warp).

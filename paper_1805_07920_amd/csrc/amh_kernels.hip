@@ -246,7 +246,7 @@ struct WinStats {
 // constants (1 / W_r, W_r / W_<=r, W_<r W_r / W_<=r, A_r) with W_r the row's
 // weight sum and A_r its sum of w (a - mean); they let the source moments be
 // formed row by row and merged exactly (see ncc_cost).
-// The blocks are 100 dwords apart (4 of them padding): the 7 pixels of a half-pass wave, or the 16 cells of a sweep
+// The blocks are 100 dwords apart (4 of them padding): the pixels of a half-pass wave, or the 16 cells of a sweep
 // wave, read the same entry of their blocks in one 16-byte access, and 100 mod 64 = 36 puts 16 consecutive blocks on
 // disjoint groups of 4 of the 64 LDS banks.  At 96 dwords they met on two groups: the sweep spent 98 % of its cycles
 // in LDS, 86 % of them conflicts (1920x1280, 4 sources: 2.95 -> 2.1 ms), the half-pass 65 %, two thirds of them
@@ -1506,9 +1506,9 @@ __device__ __forceinline__ void ablation_body(const PassArgs &a, int L, unsigned
 // 0.4 % of the short ones).  What was scored is counted by itself.
 // ---------------------------------------------------------------------------
 constexpr int kFullChunk = 53;
-// Up to this many views the own planes are listed with the propagated ones: at most k = 4 views carry weight, so with
-// 4 nearly every view does and scoring them later would only add a stage (8 views: the same time either way; 10 views:
-// later is 1.5 % faster).
+// Up to this many views the own planes are listed with the propagated ones.  k views of S_t carry weight (4 by default),
+// and those of S_{t-1} that left it, or all views where there is none: with 4 nearly every view does, and scoring them later
+// would only add a stage (8 views: the same time either way; 10 views: later is 1.5 % faster).
 constexpr int kOwnFirst = 4;
 constexpr int kPassTileW = 2 * kPix + 10;
 constexpr int kNoRow = 0xff;

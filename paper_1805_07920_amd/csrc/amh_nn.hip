@@ -740,8 +740,9 @@ static hipError_t run_conv3(Conv3Args a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Tile shapes: two rows per wave (8-row tiles) where an image has enough tiles for that, one row, or waves split over
-// the output channels, on the quarter- and eighth-resolution levels, whose few pixels would leave CUs idle.
+// Tile shapes, by layer (each layer works at one resolution), as measured at 320 x 480 cells: two rows per wave (8-row
+// tiles) on the upper levels; on the quarter- and eighth-resolution levels, whose few pixels would leave CUs idle there, one
+// row per wave or waves split over the output channels.  The image's size doesn't enter.
 hipError_t launch_conv3(int cin, int cout, const Conv3Args &a, hipStream_t s) {
     if (a.head_w) return cin == 48 && cout == 16 && a.low ? run_conv3<48, 16, 32, 1, 2, false, true>(a, s) : hipErrorInvalidValue;
     if (a.low) {
@@ -788,7 +789,7 @@ hipError_t launch_wgrad(const WgradArgs &a, int splits, hipStream_t s) {
         NN_LAUNCH((wgrad_kernel<1, 1, 1024>), grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
-    switch (a.cout_pad / 16) {  // blocks as large as 64 KB of LDS allow
+    switch (a.cout_pad / 16) {  // 33, 50, 33 and 41 KB of LDS (67 KB for the 1x1 head above)
         case 1: NN_LAUNCH((wgrad_kernel<1, 3, 512>), grid, dim3(256), 0, s, a); break;
         case 2: NN_LAUNCH((wgrad_kernel<2, 3, 512>), grid, dim3(256), 0, s, a); break;
         case 3: NN_LAUNCH((wgrad_kernel<3, 3, 256>), grid, dim3(256), 0, s, a); break;
