@@ -8,7 +8,7 @@ random init, 6 half-passes and the depth/normal/cost output, with the images
 already resident in HBM.
 
 Prints ONE JSON line: hypothesis x view NCC evaluations per second (every
-evaluation the library performs, init and refinement included), seconds per
+evaluation of the method, init and refinement included), seconds per
 depth map, the pass kernel's position against the vector-ALU roofline and the
 CPU oracle timed on a bounded sample of the same workload.
 
@@ -41,14 +41,16 @@ VALU_PEAK_OPS = 256 * 128 * 2.4e9
 # (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch, mean of the 6 half-passes of one depth map) scaled by
 # what the same counters read for a plain 256 MiB copy (bench.py --calibrate-copy: FETCH_SIZE 131080 KiB
 # for 262144 KiB read -> x2.0, WRITE_SIZE 262144 KiB for 262144 KiB written -> x1.0); summary in
-# profiles/pass_kernel_1920x1280_n10_traffic.md and pass_kernel_3200x2130_n20_fp16_traffic.md.  Per workload
-# and tile shape (rows per workgroup) of the variant the autotuner picks, and valid only for the kernel source
-# they were taken on.
-PASS_TRAFFIC = {"by_workload": {"1920x1280_n10": {2: {"fetch_kib": 537769.0, "write_kib": 195080.0},
-                                                  4: {"fetch_kib": 455355.0, "write_kib": 192316.0}},
-                                "3200x2130_n20": {3: {"fetch_kib": 6449170.0, "write_kib": 228562.0}}},
+# profiles/pass_kernel_1920x1280_n10_traffic.md and pass_kernel_3200x2130_n20_fp16_traffic.md.  Per workload,
+# tile rows and tile order (0 XCD bands, 1 hardware order), and valid only for the kernel source they were taken on.
+PASS_TRAFFIC = {"by_workload": {"1920x1280_n10": {(4, 0): {"fetch_kib": 379068.0, "write_kib": 74663.7},
+                                                  (4, 1): {"fetch_kib": 2112540.0, "write_kib": 71299.2},
+                                                  (2, 0): {"fetch_kib": 450554.0, "write_kib": 79730.2},
+                                                  (2, 1): {"fetch_kib": 2094850.0, "write_kib": 75318.9}},
+                                "3200x2130_n20": {(3, 0): {"fetch_kib": 6408310.0, "write_kib": 220478.0},
+                                                  (3, 1): {"fetch_kib": 24498800.0, "write_kib": 202351.0}}},
                 "fetch_scale": 2.0, "write_scale": 1.0,
-                "kernel_sha256": "6914b9a82bbedcfd55eaf995fd280692f040d43cb832af5bab28af94d455e742"}
+                "kernel_sha256": "cbac54ce6a06c422369a22d2a971104762726ccc6c8c349315a8286299fccdb4"}
 
 
 # The same two counters for the fusion kernel of one reference view (11 views of 1920x1280, mean over the
@@ -69,8 +71,8 @@ def fuse_traffic_bytes():
                      + FUSE_TRAFFIC["write_kib"] * FUSE_TRAFFIC["write_scale"])
 
 
-def pass_traffic_bytes(workload: str, tile_rows: int):
-    """HBM-side bytes per half-pass launch on `workload` of the variant with `tile_rows` rows per workgroup,
+def pass_traffic_bytes(workload: str, tile_rows: int, order: int):
+    """HBM-side bytes per half-pass launch on `workload` with `tile_rows` rows per workgroup in tile order `order`,
     or None when not measured for it or once the kernel source has changed since the counters."""
     import hashlib
 
@@ -78,7 +80,7 @@ def pass_traffic_bytes(workload: str, tile_rows: int):
     with open(src, "rb") as f:
         if hashlib.sha256(f.read()).hexdigest() != PASS_TRAFFIC["kernel_sha256"]:
             return None
-    c = PASS_TRAFFIC["by_workload"].get(workload, {}).get(tile_rows)
+    c = PASS_TRAFFIC["by_workload"].get(workload, {}).get((tile_rows, order))
     if c is None:
         return None
     return 1024.0 * (c["fetch_kib"] * PASS_TRAFFIC["fetch_scale"] + c["write_kib"] * PASS_TRAFFIC["write_scale"])
@@ -749,11 +751,14 @@ def main():
     # dominant kernel: the fused half-pass
     n_pass = max(1, ev["n_passes"])
     evals_per_pass = (ev["evals_propagation"] + ev["evals_refine"]) / n_pass
-    # evaluations whose cost 2 was decided before any sample (out of range, outside the source) do a few
-    # dozen operations, not OPS_PER_EVAL: the roofline credits only the evaluations that took their samples
-    sampled_per_pass = (ev["evals_propagation"] + ev["evals_refine"] - ev["evals_short"]) / n_pass
+    # the roofline credits what the kernel executed: evaluations that regions share count once, those that nothing reads
+    # not at all, and those whose cost 2 was decided before any sample (a few dozen operations, not OPS_PER_EVAL) are
+    # taken off as often as the method has them, so that it is a lower bound
+    scored_per_pass = ctx.get_scored_evals() / n_pass
+    sampled_per_pass = max(0.0, scored_per_pass - ev["evals_short"] / n_pass)
     avg_pass_ms = float(np.mean(pass_ms))
     achieved = sampled_per_pass * OPS_PER_EVAL / (avg_pass_ms / 1000.0)
+    shape = ctx.get_pass_shape()  # of the launches: tile rows and order
     rel = np.abs(depth.cpu().numpy() - sc.depth_gt) / sc.depth_gt
     vis = sc.vis_count >= 2
     acc = float((rel[vis] < 0.01).mean())
@@ -773,8 +778,7 @@ def main():
         state = O.init(O.Views.from_scene(sc), O.Params(**params_kw))
         cpu = cpu_baseline(sc, params_kw, (state.plane, state.cost, state.S, state.v))
 
-    # rows of the launch's tiles: 2 by configuration, else 4, 3 where 4 workgroups of 4 rows exceed a CU's LDS
-    tile_rows = 2 if best_cfg & 4 else 4 if n <= 12 else 3
+    tile_rows, tile_order = shape["rows"], ("XCD bands", "hardware order")[shape["order"]]
     out = {
         "metric": METRIC, "value": value, "unit": "evals/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
@@ -789,10 +793,10 @@ def main():
                    "seed": args.seed, "parallelism": "single GPU"},
         "sec_per_depth_map": ms_per_step / 1000.0,
         "value_basis": "the method's evaluations per second: a plane that several regions of a pixel hold counts for "
-                       "each and the pixel's own plane on every view, as the counters do, though equal ones share one "
-                       "computation and costs that nothing reads are not computed; ms_per_step is the wall clock",
-        # the same rate over the evaluations that took their 36 samples (those decided by the range and
-        # visibility tests alone are counted in value, as the library performs them)
+                       "each, the pixel's own plane on every view and a refinement candidate on every view that carries "
+                       "weight, as the counters do, though equal ones share one computation and costs that nothing reads "
+                       "are not computed; ms_per_step is the wall clock",
+        # the same rate without the evaluations that the range and visibility tests alone decide (counted in value)
         "sampled_evals_per_s": (ev["evals_total"] - ev["evals_short"] - ev["evals_init_short"]) / (ms_per_step / 1000.0),
         "evals_per_depth_map": {k: ev[k] for k in ("evals_total", "evals_init", "evals_propagation", "evals_refine",
                                                    "evals_short", "evals_init_short")},
@@ -804,18 +808,17 @@ def main():
                      "peak_basis": "fp32 lane-operations: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz (157.3 TFLOP/s, "
                                    "FMA = 2 flops); unpacked v_add_f32 reaches 91 %, v_fma_f32 72 % "
                                    "(bench.py --calibrate-valu)",
-                     # counters taken per workload and tile shape, in XCD bands; null for a shape or order not measured
-                     "traffic": None if best_cfg & 1 else pass_traffic_bytes(args.config, tile_rows),
+                     # counters taken per workload, tile shape and order; null for one not measured
+                     "traffic": pass_traffic_bytes(args.config, tile_rows, shape["order"]),
                      "traffic_unit": "bytes per launch (L2 <-> memory, calibrated rocprofv3 FETCH_SIZE + WRITE_SIZE)",
                      "kernel": f"pass_kernel<{1 if store == amh.AMH_F16 else 0}, {tile_rows}> "
-                               f"(fused checkerboard half-pass, {tile_rows}-row tiles)",
+                               f"(fused checkerboard half-pass, {tile_rows}-row tiles, {tile_order})",
                      "ops_per_eval": OPS_PER_EVAL, "evals_per_launch": evals_per_pass,
-                     "sampled_evals_per_launch": sampled_per_pass,
-                     # what the method asks for, not what the kernel executes: evaluations shared between regions
-                     # that hold the same plane, and the own planes' on views without weight, are counted
-                     "achieved_basis": "the method's evaluations of propagated and own planes (shared or unread ones "
-                                       "included) and the scored refinement evaluations, those decided before any "
-                                       "sample left out, x ops_per_eval (algorithmic) / mean launch time"},
+                     "scored_evals_per_launch": scored_per_pass, "sampled_evals_per_launch": sampled_per_pass,
+                     "achieved_basis": "the evaluations that the kernel computed (evals_per_launch are the method's: one "
+                                       "that regions share counts once here, one that nothing reads not at all) less "
+                                       "all that were decided before any sample, a lower bound, x ops_per_eval "
+                                       "(algorithmic) / mean launch time"},
         "speedup_vs_plain": learned["speedup_vs_plain"] if learned else None,
         "equal_accuracy": learned["equal_accuracy"] if learned else None,
         "learned_vs_plain": learned,
