@@ -20,15 +20,17 @@
 // Minimum waves per SIMD the kernels are compiled for (a register budget of
 // 512 / waves VGPRs).  The single-image and batched half-passes are held to 4
 // waves per SIMD (128 VGPRs), which they fit without spilling (112 with float16
-// sources); the ablation build gets the budget of 2 waves and settles at 120
-// VGPRs (float16 sources) and 129 by itself; the initialisation kernels, which
-// hold half a window block per lane, fit 3 waves (at 4 they spill inside the
-// source loop).
+// sources); the ablation build, held to 3, settles at 128 VGPRs (120 with
+// float16 sources) and 4 waves by itself -- held to 2 it took 129 and lost the
+// fourth wave (1920x1280, 10 sources, fast symmetric pattern, 2 iterations:
+// 21.1 against 19.8 ms), held to 4 it spills 8; the initialisation kernels,
+// which hold half a window block per lane, fit 3 waves (at 4 they spill inside
+// the source loop).
 #ifndef AMH_PASS_WAVES_PER_EU
 #define AMH_PASS_WAVES_PER_EU 4
 #endif
-#ifndef AMH_BATCH_WAVES_PER_EU
-#define AMH_BATCH_WAVES_PER_EU 2
+#ifndef AMH_ABLATION_WAVES_PER_EU
+#define AMH_ABLATION_WAVES_PER_EU 3
 #endif
 #ifndef AMH_INIT_WAVES_PER_EU
 #define AMH_INIT_WAVES_PER_EU 3
@@ -2373,7 +2375,7 @@ void pass_kernel(PassArgs a) {
 }
 
 template <int HALF, int ROWS>
-__global__ __launch_bounds__(64 * ROWS) __attribute__((amdgpu_waves_per_eu(AMH_BATCH_WAVES_PER_EU)))
+__global__ __launch_bounds__(64 * ROWS) __attribute__((amdgpu_waves_per_eu(AMH_ABLATION_WAVES_PER_EU)))
 void ablation_kernel(PassArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = tile_of_block(a.n_tiles, a.order);

@@ -1,5 +1,5 @@
-"""Registers of the built half-pass kernels, from the metadata the compiler leaves in the library: 4 waves on a SIMD and
-nothing in scratch memory."""
+"""Registers of the built half-pass kernels, the ablation build's among them, from the metadata the compiler leaves in the
+library: 4 waves on a SIMD and nothing in scratch memory."""
 import os
 import re
 import shutil
@@ -45,7 +45,7 @@ def test_half_pass_kernels_spill_nothing(tmp_path):
             field = lambda k: re.search(rf"\.{k}:\s*(\S+)", part).group(1)
             kernels[field("symbol")] = [int(field(k)) for k in ("private_segment_fixed_size", "vgpr_spill_count",
                                                                 "vgpr_count")]
-    half = {k: v for k, v in kernels.items() if re.search(r"(pass|batch|persist)_kernelILi", k)}
-    assert len(half) == 8 + 6 + 4  # float32 and float16 sources x tile rows 1 .. 4, 2 .. 4, and 2 and 4
+    half = {k: v for k, v in kernels.items() if re.search(r"(pass|batch|persist|ablation)_kernelILi", k)}
+    assert len(half) == 8 + 6 + 4 + 4  # float32 and float16 sources x tile rows 1 .. 4, 2 .. 4, and twice 2 and 4
     for name, (scratch, spilled, vgprs) in sorted(half.items()):
         assert scratch == 0 and spilled == 0 and vgprs <= 128, (name, scratch, spilled, vgprs)
