@@ -318,12 +318,14 @@ __device__ __forceinline__ void order2(float &a, float &b) {
     b = hi;
 }
 
-// A lane takes kMedianRows pixels down a column.  Whole windows without NaN (all but the image's edge): every row of 4
-// values is sorted once (5 exchanges) for the 4 windows it is in, neighbouring rows are merged into sorted eights once
-// (9 exchanges) for the 2 windows that use the pair, and the two middle values of a window are the largest of the 8
-// smaller ones and the smallest of the 8 larger ones of two sorted eights A, B, min / max(A[i], B[7 - i]): 58 minima
-// and maxima per pixel where sorting the 16 values takes 160, 5.5 loads instead of 16.  1920x1280: 35.0 -> 10.1 us
-// (bytes alone 3.9 us at the copy rate).
+// A lane takes kMedianRows pixels down a column.  Every row of 4 values is sorted once (5 exchanges) for the 4 windows it
+// is in, neighbouring rows are merged into sorted eights once (9 exchanges) for the 2 windows that use the pair, and the two
+// middle values of a window are the largest of the 8 smaller ones and the smallest of the 8 larger ones of two sorted eights
+// A, B, min / max(A[i], B[7 - i]): 58 minima and maxima per pixel where sorting the 16 values takes 160, 5.5 loads instead
+// of 16.  1920x1280: 35.0 -> 10.1 us (bytes alone 3.9 us at the copy rate).
+// Where a wave holds NaN, they are +inf to the sorts and counted by row; the middle of a window that has some is among its 8
+// smaller ones, sorted with 12 exchanges more.  (Sorting such windows' 16 values afterwards, a lane's 8 in a row, took up to
+// three times the time of one pixel to a lane.)
 // The pixels at the edges (rows 0, H - 2, H - 1, columns 0, W - 2, W - 1; every pixel of an image less than 4 wide or
 // high) are one to a lane in workgroups of their own, the first n_edge_blocks: as the odd lane of a column they would
 // hold its wave for 8 sorts in a row (24 us at any size).
@@ -335,8 +337,84 @@ __host__ __device__ inline long long median_edge_pixels(int W, int H) {
     return W < 4 || H < 4 ? (long long)W * H : 3ll * W + 3ll * (H - 3);
 }
 
-__global__ __launch_bounds__(256) void median4_kernel(const float *__restrict__ src, float *__restrict__ dst, int W,
-                                                      int H, int n_edge_blocks, int tiles_x) {
+// The windows of a lane's column: rows y0 - 1 .. of values r, pixels (x, y0) ..; NANS: some of the wave's values are NaN.
+template <bool NANS>
+__device__ __forceinline__ void median_column(float (&r)[kMedianRows + 3][4], float *__restrict__ dst, int W, int H, int x,
+                                              int y0, bool mine) {
+    unsigned long long nans = 0;  // of the rows, 4 bits each
+    float e[kMedianRows + 2][8];
+#pragma unroll
+    for (int k = 0; k < kMedianRows + 3; ++k) {
+        float *q = r[k];
+        if (NANS) {
+            unsigned n = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                n += isnan(q[i]);
+                q[i] = isnan(q[i]) ? __builtin_inff() : q[i];
+            }
+            nans |= (unsigned long long)n << (4 * k);
+        }
+        order2(q[0], q[1]);
+        order2(q[2], q[3]);
+        order2(q[0], q[2]);
+        order2(q[1], q[3]);
+        order2(q[1], q[2]);
+        if (k > 0) {
+            // odd-even merge of rows k - 1 and k
+            float *m = e[k - 1];
+            const float *p = r[k - 1];
+            // even places (p0 q0 merged with p2 q2), odd places (p1 q1 with p3 q3), then across
+            float a0 = p[0], a1 = q[0], a2 = p[2], a3 = q[2];
+            order2(a0, a1);
+            order2(a2, a3);
+            order2(a1, a2);
+            float b0 = p[1], b1 = q[1], b2 = p[3], b3 = q[3];
+            order2(b0, b1);
+            order2(b2, b3);
+            order2(b1, b2);
+            order2(b0, a1);
+            order2(b1, a2);
+            order2(b2, a3);
+            m[0] = a0; m[1] = b0; m[2] = a1; m[3] = b1; m[4] = a2; m[5] = b2; m[6] = a3; m[7] = b3;
+        }
+        if (k >= 3) {
+            const int y = y0 + k - 3;  // window rows k - 3 .. k
+            const float *A = e[k - 3], *B = e[k - 1];
+            float lo = fminf(A[0], B[7]), hi = fmaxf(A[0], B[7]);
+#pragma unroll
+            for (int i = 1; i < 8; ++i) {
+                lo = fmaxf(lo, fminf(A[i], B[7 - i]));
+                hi = fminf(hi, fmaxf(A[i], B[7 - i]));
+            }
+            float mid = 0.5f * (lo + hi);
+            const unsigned w = (unsigned)(nans >> (4 * (k - 3))) & 0xffffu;  // NaN of the window's rows
+            if (NANS && w) {
+                float s[8];  // its 8 smaller values, a bitonic sequence
+#pragma unroll
+                for (int i = 0; i < 8; ++i) s[i] = fminf(A[i], B[7 - i]);
+#pragma unroll
+                for (int d = 4; d > 0; d >>= 1)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (!(i & d)) order2(s[i], s[i + d]);
+                const int n = 16 - (int)((w & 15u) + (w >> 4 & 15u) + (w >> 8 & 15u) + (w >> 12)), h = n / 2;
+                float a = 0.f, b = 0.f;  // places h - 1 and h
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (i == h - 1) a = s[i];
+                    if (i == h) b = s[i];
+                }
+                mid = n == 0 ? __builtin_nanf("") : ((n & 1) ? b : 0.5f * (a + b));
+            }
+            if (mine && y >= 1 && y + 2 < H) dst[(size_t)y * W + x] = mid;
+        }
+    }
+}
+
+// (5 waves on a SIMD: 96 VGPRs; 98 by itself)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void median4_kernel(
+    const float *__restrict__ src, float *__restrict__ dst, int W, int H, int n_edge_blocks, int tiles_x) {
     if ((int)blockIdx.x < n_edge_blocks) {
         const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
         if (i >= median_edge_pixels(W, H)) return;
@@ -372,53 +450,12 @@ __global__ __launch_bounds__(256) void median4_kernel(const float *__restrict__ 
         r[k][2] = row[x + 1];
         r[k][3] = row[x + 2];
     }
-    unsigned bad = 0;  // rows that hold a NaN
-    float e[kMedianRows + 2][8];
+    bool nans = false;
 #pragma unroll
-    for (int k = 0; k < kMedianRows + 3; ++k) {
-        float *q = r[k];
-        if (isnan(q[0]) || isnan(q[1]) || isnan(q[2]) || isnan(q[3])) bad |= 1u << k;
-        order2(q[0], q[1]);
-        order2(q[2], q[3]);
-        order2(q[0], q[2]);
-        order2(q[1], q[3]);
-        order2(q[1], q[2]);
-        if (k > 0) {
-            // odd-even merge of rows k - 1 and k
-            float *m = e[k - 1];
-            const float *p = r[k - 1];
-            // even places (p0 q0 merged with p2 q2), odd places (p1 q1 with p3 q3), then across
-            float a0 = p[0], a1 = q[0], a2 = p[2], a3 = q[2];
-            order2(a0, a1);
-            order2(a2, a3);
-            order2(a1, a2);
-            float b0 = p[1], b1 = q[1], b2 = p[3], b3 = q[3];
-            order2(b0, b1);
-            order2(b2, b3);
-            order2(b1, b2);
-            order2(b0, a1);
-            order2(b1, a2);
-            order2(b2, a3);
-            m[0] = a0; m[1] = b0; m[2] = a1; m[3] = b1; m[4] = a2; m[5] = b2; m[6] = a3; m[7] = b3;
-        }
-        if (k >= 3) {
-            const int y = y0 + k - 3;  // window rows k - 3 .. k
-            const float *A = e[k - 3], *B = e[k - 1];
-            float lo = fminf(A[0], B[7]), hi = fmaxf(A[0], B[7]);
-#pragma unroll
-            for (int i = 1; i < 8; ++i) {
-                lo = fmaxf(lo, fminf(A[i], B[7 - i]));
-                hi = fminf(hi, fmaxf(A[i], B[7 - i]));
-            }
-            if (mine && y >= 1 && y + 2 < H) dst[(size_t)y * W + x] = 0.5f * (lo + hi);
-        }
-    }
-    // windows with NaN, sorted after all
-    if (bad && mine)
-        for (int k = 0; k < kMedianRows; ++k) {
-            const int y = y0 + k;
-            if (((bad >> k) & 15u) && y >= 1 && y + 2 < H) dst[(size_t)y * W + x] = median4_any(src, W, H, x, y);
-        }
+    for (int k = 0; k < kMedianRows + 3; ++k)
+        nans = nans || __builtin_isunordered(r[k][0], r[k][1]) || __builtin_isunordered(r[k][2], r[k][3]);
+    if (__any(nans)) median_column<true>(r, dst, W, H, x, y0, mine);
+    else median_column<false>(r, dst, W, H, x, y0, mine);
 }
 
 #define AMH_LAUNCH_F(...)                \
