@@ -43,20 +43,20 @@ VALU_PEAK_OPS = 256 * 128 * 2.4e9
 # for 262144 KiB read -> x2.0, WRITE_SIZE 262144 KiB for 262144 KiB written -> x1.0); summary in
 # profiles/pass_kernel_1920x1280_n10_traffic.md and pass_kernel_3200x2130_n20_fp16_traffic.md.  Per workload,
 # tile rows and tile order (0 XCD bands, 1 hardware order), and valid only for the kernel source they were taken on.
-PASS_TRAFFIC = {"by_workload": {"1920x1280_n10": {(4, 0): {"fetch_kib": 379068.0, "write_kib": 74663.7},
-                                                  (4, 1): {"fetch_kib": 2112540.0, "write_kib": 71299.2},
-                                                  (2, 0): {"fetch_kib": 450554.0, "write_kib": 79730.2},
-                                                  (2, 1): {"fetch_kib": 2094850.0, "write_kib": 75318.9}},
-                                "3200x2130_n20": {(3, 0): {"fetch_kib": 6408310.0, "write_kib": 220478.0},
-                                                  (3, 1): {"fetch_kib": 24498800.0, "write_kib": 202351.0}}},
+PASS_TRAFFIC = {"by_workload": {"1920x1280_n10": {(4, 0): {"fetch_kib": 375101.0, "write_kib": 74609.6},
+                                                  (4, 1): {"fetch_kib": 2113110.0, "write_kib": 71299.2},
+                                                  (2, 0): {"fetch_kib": 447375.0, "write_kib": 79700.4},
+                                                  (2, 1): {"fetch_kib": 2088730.0, "write_kib": 75318.9}},
+                                "3200x2130_n20": {(3, 0): {"fetch_kib": 6467800.0, "write_kib": 220565.0},
+                                                  (3, 1): {"fetch_kib": 24522300.0, "write_kib": 202351.0}}},
                 "fetch_scale": 2.0, "write_scale": 1.0,
-                "kernel_sha256": "cbac54ce6a06c422369a22d2a971104762726ccc6c8c349315a8286299fccdb4"}
+                "kernel_sha256": "16b9f13833c7e8228edbb88ed70b39dc4fc820350bfaba67175210545ebc808b"}
 
 
 # The same two counters for the fusion kernel of one reference view (11 views of 1920x1280, mean over the
 # 44 dispatches of one bench.py --fusion --steps 1 --warmup 0 run); profiles/fuse_kernel_1920x1280_v11.md.
-FUSE_TRAFFIC = {"fetch_kib": 102393.0, "write_kib": 38211.9, "fetch_scale": 2.0, "write_scale": 1.0,
-                "source_sha256": "dfd4f0762ddeb6d267a0546662e5489158f7f97b2acc852b344f51c7f5dab300"}
+FUSE_TRAFFIC = {"fetch_kib": 102389.6, "write_kib": 38203.5, "fetch_scale": 2.0, "write_scale": 1.0,
+                "source_sha256": "068a20ff82af0f8cceee65886ea4fb0fbe0a0f5608bbd41e196366c98869f5b6"}
 
 
 def fuse_traffic_bytes():

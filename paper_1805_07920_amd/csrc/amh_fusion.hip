@@ -322,7 +322,7 @@ __device__ __forceinline__ void order2(float &a, float &b) {
 // is in, neighbouring rows are merged into sorted eights once (9 exchanges) for the 2 windows that use the pair, and the two
 // middle values of a window are the largest of the 8 smaller ones and the smallest of the 8 larger ones of two sorted eights
 // A, B, min / max(A[i], B[7 - i]): 58 minima and maxima per pixel where sorting the 16 values takes 160, 5.5 loads instead
-// of 16.  1920x1280: 35.0 -> 10.1 us (bytes alone 3.9 us at the copy rate).
+// of 16.  1920x1280: 35.0 -> 10.6 us (bytes alone 3.9 us at the copy rate).
 // Where a wave holds NaN, they are +inf to the sorts and counted by row; the middle of a window that has some is among its 8
 // smaller ones, sorted with 12 exchanges more.  (Sorting such windows' 16 values afterwards, a lane's 8 in a row, took up to
 // three times the time of one pixel to a lane.)
