@@ -28,9 +28,10 @@ constexpr int kDefaultTileRows = 4;
 constexpr int tile_waves(int rows) { return rows == 2 ? 2 : 4; }
 // A reference with at most this many 4-row tiles of a colour takes one-row tiles: fewer workgroups than the card's 256
 // CUs leave most of them idle, and a pass lasts as long as one workgroup's chain of evaluations, which four waves on
-// one row shorten.  3 iterations with refinement, 4-row (14 sources: 3-row) and one-row tiles, us, for 4, 8 and 14
-// sources: 192 tiles (128x96) 313 / 256, 405 / 321, 489 / 413; 256 tiles (128x128) 324 / 274, 409 / 338, 566 / 453; 300
-// tiles (160x120) 348 / 376, 463 / 455, 557 / 587; 494 tiles (200x150) 350 / 432, 465 / 549, 646 / 715.
+// one row shorten.  3 iterations with refinement, 4-row (14 sources: 3-row) and one-row tiles, us, for 2, 4, 8
+// and 14 sources: 192 tiles (128x96) 237 / 205, 338 / 246, 439 / 342, 504 / 438; 256 tiles (128x128) 241 / 212, 330 / 255,
+// 429 / 355, 568 / 475; 300 tiles (160x120) 276 / 300, 343 / 342, 459 / 464, 562 / 588; 494 tiles (200x150) 273 / 345,
+// 400 / 410, 475 / 561, 667 / 718.
 constexpr int kSmallTiles = 256;
 
 // One source view relative to the current reference (Sec. 3.3: plane-induced warp).

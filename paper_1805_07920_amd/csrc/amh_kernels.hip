@@ -1488,7 +1488,9 @@ __device__ __forceinline__ void ablation_body(const PassArgs &a, int L, unsigned
 //   - A refinement candidate is scored on the pixel's most important view
 //     first; the weighted costs are not negative, so a candidate whose cost on
 //     that view alone reaches the kept plane's is out (rounding is monotone:
-//     the sum in view order cannot come out below one of its terms).
+//     the sum in view order cannot come out below one of its terms).  Where
+//     the candidates' pairs on all views are few (kAtOnce) they are scored
+//     together, and a candidate is out afterwards.
 //
 // Work items.  A full chunk of 64 hypotheses is scored view by view, the
 // view's constants in scalar registers and its texels addressed from a scalar
@@ -1512,6 +1514,12 @@ constexpr int kFullChunk = 53;
 // and those of S_{t-1} that left it, or all views where there is none: with 4 nearly every view does, and scoring them later
 // would only add a stage (8 views: the same time either way; 10 views: later is 1.5 % faster).
 constexpr int kOwnFirst = 4;
+// Up to this many (candidate, view) pairs per wave few_pass_kernel (kOwnFirst views at most) refines in one stage: two,
+// each with a barrier and half of the waves idle, last longer than the evaluations that the first would save.  3 iterations
+// (3 candidates a pixel), in two stages / one, us: 128x96 (one-row tiles) with 2 sources 230 / 204, with 4 276 / 247, with 2
+// in float16 255 / 223; 320x240 (32 pixels on 4 waves) with 2 sources, 192 pairs, 506 / 470, with 3, 288 pairs, 538 / 516;
+// 1280x960 with 2 4635 / 4375, with 3 5238 / 5306 (float16 5685 / 5567), with 4, 384 pairs, 6089 / 6466.
+constexpr int kAtOnce = 80;
 constexpr int kPassTileW = 2 * kPix + 10;
 constexpr int kNoRow = 0xff;
 // a pair: pixel of the workgroup (6 bits), view (5), candidate (3)
@@ -1546,6 +1554,10 @@ struct HalfLds {
     gf4 *u;               // [2][pixel] the refinement's draws: perturbation, random (t >= 3)
 };
 
+// row length of psi, which the pair lists replace: up to kOwnFirst views there may be 6 candidates of a pixel on all views
+// in them, 2 bytes each
+__host__ __device__ constexpr int psi_row(int n) { return n <= kOwnFirst ? 3 * n : n; }
+
 // Offsets for a tile of `rows` image rows and n views.  The refinement's pair list of a row (6 candidates x 8
 // pixels x N views, 2 bytes each) takes the end of ms past the results and the psi block after it.
 __host__ __device__ inline size_t half_layout(int n, int rows, size_t off[18]) {
@@ -1557,7 +1569,7 @@ __host__ __device__ inline size_t half_layout(int n, int rows, size_t off[18]) {
     off[2] = o; o = align16(o + sizeof(float4) * H);
     off[3] = o; o = align16(o + sizeof(QLds) * H);
     off[4] = o; o = align16(o + sizeof(float) * (n <= kOwnFirst ? H + P : H) * nl);
-    off[5] = o; o = align16(o + sizeof(float) * P * nl);
+    off[5] = o; o = align16(o + sizeof(float) * P * psi_row(n));
     off[6] = o; o = align16(o + sizeof(float) * P * nl);
     off[7] = o; o = align16(o + sizeof(unsigned short) * (H + P));
     off[8] = o; o = align16(o + H);
@@ -1761,16 +1773,18 @@ __device__ __forceinline__ QLds q_lds(const PlaneQ &q) { return QLds{q.ok ? q.q0
 
 // tid: threadIdx.x.  Registers: the float32 build has 128 for 4 waves on a SIMD and needs all of them in the evaluation;
 // what the pixel's own lanes need in a stage of its row and lane is derived anew there, and nothing is spilled.
-template <int HALF, int ROWS>
+// VIEWS: what the kernel is built for; one for any number refines in two stages.
+enum Views { kAnyViews, kFewViews, kManyViews };  // few: up to kOwnFirst
+template <int HALF, int ROWS, Views VIEWS>
 __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned char *smem, int tid) {
     constexpr int WAVES = tile_waves(ROWS);
     static_assert(ROWS <= WAVES && ROWS <= 4, "a wave per row, 32 pixels at most");
     const int N = a.n_src;
     const HalfLds S = carve_half(smem, N, ROWS);
     constexpr int P = kPix * ROWS, H = 8 * P;  // pixels, propagated hypotheses
-    const bool own_first = N <= kOwnFirst;
+    const bool own_first = VIEWS == kAnyViews ? N <= kOwnFirst : VIEWS == kFewViews;
     const int HV = own_first ? H + P : H;      // costs of a view
-    const int NL = N < 3 ? 3 : N;              // row length of psi (room for the pair lists)
+    const int NL = psi_row(N);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ty = L / a.tiles_x, tx = L - ty * a.tiles_x;
     const int y0 = ty * ROWS, x0 = tx * 2 * kPix;
@@ -1918,11 +1932,12 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
 
     // (4)-(8): pairs of a hypothesis and a view, the view per lane.  Stage 0: the hypotheses past the last chunk;
     // 1: the own planes on the views that carry weight; 2: the refinement candidates on the most important view;
-    // 3: those still in the running on the others.  A pair of stages 1..3 lies in the list of the wave that
-    // owns the pixel.
+    // 3: those still in the running on the others, or with at_once (no stage 2) all on all that carry weight.  A pair of
+    // stages 1..3 lies in the list of the wave that owns the pixel.
     const int rest0 = n_chunks * 64, n_rest = max(n_hyp - rest0, 0);
     const uint32_t div_rest = n_rest ? ((1u << 18) + n_rest - 1) / n_rest : 0u;  // exact: i n_rest < 2^18
     const int ncand = a.t >= 3 ? 6 : 3;
+    const bool at_once = VIEWS == kFewViews && ncand * P * N <= kAtOnce * WAVES;
     int n_scored = n_hyp * N;  // evaluations computed by the workgroup
     float bcost = 0.f;  // cost of the kept hypothesis
     int bcand = 6;      // its slot in cand
@@ -1968,7 +1983,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                         lo = upto[k];
                     }
                 const unsigned short *list =
-                    stage < 3 ? reinterpret_cast<const unsigned short *>(S.psi + w * kPix * NL)
+                    stage < 3 || at_once ? reinterpret_cast<const unsigned short *>(S.psi + w * kPix * NL)
                               : reinterpret_cast<const unsigned short *>(S.ms + 6 * N * P) + w * 6 * kPix * N;
                 const int d = list[i - lo];
                 hp = d & kPairPix;
@@ -2037,7 +2052,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
             if (stage == 1 && !m.refine) break;
             if (stage == 0 && own_first) {
                 if (!m.refine) break;
-                ++stage;
+                stage += at_once ? 2 : 1;
             }
             __syncthreads();
             continue;
@@ -2262,44 +2277,55 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, int L, unsigned cha
                 if (m.refine && row == 6) S.cand[pi * 7 + 6] = to_gf4(best);
             }
             if (!m.refine) break;
-            const unsigned long long has = __ballot(pix_ok && row < ncand);
-            if (pix_ok && row < ncand) {
+        }
+        // (8) continued: the candidates' pairs of the next stage
+        const bool cand = stage > 0 && pix_ok && row < ncand;
+        if (stage == 1 && !at_once) {
+            const unsigned long long has = __ballot(cand);
+            if (cand) {
+                const uint32_t act = S.act[pi];
                 const int vt = S.vt[pi];
                 const int j = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
                 list[__popcll(has & ((1ull << lane) - 1ull))] = (unsigned short)(pi | (j << kPairView) | (row << kPairCand));
             }
             if (lane == 0) S.count[ROWS + wave] = __popcll(has);
-        } else if (stage == 2) {
-            // candidates still in the running: their pairs with the pixel's other views
-            const uint32_t act = S.act[pi];
-            unsigned short *list3 = reinterpret_cast<unsigned short *>(S.ms + 6 * N * P) + wave * 6 * kPix * N;
-            uint32_t others = 0;
-            if (pix_ok && row < ncand) {
+        } else if (stage > 0) {
+            uint32_t act = cand ? S.act[pi] : 0u;
+            if (cand && stage == (at_once ? 3 : 2)) {
+                // in the running by the most important view?
                 const int vt = S.vt[pi];
                 const int j0 = vt >= 0 && ((act >> vt) & 1u) ? vt : __builtin_ctz(act);
                 const float r0 = S.ms[(pi * 6 + row) * N + __popc(act & ((1u << j0) - 1u))];
-                others = act & ~(1u << j0);
+                act &= ~(1u << j0);
                 if (!(weighted_cost(r0) / S.wsum[pi] < bcost)) {
                     // out; its other evaluations are short too where its plane is out of range
                     if (r0 < 0.f)
                         atomicAdd(&S.nshort[wave],
-                                  reinterpret_cast<const QLds *>(S.pl + pi * 8)[row].q0 < 0.0 ? 1u + __popc(others) : 1u);
+                                  reinterpret_cast<const QLds *>(S.pl + pi * 8)[row].q0 < 0.0 ? 1u + __popc(act) : 1u);
                     S.ms[(pi * 6 + row) * N] = __builtin_nanf("");
-                    others = 0;
+                    act = 0;
                 }
             }
-            // exclusive prefix of the wave's pair counts
-            int pre = __popc(others);
+            if (stage < 3) {  // 1 or 2
+                // pairs with the other views, of candidates still in the running; with at_once all
+                unsigned short *next = stage == 2 ? reinterpret_cast<unsigned short *>(S.ms + 6 * N * P) + wave * 6 * kPix * N
+                                                  : list;
+                // exclusive prefix of the wave's pair counts
+                int pre = __popc(act);
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int u = __shfl_up(pre, o, 64);
-                if (lane >= o) pre += u;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int u = __shfl_up(pre, o, 64);
+                    if (lane >= o) pre += u;
+                }
+                if (lane == 63) S.count[ROWS + wave] = pre;
+                pre -= __popc(act);
+                for (uint32_t rest = act; rest; rest &= rest - 1u)
+                    next[pre++] = (unsigned short)(pi | (__builtin_ctz(rest) << kPairView) | (row << kPairCand));
+                stage = 2;  // all pairs listed: no stage 2
             }
-            if (lane == 63) S.count[ROWS + wave] = pre;
-            pre -= __popc(others);
-            for (uint32_t rest = others; rest; rest &= rest - 1u)
-                list3[pre++] = (unsigned short)(pi | (__builtin_ctz(rest) << kPairView) | (row << kPairCand));
-        } else if (stage == 3 && pix_ok) {
+        }
+        if (stage == 3 && at_once) wave_sync();
+        if (stage == 3 && pix_ok) {
             const uint32_t act = S.act[pi];
             const int nw = __popc(act);
             const float wsum = S.wsum[pi];
@@ -2371,7 +2397,18 @@ void pass_kernel(PassArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = tile_of_block(a.n_tiles, a.order);
     if (L < 0) return;
-    pass_body<HALF, ROWS>(a, L, smem, (int)threadIdx.x);
+    pass_body<HALF, ROWS, ROWS == 2 ? kAnyViews : kManyViews>(a, L, smem, (int)threadIdx.x);
+}
+
+// ... with up to kOwnFirst views: what pass_body does for them alone is out of the other kernel, which is 0.5 to 1 %
+// faster without.  (Two-row tiles: pass_kernel has both, as this build of the float32 ones would spill a register.)
+template <int HALF, int ROWS>
+__global__ __launch_bounds__(64 * tile_waves(ROWS)) __attribute__((amdgpu_waves_per_eu(AMH_PASS_WAVES_PER_EU)))
+void few_pass_kernel(PassArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int L = tile_of_block(a.n_tiles, a.order);
+    if (L < 0) return;
+    pass_body<HALF, ROWS, kFewViews>(a, L, smem, (int)threadIdx.x);
 }
 
 template <int HALF, int ROWS>
@@ -2484,7 +2521,7 @@ void batch_kernel(BatchPhaseArgs b) {
     const int j = b.job_of[lo];
     const BatchJobDev &J = b.jobs[j];
     const PassArgs a = batch_pass_args(b, J, ROWS);
-    pass_body<HALF, ROWS>(a, __builtin_amdgcn_readfirstlane(L), smem, (int)threadIdx.x);
+    pass_body<HALF, ROWS, kAnyViews>(a, __builtin_amdgcn_readfirstlane(L), smem, (int)threadIdx.x);
     batch_stamp(b, lo, j, J.n_tiles, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
@@ -2607,7 +2644,7 @@ void persist_kernel(const PersistArgs *__restrict__ Pg) {
             a.conf_min = P->conf_min;
             a = make_uniform(a);
             a.views = P->views + __builtin_amdgcn_readfirstlane(J.view_off);
-            pass_body<HALF, ROWS>(a, L, smem, thread_again(wave));
+            pass_body<HALF, ROWS, kAnyViews>(a, L, smem, thread_again(wave));
             // per-job completion stamp of the job's last half-pass
             const PersistArgs *P2 = opaque(Pg);
             if (P2->phases[ph].is_last[lo]) {
@@ -2867,6 +2904,12 @@ template <int ROWS>
 static void launch_pass_rows(const PassArgs &a, int half, hipStream_t s) {
     const dim3 grid(grid_for(a.n_tiles)), block(64 * tile_waves(ROWS));
     const size_t lds = pass_lds_bytes(a.n_src, ROWS);
+    if constexpr (ROWS == 1 || ROWS == 4)
+        if (a.n_src <= kOwnFirst) {
+            if (half) AMH_LAUNCH((few_pass_kernel<1, ROWS>), grid, block, lds, s, a);
+            else AMH_LAUNCH((few_pass_kernel<0, ROWS>), grid, block, lds, s, a);
+            return;
+        }
     if (half) AMH_LAUNCH((pass_kernel<1, ROWS>), grid, block, lds, s, a);
     else AMH_LAUNCH((pass_kernel<0, ROWS>), grid, block, lds, s, a);
 }
@@ -2887,7 +2930,7 @@ hipError_t launch_pass(const PassArgs &a, int half, hipStream_t s) {
     } else {
         if (a.rows == 1) launch_pass_rows<1>(a, half, s);
         else if (a.rows == 2) launch_pass_rows<2>(a, half, s);
-        else if (a.rows == 3) launch_pass_rows<3>(a, half, s);
+        else if (a.rows == 3 && a.n_src > kOwnFirst) launch_pass_rows<3>(a, half, s);
         else if (a.rows == 4) launch_pass_rows<4>(a, half, s);
         else return hipErrorInvalidValue;
     }
