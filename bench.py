@@ -43,14 +43,14 @@ VALU_PEAK_OPS = 256 * 128 * 2.4e9
 # for 262144 KiB read -> x2.0, WRITE_SIZE 262144 KiB for 262144 KiB written -> x1.0); summary in
 # profiles/pass_kernel_1920x1280_n10_traffic.md and pass_kernel_3200x2130_n20_fp16_traffic.md.  Per workload,
 # tile rows and tile order (0 XCD bands, 1 hardware order), and valid only for the kernel source they were taken on.
-PASS_TRAFFIC = {"by_workload": {"1920x1280_n10": {(4, 0): {"fetch_kib": 375101.0, "write_kib": 74609.6},
-                                                  (4, 1): {"fetch_kib": 2113110.0, "write_kib": 71299.2},
-                                                  (2, 0): {"fetch_kib": 447375.0, "write_kib": 79700.4},
-                                                  (2, 1): {"fetch_kib": 2088730.0, "write_kib": 75318.9}},
-                                "3200x2130_n20": {(3, 0): {"fetch_kib": 6467800.0, "write_kib": 220565.0},
-                                                  (3, 1): {"fetch_kib": 24522300.0, "write_kib": 202351.0}}},
+PASS_TRAFFIC = {"by_workload": {"1920x1280_n10": {(4, 0): {"fetch_kib": 379787.0, "write_kib": 74695.2},
+                                                  (4, 1): {"fetch_kib": 2120830.0, "write_kib": 71299.2},
+                                                  (2, 0): {"fetch_kib": 450681.0, "write_kib": 79716.3},
+                                                  (2, 1): {"fetch_kib": 2093700.0, "write_kib": 75318.9}},
+                                "3200x2130_n20": {(3, 0): {"fetch_kib": 6413780.0, "write_kib": 220469.0},
+                                                  (3, 1): {"fetch_kib": 24432300.0, "write_kib": 202351.0}}},
                 "fetch_scale": 2.0, "write_scale": 1.0,
-                "kernel_sha256": "16b9f13833c7e8228edbb88ed70b39dc4fc820350bfaba67175210545ebc808b"}
+                "kernel_sha256": "c17b66cacaea0214e309c0064ed7c30ef7117d566b0a377c3ab672a6332facf3"}
 
 
 # The same two counters for the fusion kernel of one reference view (11 views of 1920x1280, mean over the
